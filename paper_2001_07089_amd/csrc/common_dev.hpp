@@ -50,6 +50,25 @@ __device__ inline int wave_max_i(int v)
     return v;
 }
 
+// Runs of consecutive lanes with the same cell c (padding lanes: real false,
+// distinct negative c): the first lane of a run reserves the whole run in
+// cell_count with one atomic.  Returns the run's first rank in its cell and
+// the run's first lane.  All lanes of the wavefront take part.
+__device__ inline int run_reserve(int32_t *cell_count, int c, bool real, int &first)
+{
+    const int lane = lane_id();
+    const int prev = __shfl_up(c, 1, 64);
+    const bool head = (lane == 0) || (prev != c);
+    const uint64_t heads = __ballot(head);
+    const uint64_t below = lane == 63 ? ~0ull : ((1ull << (lane + 1)) - 1ull);
+    first = 63 - __clzll((long long)(heads & below));  // head of my run
+    const uint64_t above = heads & ~below;
+    const int next = above ? __ffsll((long long)above) - 1 : 64;  // head of the next run
+    int base = 0;
+    if (head && real) base = atomicAdd(&cell_count[c], next - lane);
+    return __shfl(base, first, 64);
+}
+
 // u32 fixed-point coordinate of u in [0, L): round(u * 2^32 / L) mod 2^32.
 __device__ inline uint32_t to_fix(double u, double invL)
 {

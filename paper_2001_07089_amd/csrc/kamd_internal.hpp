@@ -139,14 +139,14 @@ struct Dev {
     RepDyn *dyn;
     uint32_t *err;
     int32_t *counters;    // [0] = rebuilds, [1] = device step counter
-    // RDF scratch; rdf_grid[r] = {cells per edge, first cell, cells} of the
-    // last measurement's grid; rdf_count / rdf_start hold rdf_cells_cap cells
+    // RDF scratch; rdf_grid[r] = {cells per edge, first cell, cells, flags
+    // (RDF_ATOMICS, RDF_NONFINITE)} of the last measurement's grid;
+    // rdf_plan[r] = {first histogram block, blocks, splits of the stencil,
+    // ticket}; rdf_count / rdf_start hold rdf_cells_cap cells
     int32_t *rdf_cell_of, *rdf_rank, *rdf_count, *rdf_start;
     double4 *rdf_pos;
-    int4 *rdf_grid;
+    int4 *rdf_grid, *rdf_plan;
     int64_t rdf_cells_cap;
-    const int32_t *rdf_block_rep;
-    const int32_t *rdf_block_start;
     // MSD origins [msd_slots][3][n_total] in caller order
     double *origin;
     int32_t msd_slots;
@@ -226,8 +226,9 @@ hipError_t launch_store_pe_w(const Dev &d, double *out, hipStream_t s);
 hipError_t launch_sample(const Dev &d, int mask, hipStream_t s);
 
 // Grid set-up on the device (k_rdf_setup), counting sort by RDF cell.
-hipError_t launch_rdf_prepare(const Dev &d, double rmax, hipStream_t s);
-hipError_t launch_rdf(const Dev &d, double dr, int nbins, int nblocks, uint64_t *hist, hipStream_t s);
+hipError_t launch_rdf_prepare(const Dev &d, double rmax, int nbins, int max_n, hipStream_t s);
+// scratch: 9 n_total doubles that hold nothing (partial histograms).
+hipError_t launch_rdf(const Dev &d, double dr, int nbins, uint64_t *hist, double *scratch, hipStream_t s);
 hipError_t launch_msd_set(const Dev &d, int slot, hipStream_t s);
 hipError_t launch_msd_measure(const Dev &d, int slot, hipStream_t s);
 hipError_t launch_msd_finish(const Dev &d, double *out, hipStream_t s);

@@ -191,19 +191,10 @@ __device__ inline void assign_wave(const Dev &d, int w)
         c = CELL_SUBX * (S.cell0 + (cz * nc + fix_cell(m.y, nc)) * nc) + fix_cell(m.x, CELL_SUBX * nc);
         d.cell_of[s] = c;
     }
-    // Runs of consecutive lanes with the same cell (the slots are still in the
-    // order of the previous build, so most neighbours share a cell): the first
-    // lane of a run reserves the whole run with one atomic.
-    const int prev = __shfl_up(c, 1, 64);
-    const bool head = (lane == 0) || (prev != c);
-    const uint64_t heads = __ballot(head);
-    const uint64_t below = lane == 63 ? ~0ull : ((1ull << (lane + 1)) - 1ull);
-    const int first = 63 - __clzll((long long)(heads & below));  // head of my run
-    const uint64_t above = heads & ~below;
-    const int next = above ? __ffsll((long long)above) - 1 : 64;  // head of the next run
-    int base = 0;
-    if (head && real) base = atomicAdd(&d.cell_count[c], next - lane);
-    base = __shfl(base, first, 64);
+    // the slots are still in the order of the previous build, so most
+    // neighbours share a cell
+    int first;
+    const int base = run_reserve(d.cell_count, c, real, first);
     if (real) d.rank[s] = base + (lane - first);
 }
 

@@ -35,7 +35,6 @@ struct Plan {
 // Sizes of the fixed part of a workspace (independent of the list parameters).
 struct Shape {
     size_t np = 0, nt = 0, nwaves = 0, nrep = 0, nseg = 0;
-    size_t rdf_blocks = 0;  // blocks of the RDF histogram kernel (BLOCK particles of one replica each)
     size_t rdf_cells = 0;   // RDF cell capacity: 2 n + 64 per replica
     size_t ring = 0;        // rows of the observables ring, all replicas
     size_t msd_slots = 16;
@@ -50,7 +49,6 @@ struct kamd_ctx {
     std::vector<SegInfo> segs;
     std::vector<RepInfo> rinfo;
     std::vector<int32_t> wave_seg;
-    std::vector<int32_t> rdf_block_rep, rdf_block_start;
     kamd_state st{};
     hipStream_t stream = nullptr;
     int device = 0;
@@ -365,10 +363,7 @@ static Shape shape_of(const kamd_config *cfg, const kamd_replica *reps, int n_re
     z.nwaves = P.nwaves;
     z.nrep = n_rep;
     z.nseg = P.segs.size();
-    for (int r = 0; r < n_rep; ++r) {
-        z.rdf_blocks += (reps[r].n + BLOCK - 1) / BLOCK;
-        z.rdf_cells += 2 * (size_t)reps[r].n + 64;
-    }
+    for (int r = 0; r < n_rep; ++r) z.rdf_cells += 2 * (size_t)reps[r].n + 64;
     z.ring = (size_t)ring_rows(cfg) * n_rep;
     z.msd_slots = msd_slots_of(cfg);
     z.fp64 = cfg->precision == KAMD_PREC_FP64;
@@ -384,7 +379,6 @@ struct CtxBufs {
     int32_t *img_tmp = nullptr;
     RepDyn *dyn_snap = nullptr;
     int32_t *cnt_snap = nullptr;
-    int32_t *rdf_block_rep = nullptr, *rdf_block_start = nullptr;
 };
 
 // The fixed part: slot-order state and its permutation scratch, layout
@@ -439,8 +433,7 @@ static void carve_fixed(Dev &d, CtxBufs &b, const Shape &z, Carve &k)
     d.rdf_count = k.take<int32_t>(z.rdf_cells);
     d.rdf_start = k.take<int32_t>(z.rdf_cells);
     d.rdf_grid = k.take<int4>(z.nrep);
-    b.rdf_block_rep = k.take<int32_t>(z.rdf_blocks);
-    b.rdf_block_start = k.take<int32_t>(z.rdf_blocks);
+    d.rdf_plan = k.take<int4>(z.nrep);
     b.state_tmp = k.take<double>(9 * nt);
     b.img_tmp = k.take<int32_t>(3 * nt);
     b.dyn_snap = k.take<RepDyn>(z.nrep);
@@ -548,8 +541,6 @@ static void bind_workspace(kamd_ctx *c, const Plan &P)
     c->img_tmp = b.img_tmp;
     c->dyn_snap = b.dyn_snap;
     c->cnt_snap = b.cnt_snap;
-    d.rdf_block_rep = b.rdf_block_rep;
-    d.rdf_block_start = b.rdf_block_start;
     Carve kl;
     kl.base = c->ws + c->list_off;
     carve_list(d, P, kl);
@@ -1099,16 +1090,6 @@ extern "C" int md_init(kamd_ctx **out, const kamd_config *cfg, const kamd_replic
             for (int i = 0; i < S.n; ++i) ids[S.slot0 + i] = (int32_t)(first + i);
         }
         HIPCHK(c, hipMemcpyAsync(c->d.id, ids.data(), 4 * ids.size(), hipMemcpyHostToDevice, c->stream));
-        // RDF block table
-        for (int q = 0; q < n_rep; ++q)
-            for (int i = 0; i < c->reps[q].n; i += BLOCK) {
-                c->rdf_block_rep.push_back(q);
-                c->rdf_block_start.push_back((int32_t)(c->reps[q].offset + i));
-            }
-        HIPCHK(c, hipMemcpyAsync((void *)c->d.rdf_block_rep, c->rdf_block_rep.data(), 4 * c->rdf_block_rep.size(),
-                                 hipMemcpyHostToDevice, c->stream));
-        HIPCHK(c, hipMemcpyAsync((void *)c->d.rdf_block_start, c->rdf_block_start.data(),
-                                 4 * c->rdf_block_start.size(), hipMemcpyHostToDevice, c->stream));
         const int64_t nt = P.n_total;
         if (cfg->init_mode == KAMD_INIT_GIVEN) {
             const double *a[9] = {st->x, st->y, st->z, st->vx, st->vy, st->vz, nullptr, nullptr, nullptr};
@@ -1240,15 +1221,17 @@ extern "C" int md_rdf(kamd_ctx *c, double dr, int32_t n_bins, uint64_t *hist_dev
     if (!(dr > 0.0) || !std::isfinite(dr) || n_bins <= 0 || !hist_dev) return fail(c, KAMD_EINVAL, "bad RDF arguments");
     if (3 * (size_t)n_bins * 4 > 60 * 1024) return fail(c, KAMD_EINVAL, "n_bins too large (max 5120)");
     const double rmax = n_bins * dr;
+    int max_n = 0;
     for (size_t r = 0; r < c->reps.size(); ++r) {
+        max_n = std::max(max_n, c->reps[r].n);
         const double L = c->reps[r].box;
         if (rmax > 0.5 * L * (1.0 + 1e-12))
             return fail(c, KAMD_EINVAL, "n_bins*dr = %.9g exceeds L/2 = %.9g (replica %zu)", rmax, 0.5 * L, r);
     }
     // the grid of each replica is chosen on the device, inside the capacity
     // the workspace holds, so nothing here waits or allocates
-    HIPCHK(c, launch_rdf_prepare(c->d, rmax, c->stream));
-    HIPCHK(c, launch_rdf(c->d, dr, n_bins, (int)c->rdf_block_rep.size(), hist_dev, c->stream));
+    HIPCHK(c, launch_rdf_prepare(c->d, rmax, n_bins, max_n, c->stream));
+    HIPCHK(c, launch_rdf(c->d, dr, n_bins, hist_dev, c->state_tmp, c->stream));
     return KAMD_OK;
 }
 
