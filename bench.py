@@ -172,12 +172,15 @@ def drift_stats(rows, n):
     return d
 
 
-def kernel_name(precision, windows=0, wg=256):
+def kernel_name(precision, windows=0, wg=256):  # at the headline's size
     """The step kernel of NVE steps (forces fused with the closing half kick
     and the next drift), with its template arguments: FIXED, ENERGY, KD,
-    then STAGE and waves per block for the mixed precisions."""
+    then STAGE and waves per block for the unsplit mixed kernel, waves per list
+    for the others."""
     if precision == "fp64":
         return f"k_force_fp64<false,true,{wg // 64}>"
+    if precision == "mixed_fixed" and not windows:
+        return "k_force_split<true,false,true,2>"  # two wavefronts share a list
     fixed = "true" if precision == "mixed_fixed" else "false"
     return f"k_force_mixed<{fixed},false,true,{'true' if windows else 'false'},{wg // 64}>"
 

@@ -385,7 +385,9 @@ int md_set_list_params(kamd_ctx *ctx, double skin, int32_t cell_div);
  * they fit (the list then stores 16-bit offsets into them), 0 gathers every
  * neighbour from global memory (the default); a change forces a rebuild at
  * the next step.  wg_size: threads per block of the step kernel, 64, 128 or 256
- * (0 keeps the current one; 256 by default).  The forces are the same either
+ * (0 keeps the current one; 256 by default); it applies with windows and in
+ * MIXED beyond half a million particles (elsewhere several wavefronts share
+ * a list, as many as the size calls for).  The forces are the same either
  * way (bit for bit with MIXED_FIXED).  Drops a captured graph.  KAMD_EINVAL
  * for windows = 1 in FP64.  Syncs. */
 int md_set_force_kernel(kamd_ctx *ctx, int32_t windows, int32_t wg_size);

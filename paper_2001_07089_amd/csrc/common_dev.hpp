@@ -123,20 +123,35 @@ __device__ inline double wrap_img(double u, double L, double invL, int32_t &img)
     return u;
 }
 
+// What the position half of a step reads of slot s besides v and a.
+struct DriftIn {
+    double r[3];
+    int32_t im[3];
+    uint4 b;  // mirror at the last list build
+};
+__device__ inline DriftIn drift_load(const Dev &d, int s)
+{
+    const int np = d.npad_total;
+    return {{ld_stream(&d.x[s]), ld_stream(&d.y[s]), ld_stream(&d.z[s])},
+            {ld_stream(&d.img[s]), ld_stream(&d.img[np + s]), ld_stream(&d.img[2 * np + s])},
+            ld_stream(&d.mbuild[s])};
+}
+
 // Position half of a velocity-Verlet step for slot s, from the velocity v at
 // the start of the step and the acceleration a: v_h = v + c (a - (xi + xi_a)
 // v), r += dt (v + dt/2 (a - xi v)), wrap into [0, L) counting images.
 // Stores r, v_h and the image counters, writes the new u32 mirror into
 // mirror_out and returns the squared displacement since the last list build
-// in d2.  NVE: xi = xi_a = 0, c = dt/2.
+// in d2, and the new position in in.r.  NVE: xi = xi_a = 0, c = dt/2.
 __device__ inline void drift_core(const Dev &d, int s, const RepInfo &R, double dt, double xi, double xia,
-                                  double c, const double v[3], const double a[3], uint4 *mirror_out, float &d2)
+                                  double c, const double v[3], const double a[3], DriftIn &in, uint4 *mirror_out,
+                                  float &d2)
 {
     const int np = d.npad_total;
     const double L = R.L, invL = R.invL;
-    double r[3] = {ld_stream(&d.x[s]), ld_stream(&d.y[s]), ld_stream(&d.z[s])};
+    double *r = in.r;
     double vn[3];
-    int32_t im[3] = {ld_stream(&d.img[s]), ld_stream(&d.img[np + s]), ld_stream(&d.img[2 * np + s])};
+    int32_t *im = in.im;
     uint32_t q[3];
     bool fin = true;
     double step2 = 0.0;  // squared length of this step's move (runaway check)
@@ -155,9 +170,8 @@ __device__ inline void drift_core(const Dev &d, int s, const RepInfo &R, double 
     st_stream(vn[0], &d.vx[s]); st_stream(vn[1], &d.vy[s]); st_stream(vn[2], &d.vz[s]);
     st_stream(im[0], &d.img[s]); st_stream(im[1], &d.img[np + s]); st_stream(im[2], &d.img[2 * np + s]);
     mirror_out[s] = make_uint4(q[0], q[1], q[2], 0u);  // gathered by the next step: cached
-    const uint4 b = ld_stream(&d.mbuild[s]);
-    const float ex = (float)(int)(q[0] - b.x), ey = (float)(int)(q[1] - b.y),
-                ez = (float)(int)(q[2] - b.z);
+    const float ex = (float)(int)(q[0] - in.b.x), ey = (float)(int)(q[1] - in.b.y),
+                ez = (float)(int)(q[2] - in.b.z);
     const float h = (float)(R.L * 2.3283064365386963e-10);
     d2 = (ex * ex + ey * ey + ez * ez) * (h * h);
     if (!fin) set_err(d.err, KAMD_DEV_NONFINITE);
@@ -169,7 +183,18 @@ __device__ inline void drift_one(const Dev &d, int s, int rep, double dt, double
 {
     const double v[3] = {d.vx[s], d.vy[s], d.vz[s]};
     const double a[3] = {d.ax[s], d.ay[s], d.az[s]};
-    drift_core(d, s, d.rep[rep], dt, xi, xia, c, v, a, mirror_out, d2);
+    DriftIn in = drift_load(d, s);
+    drift_core(d, s, d.rep[rep], dt, xi, xia, c, v, a, in, mirror_out, d2);
+}
+
+// Raise a replica's displacement maximum to m.  Read first: the maximum only
+// grows during the step, so most blocks find it already larger and skip the
+// atomic.
+__device__ inline void disp_push(uint32_t *maxdisp, int r, float m)
+{
+    const uint32_t bits = __float_as_uint(m);
+    const uint32_t cur = __hip_atomic_load(&maxdisp[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (bits > cur) atomicMax(&maxdisp[r], bits);
 }
 
 // Per-replica maximum of the wavefront maxima of one block, one atomicMax per
@@ -188,24 +213,17 @@ __device__ inline void block_disp_max(uint32_t *maxdisp, bool valid, int rep, fl
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        // read first: the maximum only grows during the step, so most blocks
-        // find it already larger and skip the atomic
-        auto push = [&](int r, float m) {
-            const uint32_t bits = __float_as_uint(m);
-            const uint32_t cur = __hip_atomic_load(&maxdisp[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (bits > cur) atomicMax(&maxdisp[r], bits);
-        };
         int r = -1;
         float m = 0.0f;
         for (int k = 0; k < WPB; ++k) {
             if (wrep[k] != r) {
-                if (r >= 0) push(r, m);
+                if (r >= 0) disp_push(maxdisp, r, m);
                 r = wrep[k];
                 m = 0.0f;
             }
             m = fmaxf(m, wmax[k]);
         }
-        if (r >= 0) push(r, m);
+        if (r >= 0) disp_push(maxdisp, r, m);
     }
 }
 
