@@ -76,6 +76,7 @@ struct RepInfo {
     // pair constants in the u32 fixed-point length unit h = L / 2^32
     float rc2_fx[3];       // r_c(ab)^2 / h^2
     float rl2_fx[3];       // (r_c(ab) + skin)^2 / h^2, slightly enlarged
+    int32_t r2c[3];        // bound of the list builder's coarse test, in units of 2^16 h
     float sig2_fx[3];      // sigma(ab)^2 / h^2
     float ir2_lim_fx[3];   // h^2 / r_lim(ab)^2: a pair closer than r_lim has a force whose
                            // 2^-26-unit rounding in MIXED_FIXED is no longer exact
@@ -102,7 +103,8 @@ struct RepDyn {
 
 // All device pointers, passed by value to kernels.
 struct Dev {
-    // slot-order state
+    // slot-order state; the nine arrays follow one another (y = x + npad_total,
+    // ...), and so do those of the permutation scratch
     double *x, *y, *z, *vx, *vy, *vz, *ax, *ay, *az;
     int32_t *img;         // [3][npad_total]
     int32_t *id;          // caller global index or -1
@@ -162,6 +164,8 @@ struct Dev {
     int32_t dim;          // 3, or 2 for a planar system (z = vz = 0)
     int32_t ncells;
     int32_t rows;         // neighbour-list row capacity
+    double box_max;       // largest box edge
+    int32_t rep_waves_max; // wavefronts of the largest replica
     int32_t scan_cps;     // scan chunks (SCAN_CHUNK cells) of the largest segment
     int32_t *chunk_sum;   // [nseg][scan_cps]: particles of each scan chunk (segments of several chunks)
 };

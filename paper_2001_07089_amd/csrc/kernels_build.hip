@@ -471,11 +471,11 @@ constexpr int LIST_WIN = 384;
 // parts whose windows fit are written in the window format; without it the
 // window code is compiled out.
 template <bool STAGE>
-__global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach)
+__global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach, int min_waves)
 {
     __shared__ int32_t stage[WAVES_PER_BLOCK][LIST_STAGE][WAVE];
     __shared__ __attribute__((aligned(16))) uint32_t win_s[WAVES_PER_BLOCK][3][LIST_WIN + LIST_UNROLL];
-    if (d.rb_any[0] == 0) return;
+    if (d.rb_any[0] < min_waves) return;  // nothing to do, or k_rb_list_wide's
     const int w = rb_work_wave(d);  // each XCD walks a contiguous part of the worklist
     if (w < 0) return;
     const SegInfo &S = d.seg[d.wave_seg[w]];
@@ -554,8 +554,8 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach)
         // r + sqrt(3).  Accepting every coarse r2 below that bound squared
         // keeps the list a superset of the exact one; the extra entries lie
         // in a shell sqrt(3) units thick (0.3% more entries at L = 100).
-        const double rc16 = sqrt((double)rl2) * (1.0 / 65536.0) + 1.7320508075688772;
-        const int r2c = (int)ceil(rc16 * rc16) + 1;
+        // r2c = ceil((r + sqrt(3))^2) + 1, from the host.
+        const int r2c = R.r2c[S.type + tj];
         const double rp2 = rp * rp;
         // lowest start and highest end of the lanes' non-empty ranges
         // (x = INT_MAX when no lane has one); all lanes take part
@@ -951,6 +951,344 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach)
     d.nlen[s] = real ? (total - 1) | (n16 << 16) : 0;
 }
 
+// Neighbour lists, a block of LIST_ROWS wavefronts per listed wave: wavefront r
+// takes stencil row r of both partner types.  The lists are those of k_rb_list
+// (one cell per list radius, no windows, coarse test), entry for entry.
+//
+// Why: a wave's lists are a chain of 18 row pieces (bounds, union, staging,
+// scan), and a lone wavefront takes 100 us for it however small the system;
+// on the steps of a batch where a few replicas rebuild it is as long.  Here
+// the rows run side by side.  A wavefront stages the unions of its row's pieces
+// that fit its LDS window (the others it reads from global memory) and tests
+// the candidates 32 at a time into bit masks (five vector operations each);
+// the rows' counts then give every lane the place of its entries, and the
+// accepted ones, about a sixth, go from the masks into an LDS image of the
+// wave's lists (slots relative to the replica's first, 16 bits), which the
+// block writes out 16 bytes a lane.  A wave with rows of more chunks than there
+// are masks, or lists longer than the image, is scanned a second time and
+// stored entry by entry.
+//
+// Bound by latency and, inside its compute unit, by the vector ALU: of 19 us a
+// block, 2.4 are the chain of dependent loads up to the cell ranges, 2.8 the
+// staging, 4.7 the tests and 4.8 the expansion of the middle row.  A rebuild of
+// one to 256 waves takes 27 us, of k_rb_list 100 us.
+constexpr int LIST_ROWS = 9;
+constexpr int WIDE_WIN = 432;     // candidates staged per wavefront
+constexpr int WIDE_CHUNKS = 8;    // masks per wavefront
+constexpr int WIDE_LIST = 192;    // entries of the list image
+constexpr int WIDE_BLOCKS = 512;  // two blocks of nine wavefronts per compute unit
+
+// {m, d} shifted left by one: m with the sign bit of d appended.
+__device__ inline uint32_t push_sign(uint32_t m, int d) { return __builtin_amdgcn_alignbit(m, (uint32_t)d, 31); }
+
+__global__ __launch_bounds__(WAVE * LIST_ROWS) void k_rb_list_wide(Dev d, int max_waves)
+{
+    // the windows (a chunk reads up to 31 past a range), then the list image
+    __shared__ union {
+        uint2 win[LIST_ROWS][WIDE_WIN + 32];
+        uint16_t fin[WIDE_LIST + 1][WAVE];  // and a row that takes the rejected
+    } u;
+    __shared__ uint32_t mask_s[LIST_ROWS][WIDE_CHUNKS][WAVE];
+    __shared__ uint16_t rowcnt[2][LIST_ROWS][WAVE];
+    const int nact = d.rb_any[0];
+    if (nact == 0 || nact > max_waves) return;
+    const int nrw = blockDim.x / WAVE;  // rows at most: 9, or 3 of a planar system
+    const int r = threadIdx.x / WAVE, lane = lane_id();
+    const int np = d.npad_total, rows = d.rows;
+    uint2 *wc = u.win[r];
+    uint16_t(*fin)[WAVE] = u.fin;
+    uint32_t(*mk)[WAVE] = mask_s[r];
+    for (int i0 = 0; i0 < nact; i0 += gridDim.x) {
+        const int nb = min((int)gridDim.x, nact - i0);
+        if ((int)blockIdx.x >= nb) return;  // block-uniform
+        const int w = d.rb_wlist[i0 + xcd_block(blockIdx.x, nb)];
+        const int s = w * WAVE + lane;
+        uint4 mi = d.smirror[s];
+        // the sorted state, for its way back at the end: wavefront r takes the
+        // FP64 arrays r, r + nrw, ... and a share of the others
+        double sv[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (k == 0 || nrw == 3) sv[k] = ld_stream(&d.sx[(size_t)(r + 3 * k) * np + s]);
+        const int vi = r < 3 ? ld_stream(&d.simg[r * np + s]) : 0;
+        const SegInfo &S = d.seg[d.wave_seg[w]];
+        const RepInfo &R = d.rep[S.rep];
+        const bool real = (s - S.slot0) < S.n;
+        if (!real) mi = make_uint4(0, 0, 0, 0);
+        const int nc = R.nc, slot0 = R.wave0 * WAVE;
+        const int noff = min(nc, 3);
+        const bool whole = nc < 3;  // every cell of a row is in the stencil
+        const int oz0 = d.dim == 2 ? 0 : -1, nz = d.dim == 2 ? 1 : noff;
+        const bool active = r < nz * noff;
+        const int oz = oz0 + r / noff, oy = -1 + r % noff;
+        const int fx = fix_cell(mi.x, CELL_SUBX * nc);  // x in quarter cells
+        const int cx = fx / CELL_SUBX, qx = fx % CELL_SUBX;
+        const int cy = fix_cell(mi.y, nc), cz = d.dim == 2 ? 0 : fix_cell(mi.z, nc);
+        const uint32_t ixy = (mi.x >> 16) | (mi.y & 0xffff0000u), iz = mi.z >> 16;
+        const int32_t *cstart = d.cell_start, *cend = d.cell_end;
+        // pieces of the lane's row: per partner type the main run of cells and
+        // the end cell that wraps around (see k_rb_list); [st, en) in slots
+        int st_[4], en_[4];
+#pragma unroll
+        for (int tj = 0; tj < 2; ++tj) {
+            const SegInfo &SJ = d.seg[R.seg[tj]];
+            st_[2 * tj] = en_[2 * tj] = st_[2 * tj + 1] = en_[2 * tj + 1] = 0;
+            if (real && active && SJ.n > 0) {
+                const int qz = (cz + oz + nc) % nc, qy = (cy + oy + nc) % nc;
+                const int rowc = SJ.cell0 + (qz * nc + qy) * nc;
+                if (whole) {
+                    st_[2 * tj] = cstart[CELL_SUBX * rowc];
+                    en_[2 * tj] = cend[CELL_SUBX * (rowc + nc) - 1];
+                } else {
+                    const int a = cx - 1, e = cx + 1;
+                    st_[2 * tj] = cstart[a < 0 ? CELL_SUBX * rowc : CELL_SUBX * (rowc + a) + qx];
+                    en_[2 * tj] = cend[e >= nc ? CELL_SUBX * (rowc + nc) - 1 : CELL_SUBX * (rowc + e) + qx];
+                    const bool lw = a < 0;
+                    if (lw || e >= nc) {
+                        st_[2 * tj + 1] = cstart[lw ? CELL_SUBX * (rowc + a + nc) + qx : CELL_SUBX * rowc];
+                        en_[2 * tj + 1] = cend[lw ? CELL_SUBX * (rowc + nc) - 1 : CELL_SUBX * (rowc + e - nc) + qx];
+                    }
+                }
+            }
+        }
+        // base slot of 16-bit entries (the part of the own type), or -1
+        int base = -1;
+        {
+            const SegInfo &SJ = d.seg[R.seg[S.type]];
+            int lo = s, hi = s + 1;
+            if (real) {
+                int z0 = cz + oz0, z1 = cz + oz0 + nz - 1;
+                if (z0 < 0 || z1 >= nc) z0 = 0, z1 = nc - 1;
+                int y0 = cy - 1, y1 = cy - 1 + noff - 1;
+                if (y0 < 0 || y1 >= nc) y0 = 0, y1 = nc - 1;
+                lo = min(lo, cstart[CELL_SUBX * (SJ.cell0 + (z0 * nc + y0) * nc)]);
+                hi = max(hi, cend[CELL_SUBX * (SJ.cell0 + (z1 * nc + y1) * nc + nc) - 1]);
+            }
+            lo = -wave_max_all(-lo);
+            hi = wave_max_all(hi);
+            if (hi - lo <= 65536) base = lo;
+        }
+        // Unions over the lanes, staged one after the other while they fit;
+        // longest range and chunks of each piece.  (The loops over the pieces
+        // stay rolled: the kernel runs for some 20 us, and four copies of its
+        // loops cost more in instruction fetches than the selects do.)
+        auto sel = [](int4 v, int p) __attribute__((always_inline)) {
+            int x = v.x;
+            x = p == 1 ? v.y : x;
+            x = p == 2 ? v.z : x;
+            return p == 3 ? v.w : x;
+        };
+        auto vec = [](const int (&v)[4]) __attribute__((always_inline)) { return make_int4(v[0], v[1], v[2], v[3]); };
+        int lo_[4], off_[4], long_[4], used = 0, chunks = 0;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const bool has = st_[p] < en_[p];
+            long_[p] = wave_max_all(en_[p] - st_[p]);
+            lo_[p] = has ? st_[p] : INT_MAX;
+            lo_[p] = -wave_max_all(-lo_[p]);
+            const int len = wave_max_all(has ? en_[p] : -1) - lo_[p];
+            const bool fits = long_[p] > 0 && used + len <= WIDE_WIN;
+            chunks += (long_[p] + 31) / 32;
+            off_[p] = fits ? used : -1;
+            used += fits ? len : 0;
+        }
+        const int4 st = vec(st_), en = vec(en_), lo = vec(lo_), off = vec(off_), longest = vec(long_);
+#pragma unroll 1
+        for (int p = 0; p < 4; ++p) {
+            const int o = sel(off, p);
+            if (o < 0) continue;
+            int next = used;  // where the next staged piece starts
+            for (int q = 3; q > p; --q) next = sel(off, q) >= 0 ? sel(off, q) : next;
+            const int len = next - o;
+            const uint4 *src = d.smirror + sel(lo, p);
+            for (int e = lane; e < len; e += 2 * WAVE) {
+                const uint4 a = src[e], b = src[min(e + WAVE, len - 1)];
+                wc[o + e] = make_uint2((a.x >> 16) | (a.y & 0xffff0000u), a.z >> 16);
+                if (e + WAVE < len) wc[o + e + WAVE] = make_uint2((b.x >> 16) | (b.y & 0xffff0000u), b.z >> 16);
+            }
+        }
+        const bool masked = chunks <= WIDE_CHUNKS;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // the general path: every candidate of the lane's ranges in slot
+        // order, from global memory: take(part, j) for the accepted ones
+        auto walk = [&](auto take) __attribute__((always_inline)) {
+#pragma unroll 1
+            for (int p = 0; p < 4; ++p) {
+                const int r2c = R.r2c[S.type + (p >> 1)], e = sel(en, p);
+#pragma unroll 1
+                for (int j = sel(st, p); j < e; ++j) {
+                    const uint4 v = d.smirror[j];
+                    if (r2_coarse_below(ixy, iz, (v.x >> 16) | (v.y & 0xffff0000u), v.z >> 16, r2c) < 0) take(p >> 1, j);
+                }
+            }
+        };
+        int cnt0 = 0, cnt1 = 0;
+        if (masked) {
+            int c = 0;
+#pragma unroll 1
+            for (int p = 0; p < 4; ++p) {
+                const int r2c = R.r2c[S.type + (p >> 1)], top = sel(longest, p), o = sel(off, p), l = sel(lo, p);
+                const int a = sel(st, p), len = sel(en, p) - a;
+#pragma unroll 1
+                for (int k = 0; k < top; k += 32, ++c) {
+                    const int n = min(max(len - k, 0), 32);  // candidates of the lane's chunk
+                    const int j = n > 0 ? a + k : l;
+                    const int ng = (min(top - k, 32) + 7) / 8;
+                    uint32_t m = 0;
+                    if (o >= 0) {
+                        const uint2 *v = wc + (o + j - l);
+#pragma unroll 1
+                        for (int g = 0; g < ng; ++g, v += 8)
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) m = push_sign(m, r2_coarse_below(ixy, iz, v[i].x, v[i].y, r2c));
+                    } else {
+                        const uint4 *v = d.smirror + j;
+#pragma unroll 1
+                        for (int g = 0; g < ng; ++g) {
+                            uint4 q[8];  // clamped: a chunk may pass the end of the array
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) q[i] = v[min(8 * g + i, max(n - 1, 0))];
+#pragma unroll
+                            for (int i = 0; i < 8; ++i)
+                                m = push_sign(m, r2_coarse_below(ixy, iz, (q[i].x >> 16) | (q[i].y & 0xffff0000u), q[i].z >> 16, r2c));
+                        }
+                    }
+                    m <<= 32 - 8 * ng;  // candidate i of the chunk in bit 31 - i
+                    m = n > 0 ? m & (0xffffffffu << (32 - n)) : 0u;
+                    mk[c][lane] = m;
+                    cnt0 += p < 2 ? __popc(m) : 0;
+                    cnt1 += p < 2 ? 0 : __popc(m);
+                }
+            }
+        } else {
+            walk([&](int tj, int) __attribute__((always_inline)) {
+                cnt0 += 1 - tj;
+                cnt1 += tj;
+            });
+        }
+        rowcnt[0][r][lane] = (uint16_t)cnt0;
+        rowcnt[1][r][lane] = (uint16_t)cnt1;
+        const bool all_masked = __syncthreads_and(masked) != 0;
+        int at0 = 0, at1 = 0, tot0 = 0, tot1 = 0;
+#pragma unroll 1
+        for (int q = 0; q < nrw; ++q) {
+            const int a = rowcnt[0][q][lane], b = rowcnt[1][q][lane];
+            at0 += q < r ? a : 0;
+            at1 += q < r ? b : 0;
+            tot0 += a;
+            tot1 += b;
+        }
+        int2 kpart, bpart = make_int2(S.type == 0 ? base : -1, S.type == 1 ? base : -1);
+        const bool h0 = bpart.x >= 0, h1 = bpart.y >= 0;
+        const int al0 = h0 ? 2 * LIST_ROW_ALIGN : LIST_ROW_ALIGN, al1 = h1 ? 2 * LIST_ROW_ALIGN : LIST_ROW_ALIGN;
+        kpart.x = (wave_max_all(tot0) + al0 - 1) & -al0;
+        kpart.y = (wave_max_all(tot1) + al1 - 1) & -al1;
+        const int row1 = h0 ? kpart.x / 2 : kpart.x;  // 32-bit words of the A part
+        const int used_rows = row1 + (h1 ? kpart.y / 2 : kpart.y);
+        int32_t *col = d.nbr + list_index(w, rows, 0, lane);
+        if (all_masked && kpart.x + kpart.y <= WIDE_LIST) {  // block-uniform: through the image
+            uint16_t *out = &fin[at0][lane], *dump = &fin[WIDE_LIST][lane];
+            int c = 0;
+#pragma unroll 1
+            for (int p = 0; p < 4; ++p) {
+                const int top = sel(longest, p);
+                if (p == 2) out = &fin[kpart.x + at1][lane];
+                int j = sel(st, p) - slot0;
+#pragma unroll 1
+                for (int k = 0; k < top; k += 32, ++c) {
+                    int m = (int)mk[c][lane];
+                    const int ng = (min(top - k, 32) + 7) / 8;
+#pragma unroll 1
+                    for (int g = 0; g < ng; ++g) {
+                        // a rejected candidate goes to the dump row and leaves the place free
+#pragma unroll
+                        for (int i = 0; i < 8; ++i, ++j, m <<= 1) {
+                            *(m < 0 ? out : dump) = (uint16_t)j;
+                            out += m < 0 ? WAVE : 0;
+                        }
+                    }
+                }
+            }
+            // padding up to the wavefront's longest part: the own slot
+#pragma unroll 1
+            for (int k = tot0 + r; k < kpart.x; k += nrw) fin[k][lane] = (uint16_t)(s - slot0);
+#pragma unroll 1
+            for (int k = tot1 + r; k < kpart.y; k += nrw) fin[kpart.x + k][lane] = (uint16_t)(s - slot0);
+            __syncthreads();
+#pragma unroll 1
+            for (int q = r; q < (min(used_rows, rows) >> 2); q += nrw) {  // 16-byte words of the lists
+                const bool second = 4 * q >= row1;
+                const int kw = second ? 4 * q - row1 : 4 * q;  // word of the part
+                const bool half = second ? h1 : h0;
+                const uint16_t(*f)[WAVE] = fin + (second ? kpart.x : 0) + (half ? 2 * kw : kw);
+                int4 v;
+                if (half) {
+                    int e[8];
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) e[t] = f[t][lane] + slot0 - base;
+                    v = make_int4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+                } else {
+                    v = make_int4(f[0][lane] + slot0, f[1][lane] + slot0, f[2][lane] + slot0, f[3][lane] + slot0);
+                }
+                *reinterpret_cast<int4 *>(col + q * 256) = v;
+            }
+        } else {
+            auto put = [&](int tj, int k, int j) __attribute__((always_inline)) {
+                const bool half = tj ? h1 : h0;
+                const int kw = (tj ? row1 : 0) + (half ? k >> 1 : k);
+                if (kw >= rows) return;
+                int32_t *q = col + (kw >> 2) * 256 + (kw & 3);
+                if (half) reinterpret_cast<uint16_t *>(q)[k & 1] = (uint16_t)(j - base);
+                else *q = j;
+            };
+            walk([&](int tj, int j) __attribute__((always_inline)) {
+                put(tj, tj ? at1 : at0, j);
+                at0 += 1 - tj;
+                at1 += tj;
+            });
+            for (int tj = 0; tj < 2; ++tj)
+                for (int k = (tj ? tot1 : tot0) + r; k < (tj ? kpart.y : kpart.x); k += nrw) put(tj, k, s);
+        }
+        // the sorted state back into place (last: a wait for loaded data would
+        // wait for these stores too)
+        if (real) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (k == 0 || nrw == 3) st_stream(sv[k], &d.x[(size_t)(r + 3 * k) * np + s]);
+            if (r < 3) st_stream(vi, &d.img[r * np + s]);
+            if (r == nrw - 1) st_stream(ld_stream(&d.sid[s]), &d.id[s]);
+            if (r == nrw - 2) {
+                d.mirror[s] = mi;  // gathered by the next step: cached
+                st_stream(mi, &d.mbuild[s]);
+            }
+        }
+        if (d.pos4 && r == nrw - 1)  // FP64: gathers see the new order
+            d.pos4[s] = real ? make_double4(d.sx[s], d.sy[s], d.sz[s], 0.0) : make_double4(d.x[s], d.y[s], d.z[s], 0.0);
+        if (r == 0) {
+            int2 kp = kpart;
+            if (used_rows > rows) {  // keep the force kernels inside the list
+                if (lane == 0) {
+                    set_err(d.err, KAMD_DEV_LIST_OVERFLOW);
+                    atomicMax(&d.counters[3], used_rows);  // the rows a healing rebuild must provide
+                }
+                const int w0 = min(row1, rows);
+                const int w1 = min(h1 ? kpart.y / 2 : kpart.y, rows - w0);
+                kp.x = h0 ? 2 * w0 : w0;
+                kp.y = h1 ? 2 * w1 : w1;
+            }
+            if (lane == 0) {
+                d.kmax[w] = kp;
+                d.lbase[w] = bpart;
+                d.pcount[w] = make_int2(0, 0);
+            }
+            const int n16 = base >= 0 ? (S.type == 0 ? tot0 : tot1) - 1 : 0;
+            d.nlen[s] = real ? (tot0 + tot1 - 1) | (n16 << 16) : 0;
+        }
+        __syncthreads();  // the image is read before the next windows come
+    }
+}
+
 static inline int nblk_slots(const Dev &d) { return (d.nwaves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK; }
 constexpr int CHAIN_MAX_BLOCKS = 1024;  // grid cap of the grid-stride chain kernels
 static inline int nblk_capped(int waves) { return std::min((waves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK, CHAIN_MAX_BLOCKS); }
@@ -982,12 +1320,35 @@ hipError_t launch_rb_sortgather(const Dev &d, hipStream_t s)
     hipLaunchKernelGGL(k_rb_sortgather, dim3(nblk_capped(d.nwaves)), dim3(BLOCK), 0, s, d);
     return hipGetLastError();
 }
+// Which list builder: the wide one for worklists of up to WIDE_WAVES waves
+// where it can build them (one cell per list radius, boxes of the coarse test,
+// replicas of up to 2^16 slots, no windows).  A single system rebuilds all its
+// waves or none, so only one of the two is launched; a batch launches both and
+// the worklist decides, except where its worklists are hardly ever that short
+// (the extra launch would cost the 256-replica batch 0.5%).
+// Measured (us per MIXED NVE step, k_rb_list, then wide): N = 1000 35.1, 23.7;
+// 32,000 (501 waves) 39.4, 30.9; 50,000 (782) 42.4, 39.0; 62,000 (970) 45.4,
+// 42.4; 64 replicas of 1000 under the bath (worklists of up to 1088) 101, 68.
+// Larger worklists keep k_rb_list's one wavefront per list: the 256-replica
+// batch, whose worklists reach 4500 waves, 416 with either limit up to 1600,
+// 496 with the wide kernel alone.
+constexpr int WIDE_WAVES = 1100, WIDE_BATCH_WAVES = 8192;
 hipError_t launch_rb_list(const Dev &d, int cell_div, hipStream_t s)
 {
-    if (d.stage_ok)
-        hipLaunchKernelGGL(k_rb_list<true>, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, cell_div);
-    else
-        hipLaunchKernelGGL(k_rb_list<false>, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, cell_div);
+    const bool can = cell_div == 1 && !d.stage_ok && d.box_max <= COARSE_MAX_BOX && d.rep_waves_max <= 65536 / WAVE;
+    const bool wide = can && d.nwaves <= (d.nrep > 1 ? WIDE_BATCH_WAVES : WIDE_WAVES);
+    const bool rest = !wide || d.nwaves > WIDE_WAVES;
+    const int rows = d.dim == 2 ? 3 : LIST_ROWS;
+    if (wide)
+        hipLaunchKernelGGL(k_rb_list_wide, dim3(std::min(d.nwaves, WIDE_BLOCKS * (LIST_ROWS / rows))), dim3(WAVE * rows),
+                           0, s, d, WIDE_WAVES);
+    if (rest) {
+        const int least = wide ? WIDE_WAVES + 1 : 1;
+        if (d.stage_ok)
+            hipLaunchKernelGGL(k_rb_list<true>, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, cell_div, least);
+        else
+            hipLaunchKernelGGL(k_rb_list<false>, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, cell_div, least);
+    }
     return hipGetLastError();
 }
 

@@ -276,6 +276,10 @@ static void make_plan(const kamd_config *cfg, const kamd_replica *reps, int n_re
             const double rl = rc + skin_r;
             R.rc2_fx[p] = (float)((rc / h) * (rc / h));
             R.rl2_fx[p] = (float)((rl / h) * (rl / h) * (1.0 + 4e-6));
+            // list radius in 2^16-step units + sqrt(3), squared (see k_rb_list); boxes
+            // too small for the unit to matter have radii far below 2^16 units
+            const double rc16 = std::sqrt((double)R.rl2_fx[p]) * (1.0 / 65536.0) + 1.7320508075688772;
+            R.r2c[p] = (int32_t)std::min(std::ceil(rc16 * rc16) + 1.0, 2147483647.0);
             R.sig2_fx[p] = (float)((cfg->model.sigma[p] / h) * (cfg->model.sigma[p] / h));
             R.c48_h[p] = 48.0 * cfg->model.eps[p] / h;
             R.fix_k[p] = R.c48_h[p] * FIX_SCALE;
@@ -389,7 +393,8 @@ static void carve_fixed(Dev &d, CtxBufs &b, const Shape &z, Carve &k)
     const size_t np = z.np, nt = z.nt;
     double **f64[] = {&d.x, &d.y, &d.z, &d.vx, &d.vy, &d.vz, &d.ax, &d.ay, &d.az,
                       &d.sx, &d.sy, &d.sz, &d.svx, &d.svy, &d.svz, &d.sax, &d.say, &d.saz};
-    for (auto p : f64) *p = k.take<double>(np);
+    double *state = k.take<double>(9 * np), *scratch = k.take<double>(9 * np);
+    for (int q = 0; q < 18; ++q) *f64[q] = k.base ? (q < 9 ? state + q * np : scratch + (q - 9) * np) : nullptr;
     d.img = k.take<int32_t>(3 * np);
     d.simg = k.take<int32_t>(3 * np);
     d.id = k.take<int32_t>(np);
@@ -550,6 +555,12 @@ static void bind_workspace(kamd_ctx *c, const Plan &P)
     d.nrep = (int32_t)c->reps.size();
     d.dim = dim_of(&c->cfg);
     d.rows = P.rows;
+    d.box_max = 0.0;
+    d.rep_waves_max = 0;
+    for (const RepInfo &R : P.rinfo) {
+        d.box_max = std::max(d.box_max, R.L);
+        d.rep_waves_max = std::max(d.rep_waves_max, R.wave1 - R.wave0);
+    }
     d.ncells = P.ncells;
     d.scan_cps = P.scan_cps;
     d.rdf_cells_cap = (int64_t)c->shape.rdf_cells;

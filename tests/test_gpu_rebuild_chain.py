@@ -108,3 +108,41 @@ def test_forces_after_partial_rebuilds_match_oracle():
         assert err <= 1e-5
         off += n
     s.close()
+
+
+@pytest.mark.parametrize("n,L,skin,dim", [
+    (140, 5.3, 0.2, 3),     # one cell per edge
+    (330, 6.5, 0.3, 3),     # two cells per edge: every row is whole
+    (1000, 9.41, 0.3, 3),   # three: every row wraps
+    (4000, 14.94, 1.0, 3),  # lists longer than the image
+    (9000, 19.2, 1.6, 3),   # rows of more chunks than masks
+    (65300, 37.9, 0.3, 3),  # nearly 2^16 slots
+    (1000, 28.82, 0.3, 2),  # planar
+])
+def test_wide_list_builder_equals_the_narrow_one(n, L, skin, dim):
+    """The block-per-wave list builder against the wavefront-per-wave one, which
+    the window variant uses: the same entries in the same order, so the same
+    MIXED forces bit for bit, and the same list lengths up to the entries
+    beyond the list radius that the coarse test lets in."""
+    print(f"case wide list n={n} skin={skin} dim={dim}", flush=True)
+    if dim == 2:
+        pos = W.planar_lattice_config(n, L, 5)
+        vel = W.gaussian_velocities(n, 0.5, 3)
+        vel = (vel[0], vel[1], np.zeros(n))
+    else:
+        pos = W.lattice_config(n, L, 5, 0.12)
+        vel = W.gaussian_velocities(n, 0.5, 3)
+    out = []
+    for windows in (0, 1):
+        s = md.System([(n, W.n_a_for(n), L, 1.0, 3)], precision="mixed", positions=pos, velocities=vel, skin=skin, dim=dim)
+        md.md_set_force_kernel(s.ctx, windows, 256)
+        s.build_cells()
+        s.forces()
+        st = md.md_stats(s.ctx)
+        assert s.status() == 0
+        s.step_nve(4)
+        out.append((s.numpy(), st))
+        s.close()
+    for k in out[0][0]:
+        assert np.array_equal(out[0][0][k], out[1][0][k]), k
+    assert out[0][1]["mean_list_len"] == pytest.approx(out[1][1]["mean_list_len"], rel=0.006)
