@@ -26,6 +26,8 @@ constexpr int CELL_SUBX = 4;             // list cells are sorted in sub-cells o
                                          // cell edge along x (cell_count/start/end per sub-cell)
 constexpr int VH_MAX_BINS = 1024;       // bins of the self van Hove histogram
 constexpr int SCAN_CHUNK = 2048;         // cells per block of the cell-range scan
+constexpr int SORT_SLOTS = 8192;         // slots and sub-cells per replica up to which
+constexpr int SORT_CELLS = 8192;         // one block sorts a replica (k_rb_sort_small)
 constexpr int LIST_UNROLL = 8;           // candidates per step of the list builder's scan
 // Force-kernel windows (mixed precisions): per wavefront and list part at
 // most STAGE_PIECES row pieces (9 stencil rows, each a main run and a wrapped
@@ -166,6 +168,7 @@ struct Dev {
     int32_t rows;         // neighbour-list row capacity
     double box_max;       // largest box edge
     int32_t rep_waves_max; // wavefronts of the largest replica
+    int32_t sort_small;   // every replica within SORT_SLOTS and SORT_CELLS
     int32_t scan_cps;     // scan chunks (SCAN_CHUNK cells) of the largest segment
     int32_t *chunk_sum;   // [nseg][scan_cps]: particles of each scan chunk (segments of several chunks)
 };
@@ -179,6 +182,7 @@ void mark_static(kamd_ctx *c, int device);
 
 // ---------------------------------------------------------------- launchers
 // Each returns hipGetLastError() after its launch(es).
+hipError_t launch_rb_sort_small(const Dev &d, hipStream_t s);  // plans with sort_small: all before the list
 hipError_t launch_rb_gate(const Dev &d, hipStream_t s);
 hipError_t launch_rb_assign(const Dev &d, hipStream_t s);
 hipError_t launch_rb_scan(const Dev &d, int nseg, hipStream_t s);

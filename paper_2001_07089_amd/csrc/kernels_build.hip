@@ -30,7 +30,8 @@
 //   rb_list       per listed wave: copy its state back, record the build
 //                 position, write its neighbour list
 // Every kernel returns at once when the worklist is empty; the scan also
-// skips replicas whose flag is clear.
+// skips replicas whose flag is clear.  Plans of small replicas only run
+// everything before rb_list as one kernel (k_rb_sort_small).
 #include <climits>
 
 #include "common_dev.hpp"
@@ -379,6 +380,160 @@ __global__ __launch_bounds__(BLOCK) void k_rb_sortgather(Dev d)
             gather_one(d, s, st + rank);
             d.cell_count[sc] = 0;
         }
+    }
+}
+
+// Small replicas (every one of the plan within SORT_SLOTS slots and SORT_CELLS
+// sub-cells): the gate and the whole counting sort in one kernel, one block per
+// replica, with the counters, their scan and the order in LDS.  A step without
+// a rebuild then launches two chain kernels instead of six, and a rebuild's sort
+// is one pass over its replica instead of five kernels.  Every block decides the
+// flags of all replicas by itself (the rule of k_rb_gate), from which follow the
+// worklist's length and the place of its own replica in it.  The result is that
+// of the other chain: a stable sort by sub-cell.
+// @@MEASURED@@
+constexpr int SORT_THREADS = 1024;
+constexpr int SORT_PER = SORT_SLOTS / SORT_THREADS;
+
+__device__ inline int block_sum(int v, int *part)  // all threads of a SORT_THREADS block
+{
+    v = wave_sum_i(v);
+    if (lane_id() == 0) part[threadIdx.x / WAVE] = v;
+    __syncthreads();
+    int t = 0;
+#pragma unroll
+    for (int k = 0; k < SORT_THREADS / WAVE; ++k) t += part[k];
+    __syncthreads();
+    return t;
+}
+
+template <bool GATHER>
+__global__ __launch_bounds__(SORT_THREADS) void k_rb_sort_small(Dev d)
+{
+    __shared__ int start[SORT_CELLS];         // counters, then the sub-cells' first slots
+    __shared__ uint16_t order[SORT_SLOTS];
+    __shared__ int part[SORT_THREADS / WAVE];
+    const int me = blockIdx.x, t = threadIdx.x, lane = lane_id();
+    // the gate
+    bool along = false, mine;
+    int before = 0;
+    if (d.nrep == 1) {
+        mine = rebuild_flag(d, 0, false);
+        if (t == 0) {
+            d.rb_any[0] = mine ? d.nwaves : 0;
+            d.rb_any[1] = 0;
+        }
+        if (!mine) return;
+    } else {
+        int must = 0;
+        for (int r = t; r < d.nrep; r += SORT_THREADS)
+            if (rebuild_flag(d, r, false)) must += d.rep[r].wave1 - d.rep[r].wave0;
+        must = block_sum(must, part);
+        along = must > 0 && must < LIST_ALONG_WAVES;
+        int total = 0;
+        if (must > 0) {
+            for (int r = t; r < d.nrep; r += SORT_THREADS)
+                if (rebuild_flag(d, r, along)) {
+                    const int nw = d.rep[r].wave1 - d.rep[r].wave0;
+                    total += nw;
+                    before += r < me ? nw : 0;
+                }
+            if (me == 0) total = block_sum(total, part);
+            before = block_sum(before, part);
+        }
+        if (me == 0 && t == 0) {
+            d.rb_any[0] = total;
+            d.rb_any[1] = along ? 1 : 0;
+        }
+        if (must == 0 || !rebuild_flag(d, me, along)) return;
+    }
+    const RepInfo &R = d.rep[me];
+    const SegInfo &A = d.seg[R.seg[0]], &B = d.seg[R.seg[1]];
+    const int base = R.wave0 * WAVE, nc = R.nc, nslot = (R.wave1 - R.wave0) * WAVE;
+    const int b0 = B.slot0 - base;                            // the replica's first B slot
+    const int sub0 = CELL_SUBX * A.cell0, nsub = CELL_SUBX * (A.ncell + B.ncell);
+    for (int i = t; i < R.wave1 - R.wave0; i += SORT_THREADS) d.rb_wlist[before + i] = R.wave0 + i;
+    if (t == 0) atomicAdd(&d.counters[0], 1);
+    for (int i = t; i < nsub; i += SORT_THREADS) start[i] = 0;
+    __syncthreads();
+    // count; each thread keeps the sub-cell and the arrival rank of its particles
+    int cell[SORT_PER], rank[SORT_PER];
+#pragma unroll
+    for (int k = 0; k < SORT_PER; ++k) {
+        const int l = k * SORT_THREADS + t;
+        cell[k] = -1;
+        if (l < nslot && (l < b0 ? l < A.n : l - b0 < B.n)) {
+            const uint4 m = d.mirror[base + l];
+            const int cz = d.dim == 2 ? 0 : fix_cell(m.z, nc);
+            const SegInfo &S = l < b0 ? A : B;
+            cell[k] = CELL_SUBX * (S.cell0 + (cz * nc + fix_cell(m.y, nc)) * nc) + fix_cell(m.x, CELL_SUBX * nc) - sub0;
+            rank[k] = atomicAdd(&start[cell[k]], 1);
+        }
+    }
+    __syncthreads();
+    // exclusive scan: nsub / 1024 consecutive sub-cells per thread
+    constexpr int CPT = SORT_CELLS / SORT_THREADS;
+    const int per = (nsub + SORT_THREADS - 1) / SORT_THREADS;
+    int cnt[CPT], sum = 0;
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+        const int c = t * per + k;
+        cnt[k] = k < per && c < nsub ? start[c] : 0;
+        sum += cnt[k];
+    }
+    int inc = sum;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const int u = __shfl_up(inc, o, WAVE);
+        if (lane >= o) inc += u;
+    }
+    if (lane == WAVE - 1) part[t / WAVE] = inc;
+    __syncthreads();
+    int run = inc - sum;
+    for (int k = 0; k < t / WAVE; ++k) run += part[k];
+    const int nsubA = CELL_SUBX * A.ncell, shift = b0 - A.n;  // B's slots start at the next wavefront
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+        const int c = t * per + k;
+        if (k < per && c < nsub) {
+            const int at = run + (c < nsubA ? 0 : shift);
+            start[c] = at;
+            d.cell_start[sub0 + c] = base + at;
+            d.cell_end[sub0 + c] = base + at + cnt[k];
+        }
+        run += cnt[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SORT_PER; ++k)
+        if (cell[k] >= 0) order[start[cell[k]] + rank[k]] = (uint16_t)(k * SORT_THREADS + t);
+    __syncthreads();
+    // rank by previous slot among the sub-cell's members, then the state moves
+#pragma unroll
+    for (int k = 0; k < SORT_PER; ++k)
+        if (cell[k] >= 0) {
+            const int l = k * SORT_THREADS + t, c = cell[k], st = start[c];
+            // the sub-cell ends where the next one starts (segments end apart)
+            const int last = c < nsubA ? A.n : b0 + B.n;
+            const int en = c + 1 == nsubA || c + 1 == nsub ? last : start[c + 1];
+            int at = st;
+            for (int e = st; e < en; ++e) at += order[e] < l ? 1 : 0;
+            if (GATHER) gather_one(d, base + l, base + at);
+            else d.rank[base + l] = base + at;
+        }
+}
+
+// The state of the listed waves into the sorted places in d.rank.
+__global__ __launch_bounds__(BLOCK) void k_rb_gather(Dev d)
+{
+    const int nact = d.rb_any[0];
+    if (nact == 0) return;
+    const int stride = gridDim.x * WAVES_PER_BLOCK;
+    for (int i = blockIdx.x * WAVES_PER_BLOCK + (threadIdx.x >> 6); i < nact; i += stride) {
+        const int w = d.rb_wlist[i];
+        const SegInfo &S = d.seg[d.wave_seg[w]];
+        const int s = w * WAVE + lane_id();
+        if (s - S.slot0 < S.n) gather_one(d, s, d.rank[s]);
     }
 }
 
@@ -1293,6 +1448,17 @@ static inline int nblk_slots(const Dev &d) { return (d.nwaves + WAVES_PER_BLOCK 
 constexpr int CHAIN_MAX_BLOCKS = 1024;  // grid cap of the grid-stride chain kernels
 static inline int nblk_capped(int waves) { return std::min((waves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK, CHAIN_MAX_BLOCKS); }
 
+constexpr int SORT_GATHER_WAVES = 48;  // N = 3000: equal either way
+hipError_t launch_rb_sort_small(const Dev &d, hipStream_t s)
+{
+    if (d.rep_waves_max <= SORT_GATHER_WAVES) {
+        hipLaunchKernelGGL(k_rb_sort_small<true>, dim3(d.nrep), dim3(SORT_THREADS), 0, s, d);
+    } else {
+        hipLaunchKernelGGL(k_rb_sort_small<false>, dim3(d.nrep), dim3(SORT_THREADS), 0, s, d);
+        hipLaunchKernelGGL(k_rb_gather, dim3(nblk_capped(d.nwaves)), dim3(BLOCK), 0, s, d);
+    }
+    return hipGetLastError();
+}
 hipError_t launch_rb_gate(const Dev &d, hipStream_t s)
 {
     hipLaunchKernelGGL(k_rb_gate, dim3(1), dim3(GATE_THREADS), 0, s, d);

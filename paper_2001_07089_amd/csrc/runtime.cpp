@@ -561,6 +561,8 @@ static void bind_workspace(kamd_ctx *c, const Plan &P)
         d.box_max = std::max(d.box_max, R.L);
         d.rep_waves_max = std::max(d.rep_waves_max, R.wave1 - R.wave0);
     }
+    d.sort_small = d.rep_waves_max <= SORT_SLOTS / WAVE;
+    for (const SegInfo &S : P.segs) d.sort_small = d.sort_small && 2 * (int64_t)CELL_SUBX * S.ncell <= SORT_CELLS;
     d.ncells = P.ncells;
     d.scan_cps = P.scan_cps;
     d.rdf_cells_cap = (int64_t)c->shape.rdf_cells;
@@ -736,6 +738,11 @@ static void lattice_positions(const kamd_replica &K, int dim, std::vector<double
 // ---------------------------------------------------------------- kernels
 static int rebuild_chain(kamd_ctx *c, const Dev &d)
 {
+    if (d.sort_small) {
+        HIPCHK(c, launch_rb_sort_small(d, c->stream));
+        HIPCHK(c, launch_rb_list(d, c->cell_div, c->stream));
+        return KAMD_OK;
+    }
     HIPCHK(c, launch_rb_gate(d, c->stream));
     HIPCHK(c, launch_rb_assign(d, c->stream));
     HIPCHK(c, launch_rb_scan(d, (int)c->segs.size(), c->stream));

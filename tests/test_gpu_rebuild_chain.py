@@ -146,3 +146,39 @@ def test_wide_list_builder_equals_the_narrow_one(n, L, skin, dim):
     for k in out[0][0]:
         assert np.array_equal(out[0][0][k], out[1][0][k]), k
     assert out[0][1]["mean_list_len"] == pytest.approx(out[1][1]["mean_list_len"], rel=0.006)
+
+
+@pytest.mark.parametrize("n,L", [
+    (65, 6.5),       # one wavefront per species
+    (2990, 13.6),    # 47 wavefronts: sorted and gathered by one block
+    (3100, 13.7),    # 50: gathered by the whole device
+    (8100, 18.9),    # just under 2^13 slots
+    (8250, 19.0),    # just over
+    (500, 30.0),     # 10 cells per edge: 8000 sub-cells
+    (500, 31.0),     # 11: too many for one block
+])
+def test_one_block_sort_equals_the_chain(n, L):
+    """A replica alone (sorted by one block where it is small enough) and the
+    same replica beside a large one (always sorted by the kernel chain): one
+    build from the same start gives the same slot order, so the same MIXED
+    forces bit for bit, and through a few rebuilds the same MIXED_FIXED
+    trajectory."""
+    print(f"case one-block sort n={n} L={L}", flush=True)
+    big = (9000, W.n_a_for(9000), W.box_for(9000, 1.2), 0.6, 9)
+    small = (n, W.n_a_for(n), L, 1.5, 4)
+    p0, p1 = W.lattice_config(n, L, 5, 0.1), W.lattice_config(9000, big[2], 6, 0.1)
+    v0, v1 = W.gaussian_velocities(n, 1.2, 3), W.gaussian_velocities(9000, 0.7, 4)
+    for prec, steps in (("mixed", 0), ("mixed_fixed", 30)):
+        out = []
+        for reps, pos, vel in (([small], p0, v0), ([small, big], [np.concatenate(q) for q in zip(p0, p1)],
+                                                   [np.concatenate(q) for q in zip(v0, v1)])):
+            s = md.System(reps, precision=prec, positions=pos, velocities=vel)
+            if steps:
+                s.step_nve(steps)
+                assert md.md_stats(s.ctx)["rebuilds"] >= len(reps) + 1
+            assert s.status() == 0
+            a = s.numpy()
+            out.append({k: a[k][:n] for k in a})
+            s.close()
+        for k in out[0]:
+            assert np.array_equal(out[0][k], out[1][k]), (prec, k)
