@@ -116,3 +116,27 @@ def test_nve_drift_bound_at_32000(prec):
     assert d <= 1e-4
     assert slope <= 1e-4
     s.close()
+
+
+def test_van_hove_across_replicas_and_block_runs():
+    """Replicas of one wavefront to 300 (a block of the histogram kernel takes
+    16 or more consecutive wavefronts, here of several replicas and both
+    species), against the definition: whole counts."""
+    ns = (70, 19000, 250, 65, 1030, 9000)
+    reps = [(n, W.n_a_for(n), max(W.box_for(n, 1.2), 6.5), 1.0, 3) for n in ns]
+    pos = [np.concatenate(q) for q in zip(*(W.lattice_config(n, L, 5 + n, 0.1) for n, _, L, _, _ in reps))]
+    s = md.System(reps, precision="mixed", positions=pos, velocities=W.gaussian_velocities(sum(ns), 0.8, 2))
+    s.msd_set_origin(3)
+    s.step_nve(12)
+    dr, nb = 0.004, 37
+    h = s._host(s.van_hove(3, dr, nb))
+    a, img = s.numpy(("x", "y", "z")), s.images()
+    o = 0
+    for r, (n, na, L, _, _) in enumerate(reps):
+        sl = slice(o, o + n)
+        d = [(a[k][sl] + img[i][sl] * L) - pos[i][sl] for i, k in enumerate(("x", "y", "z"))]
+        b = (np.sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]) / dr).astype(np.int64)
+        for t, part in enumerate((b[:na], b[na:])):
+            assert np.array_equal(h[r, t], np.bincount(part[part < nb], minlength=nb)), (r, t)
+        o += n
+    s.close()
