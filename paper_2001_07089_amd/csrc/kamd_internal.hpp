@@ -209,7 +209,6 @@ hipError_t launch_drift(const Dev &d, double dt, hipStream_t s);
 hipError_t launch_drift_nh(const Dev &d, double dt, hipStream_t s);
 hipError_t launch_kick_nve(const Dev &d, double dt, bool want_ke, hipStream_t s);
 hipError_t launch_kick_nh(const Dev &d, hipStream_t s);
-hipError_t launch_kick_drift(const Dev &d, double dt, bool want_ke, hipStream_t s);
 hipError_t launch_rep_reduce(const Dev &d, int mask, hipStream_t s);
 hipError_t launch_nh_begin(const Dev &d, double dt, const double *Q, hipStream_t s);
 hipError_t launch_nh_end(const Dev &d, double dt, const double *Q, hipStream_t s);

@@ -78,31 +78,6 @@ __global__ __launch_bounds__(BLOCK) void k_kick(Dev d, double c_nve, int nh, int
     }
 }
 
-// NVE only: the closing half-kick of one step fused with the drift of the
-// next (both use the same acceleration), one pass over the state.
-__global__ __launch_bounds__(BLOCK) void k_kick_drift(Dev d, double dt, int want_ke)
-{
-    SlotCtx c;
-    const bool valid = slot_ctx(d, c);
-    float d2 = 0.0f;
-    double k2 = 0.0;
-    if (valid && c.real) {
-        const int s = c.s;
-        const double h = 0.5 * dt;
-        const double vx = fma(h, d.ax[s], d.vx[s]);
-        const double vy = fma(h, d.ay[s], d.vy[s]);
-        const double vz = fma(h, d.az[s], d.vz[s]);
-        k2 = vx * vx + vy * vy + vz * vz;
-        d.vx[s] = vx; d.vy[s] = vy; d.vz[s] = vz;
-        drift_one(d, s, c.rep, dt, 0.0, 0.0, h, d.mirror, d2);
-    }
-    if (want_ke && valid) {
-        k2 = wave_sum(k2);
-        if (lane_id() == 0) d.wred[4 * c.w + 0] = k2;
-    }
-    block_disp_max(d.maxdisp, valid, valid ? c.rep : -1, d2);
-}
-
 // Per-replica sum of the 4 per-wave partials (fixed order).  what: 0 -> rsum.
 // Each thread reads a wave's four partials as one 32-byte load, four waves
 // (BLOCK apart) per pass, so that a replica of many waves (16,384 at N =
@@ -450,11 +425,6 @@ hipError_t launch_kick_nve(const Dev &d, double dt, bool want_ke, hipStream_t s)
 hipError_t launch_kick_nh(const Dev &d, hipStream_t s)
 {
     hipLaunchKernelGGL(k_kick, dim3(nblk(d)), dim3(BLOCK), 0, s, d, 0.0, 1, 1);
-    return hipGetLastError();
-}
-hipError_t launch_kick_drift(const Dev &d, double dt, bool want_ke, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_kick_drift, dim3(nblk(d)), dim3(BLOCK), 0, s, d, dt, want_ke ? 1 : 0);
     return hipGetLastError();
 }
 hipError_t launch_rep_reduce(const Dev &d, int mask, hipStream_t s)

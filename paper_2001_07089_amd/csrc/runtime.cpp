@@ -823,9 +823,9 @@ static int enqueue_steps(kamd_ctx *c, int nsteps, int ensemble, int mode, int nb
     // The force of a step is fused with its closing half kick and the next
     // drift whenever no thermostat acts in between.  Fused steps alternate
     // the two position mirrors, the two displacement buffers and (FP64) the
-    // two packed position buffers; their number is made even so that every
-    // call starts and ends on the first buffers (which keeps graph replays
-    // consistent).
+    // two packed position buffers.  The first drift writes the buffers from
+    // which that many alternations end on the first ones, so that every call
+    // starts and ends there (which keeps graph replays consistent).
     std::vector<char> fused(nsteps + 1, 0);
     int nf = 0;
     for (int s = 1; s < nsteps; ++s) {
@@ -834,12 +834,9 @@ static int enqueue_steps(kamd_ctx *c, int nsteps, int ensemble, int mode, int nb
         fused[s] = !reassign;
         nf += fused[s];
     }
-    if (nf % 2)
-        for (int s = 1; s < nsteps; ++s)
-            if (fused[s]) { fused[s] = 0; break; }
     uint4 *mir[2] = {c->d.mirror, c->mirror_alt};
     double4 *p4[2] = {c->d.pos4, c->pos4_alt};
-    int cur = 0, par = 0;
+    int cur = nf & 1, par = nf & 1;
     Dev dd = c->d;
     bool need_drift = true, p4_ok = false;
     for (int s = 1; s <= nsteps; ++s) {
@@ -869,34 +866,26 @@ static int enqueue_steps(kamd_ctx *c, int nsteps, int ensemble, int mode, int nb
         }
         p4_ok = false;
         HIPCHK(c, launch_force(dd, c->model, prec, smp, true, c->stream));
-        if (s == nsteps || reassign) {
-            HIPCHK(c, launch_kick_nve(dd, dt, smp, c->stream));
-            if (reassign) {
-                // a sample describes the end of the step: PE and W now, KE
-                // after the redraw
-                if (smp) {
-                    HIPCHK(c, launch_rep_reduce(dd, 6, c->stream));
-                    HIPCHK(c, launch_sample(dd, 2, c->stream));
-                }
-                TRY(mb_reassign(c, device_tags, (uint32_t)gstep));
-                if (smp) {
-                    HIPCHK(c, launch_ke_partial(dd, c->stream));
-                    HIPCHK(c, launch_rep_reduce(dd, 1, c->stream));
-                    HIPCHK(c, launch_sample(dd, 5, c->stream));
-                }
-            } else if (smp) {
-                HIPCHK(c, launch_rep_reduce(dd, 7, c->stream));
-                HIPCHK(c, launch_sample(dd, 7, c->stream));
-            }
-            need_drift = true;
-        } else {
-            HIPCHK(c, launch_kick_drift(dd, dt, smp, c->stream));
+        // the last step, or one before a velocity redraw
+        HIPCHK(c, launch_kick_nve(dd, dt, smp, c->stream));
+        if (reassign) {
+            // a sample describes the end of the step: PE and W now, KE
+            // after the redraw
             if (smp) {
-                HIPCHK(c, launch_rep_reduce(dd, 7, c->stream));
-                HIPCHK(c, launch_sample(dd, 7, c->stream));
+                HIPCHK(c, launch_rep_reduce(dd, 6, c->stream));
+                HIPCHK(c, launch_sample(dd, 2, c->stream));
             }
-            need_drift = false;
+            TRY(mb_reassign(c, device_tags, (uint32_t)gstep));
+            if (smp) {
+                HIPCHK(c, launch_ke_partial(dd, c->stream));
+                HIPCHK(c, launch_rep_reduce(dd, 1, c->stream));
+                HIPCHK(c, launch_sample(dd, 5, c->stream));
+            }
+        } else if (smp) {
+            HIPCHK(c, launch_rep_reduce(dd, 7, c->stream));
+            HIPCHK(c, launch_sample(dd, 7, c->stream));
         }
+        need_drift = true;
     }
     if (cur != 0 || par != 0) return fail(c, KAMD_EHIP, "internal: unbalanced mirror buffers");
     return KAMD_OK;
@@ -1781,9 +1770,6 @@ extern "C" int md_profile(kamd_ctx *c, int32_t nsteps, double *host_out)
         fused[s] = 1;
         nf += fused[s];
     }
-    if (nf % 2)
-        for (int s = 1; s < nsteps; ++s)
-            if (fused[s]) { fused[s] = 0; break; }
     std::vector<hipEvent_t> ev(5 * (size_t)nsteps + 2);
     for (auto &e : ev) HIPCHK(c, hipEventCreate(&e));
     int32_t cnt0[8], cnt1[8];
@@ -1791,7 +1777,7 @@ extern "C" int md_profile(kamd_ctx *c, int32_t nsteps, double *host_out)
     HIPCHK(c, hipStreamSynchronize(c->stream));
     uint4 *mir[2] = {c->d.mirror, c->mirror_alt};
     double4 *p4[2] = {c->d.pos4, c->pos4_alt};
-    int cur = 0, par = 0;
+    int cur = nf & 1, par = nf & 1;
     Dev dd = c->d;
     bool need_drift = true, p4_ok = false;
     size_t k = 0;
@@ -1818,14 +1804,7 @@ extern "C" int md_profile(kamd_ctx *c, int32_t nsteps, double *host_out)
             HIPCHK(c, launch_force(dd, c->model, prec, false, true, c->stream));
         }
         HIPCHK(c, hipEventRecord(ev[k++], c->stream));
-        if (!fused[s]) {
-            if (s == nsteps) {
-                HIPCHK(c, launch_kick_nve(dd, dt, false, c->stream));
-            } else {
-                HIPCHK(c, launch_kick_drift(dd, dt, false, c->stream));
-                need_drift = false;
-            }
-        }
+        if (!fused[s]) HIPCHK(c, launch_kick_nve(dd, dt, false, c->stream));  // the last step
         HIPCHK(c, hipEventRecord(ev[k++], c->stream));
     }
     HIPCHK(c, hipEventRecord(ev[k++], c->stream));
