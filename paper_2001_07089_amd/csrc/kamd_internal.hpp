@@ -202,6 +202,8 @@ hipError_t launch_force(const Dev &d, const Model &m, int prec, bool energy, boo
 // wpb: wavefronts per block of the step kernel (1, 2 or 4; an autotuner axis).
 hipError_t launch_force_kd(const Dev &d, const Model &m, int prec, double dt, uint4 *mirror_out, uint32_t *md_out,
                            double4 *pos4_out, bool energy, int wpb, hipStream_t s);
+// Close the running rebuild check as a force launch does.
+hipError_t launch_close_check(const Dev &d, hipStream_t s);
 // Pack d.x, d.y, d.z into d.pos4 (every slot, padding included).
 hipError_t launch_pack_pos(const Dev &d, hipStream_t s);
 

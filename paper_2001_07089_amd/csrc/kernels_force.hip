@@ -47,6 +47,9 @@ __device__ inline void close_step(const Dev &d, int step_inc)
     if (step_inc && threadIdx.x == 0) d.counters[1] += 1;
 }
 
+// The same without a force launch (after an explicit list build).
+__global__ void k_close_check(Dev d) { close_step(d, 0); }
+
 __device__ inline double rcp_f64(double a)
 {
     double y = __builtin_amdgcn_rcp(a);
@@ -769,6 +772,12 @@ hipError_t launch_force(const Dev &d, const Model &m, int prec, bool energy, boo
         else
             launch_mixed_wpb<true, false, false, W4>(d, m, si, 0.0, nullptr, nullptr, s);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_close_check(const Dev &d, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_close_check, dim3(1), dim3(BLOCK), 0, s, d);
     return hipGetLastError();
 }
 

@@ -1150,7 +1150,11 @@ extern "C" int md_build_cells(kamd_ctx *c)
 {
     if (!c) return fail(nullptr, KAMD_EINVAL, "null context");
     TRY(force_rebuild_all(c));
-    return heal_build(c, false, false);
+    TRY(heal_build(c, false, false));
+    // the lists are those of the present positions: the next call need not
+    // build them again
+    HIPCHK(c, launch_close_check(c->d, c->stream));
+    return KAMD_OK;
 }
 
 extern "C" int md_forces(kamd_ctx *c, uint32_t flags, double *obs_dev)

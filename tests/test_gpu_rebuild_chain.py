@@ -182,3 +182,31 @@ def test_one_block_sort_equals_the_chain(n, L):
             s.close()
         for k in out[0]:
             assert np.array_equal(out[0][k], out[1][k]), (prec, k)
+
+
+def test_explicit_build_is_not_repeated_by_the_next_call():
+    """md_build_cells builds the lists once; md_forces on the same positions
+    uses them, and a step after it rebuilds only once a particle has moved far
+    enough."""
+    n = 4000
+    L = W.box_for(n, 1.2)
+    s = md.System([(n, W.n_a_for(n), L, 0.8, 3)], precision="mixed_fixed", positions=W.lattice_config(n, L, 5, 0.1),
+                  velocities=W.gaussian_velocities(n, 0.8, 3))
+    s.forces()
+    a = s.numpy(("ax", "ay", "az"))
+    k = md.md_stats(s.ctx)["rebuilds"]
+    s.build_cells()
+    s.forces()
+    s.step_nve(1)
+    assert md.md_stats(s.ctx)["rebuilds"] == k + 1
+    s.build_cells()
+    assert md.md_stats(s.ctx)["rebuilds"] == k + 2
+    b = md.System([(n, W.n_a_for(n), L, 0.8, 3)], precision="mixed_fixed", positions=W.lattice_config(n, L, 5, 0.1),
+                  velocities=W.gaussian_velocities(n, 0.8, 3))
+    b.build_cells()
+    b.forces()
+    c = b.numpy(("ax", "ay", "az"))
+    for q in a:
+        assert np.array_equal(a[q], c[q])
+    s.close()
+    b.close()
