@@ -117,6 +117,7 @@ struct Dev {
     double *sx, *sy, *sz, *svx, *svy, *svz, *sax, *say, *saz;
     int32_t *simg, *sid;
     uint4 *smirror;
+    uint2 *scoarse;       // smirror reduced to 16 bits per axis (list candidates of the coarse test)
     // layout tables
     const SegInfo *seg;
     const RepInfo *rep;

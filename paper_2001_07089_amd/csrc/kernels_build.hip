@@ -334,6 +334,9 @@ __device__ inline void st_stream(uint4 v, uint4 *p)
     __builtin_nontemporal_store(w, reinterpret_cast<v4u *>(p));
 }
 
+// A position reduced to its high 16 bits per axis: x and y packed (x low), z.
+__device__ inline uint2 coarse_of(const uint4 &m) { return make_uint2((m.x >> 16) | (m.y & 0xffff0000u), m.z >> 16); }
+
 // One particle's state from slot v to sorted slot t.  The old copy is dead
 // once read (non-temporal loads); the sorted copy is read back soon by the
 // list builder, and the sorted mirror is its candidates (plain stores).
@@ -353,7 +356,9 @@ __device__ inline void gather_one(const Dev &d, int v, int t)
     d.simg[np + t] = ld_stream(&d.img[np + v]);
     d.simg[2 * np + t] = ld_stream(&d.img[2 * np + v]);
     d.sid[t] = ld_stream(&d.id[v]);
-    d.smirror[t] = d.mirror[v];  // the list builder's candidates: cached
+    const uint4 m = d.mirror[v];
+    d.smirror[t] = m;  // the list builder's candidates: cached
+    d.scoarse[t] = coarse_of(m);
 }
 
 // One thread per particle of the replicas that rebuild.  The scatter put the
@@ -622,6 +627,39 @@ constexpr int LIST_STAGE = 16;
 constexpr double COARSE_MAX_BOX = 220.0;
 constexpr int LIST_WIN = 384;
 
+// The sorted state of slot s back into place, with the mirror (mi) and the
+// build position.
+__device__ inline void copy_back(const Dev &d, int s, bool real, const uint4 &mi)
+{
+    const int np = d.npad_total;
+    double px, py, pz;  // the position, for the FP64 packed copy
+    if (real) {
+        px = ld_stream(&d.sx[s]);
+        py = ld_stream(&d.sy[s]);
+        pz = ld_stream(&d.sz[s]);
+        st_stream(px, &d.x[s]);
+        st_stream(py, &d.y[s]);
+        st_stream(pz, &d.z[s]);
+        st_stream(ld_stream(&d.svx[s]), &d.vx[s]);
+        st_stream(ld_stream(&d.svy[s]), &d.vy[s]);
+        st_stream(ld_stream(&d.svz[s]), &d.vz[s]);
+        st_stream(ld_stream(&d.sax[s]), &d.ax[s]);
+        st_stream(ld_stream(&d.say[s]), &d.ay[s]);
+        st_stream(ld_stream(&d.saz[s]), &d.az[s]);
+        st_stream(ld_stream(&d.simg[s]), &d.img[s]);
+        st_stream(ld_stream(&d.simg[np + s]), &d.img[np + s]);
+        st_stream(ld_stream(&d.simg[2 * np + s]), &d.img[2 * np + s]);
+        st_stream(ld_stream(&d.sid[s]), &d.id[s]);
+        d.mirror[s] = mi;  // gathered by the next step: cached
+        st_stream(mi, &d.mbuild[s]);
+    } else {
+        px = d.x[s];
+        py = d.y[s];
+        pz = d.z[s];
+    }
+    if (d.pos4) d.pos4[s] = make_double4(px, py, pz, 0.0);  // FP64: gathers see the new order
+}
+
 // STAGE: the window variant of the force kernels is on (d.stage_ok), so
 // parts whose windows fit are written in the window format; without it the
 // window code is compiled out.
@@ -641,33 +679,8 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach, int min_wav
     const bool real = (s - S.slot0) < S.n;
     const int np = d.npad_total;
     uint4 mi = make_uint4(0, 0, 0, 0);
-    double px, py, pz;  // the position, for the FP64 packed copy
-    if (real) {
-        px = ld_stream(&d.sx[s]);
-        py = ld_stream(&d.sy[s]);
-        pz = ld_stream(&d.sz[s]);
-        st_stream(px, &d.x[s]);
-        st_stream(py, &d.y[s]);
-        st_stream(pz, &d.z[s]);
-        st_stream(ld_stream(&d.svx[s]), &d.vx[s]);
-        st_stream(ld_stream(&d.svy[s]), &d.vy[s]);
-        st_stream(ld_stream(&d.svz[s]), &d.vz[s]);
-        st_stream(ld_stream(&d.sax[s]), &d.ax[s]);
-        st_stream(ld_stream(&d.say[s]), &d.ay[s]);
-        st_stream(ld_stream(&d.saz[s]), &d.az[s]);
-        st_stream(ld_stream(&d.simg[s]), &d.img[s]);
-        st_stream(ld_stream(&d.simg[np + s]), &d.img[np + s]);
-        st_stream(ld_stream(&d.simg[2 * np + s]), &d.img[2 * np + s]);
-        st_stream(ld_stream(&d.sid[s]), &d.id[s]);
-        mi = d.smirror[s];
-        d.mirror[s] = mi;  // gathered by the next step: cached
-        st_stream(mi, &d.mbuild[s]);
-    } else {
-        px = d.x[s];
-        py = d.y[s];
-        pz = d.z[s];
-    }
-    if (d.pos4) d.pos4[s] = make_double4(px, py, pz, 0.0);  // FP64: gathers see the new order
+    if (real) mi = d.smirror[s];
+    copy_back(d, s, real, mi);
     const int nc = R.nc;
     const int noff = min(nc, 2 * reach + 1);
     const bool whole = nc < 2 * reach + 1;  // every cell of a row is in the stencil
@@ -1106,6 +1119,272 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach, int min_wav
     d.nlen[s] = real ? (total - 1) | (n16 << 16) : 0;
 }
 
+// {m, d} shifted left by one: m with the sign bit of d appended.
+__device__ inline uint32_t push_sign(uint32_t m, int d) { return __builtin_amdgcn_alignbit(m, (uint32_t)d, 31); }
+
+// x + o on a ring of nc cells, -1 <= o <= 1, 0 <= x < nc.
+__device__ inline int ring_cell(int x, int o, int nc)
+{
+    x += o;
+    x += x < 0 ? nc : 0;
+    return x >= nc ? x - nc : x;
+}
+
+// The list builder of k_rb_list for one cell per list radius, boxes of the
+// coarse test and no windows: the same rows, unions, staging and entries, but a
+// row piece's candidates are tested 32 at a time into a bit mask per lane, and
+// only the accepted ones, about a sixth, are then taken out of the mask into the
+// lane's stage.  A test costs five vector operations (two subtractions, two dot
+// products, one shift that appends the sign) where k_rb_list's, with an
+// unconditional stage write per candidate, costs ten; an accepted candidate
+// costs eight more.  Cells of a row are found without divisions, the wrapped
+// piece is looked at only where a lane has one, entries are stored in the
+// stage as the list holds them, and the state is copied back last, so that no
+// wait for loaded data waits for its stores.  Candidates come from an 8-byte
+// copy of the sorted mirror that the sort writes (scoarse); a union too long
+// for the window (most of the B wavefronts', which span several grid rows) is
+// read from it directly at the same cost per test.
+//
+// Bound by the vector ALU: 12,300 instructions per wavefront, 14,800 before, and
+// 87 registers instead of 123 (five wavefronts per SIMD).  Measured: 2^20 MIXED
+// 310 -> 298 us per step, 400,000 140 -> 133, the 256-replica batch 400 -> 372.
+__global__ __launch_bounds__(BLOCK) void k_rb_list_masks(Dev d, int min_waves)
+{
+    __shared__ int32_t stage[WAVES_PER_BLOCK][LIST_STAGE][WAVE];
+    __shared__ uint2 win_s[WAVES_PER_BLOCK][LIST_WIN + 32];  // a mask reads up to 31 past a range
+    if (d.rb_any[0] < min_waves) return;  // nothing to do, or k_rb_list_wide's
+    const int w = rb_work_wave(d);        // each XCD walks a contiguous part of the worklist
+    if (w < 0) return;
+    const int lane = lane_id();
+    const int s = w * WAVE + lane;
+    uint4 mi = d.smirror[s];
+    const SegInfo &S = d.seg[d.wave_seg[w]];
+    const RepInfo &R = d.rep[S.rep];
+    const bool real = (s - S.slot0) < S.n;
+    if (!real) mi = make_uint4(0, 0, 0, 0);
+    const int nc = R.nc;
+    const int noff = min(nc, 3);
+    const bool whole = nc < 3;  // every cell of a row is in the stencil
+    const int oz0 = d.dim == 2 ? 0 : -1, nz = d.dim == 2 ? 1 : noff;
+    const int nrow = nz * noff;
+    const int fx = fix_cell(mi.x, CELL_SUBX * nc);  // x in quarter cells
+    const int cx = fx / CELL_SUBX, qx = fx % CELL_SUBX;
+    const int cy = fix_cell(mi.y, nc), cz = d.dim == 2 ? 0 : fix_cell(mi.z, nc);
+    const uint32_t ixy = coarse_of(mi).x, iz = coarse_of(mi).y;
+    // sub-cells of the lane's main run within a row, and of the end cell that
+    // wraps around (see k_rb_list): first and last of each
+    const bool lw = !whole && cx == 0, rw = !whole && cx == nc - 1;
+    const int m0 = whole || lw ? 0 : CELL_SUBX * (cx - 1) + qx;
+    const int m1 = whole || rw ? CELL_SUBX * nc - 1 : CELL_SUBX * (cx + 1) + qx;
+    const int e0 = lw ? CELL_SUBX * (nc - 1) + qx : 0, e1 = lw ? CELL_SUBX * nc - 1 : qx;
+    const bool wraps = lw || rw;
+    const bool any_wrap = __any(real && wraps);
+    int32_t *col = d.nbr + list_index(w, d.rows, 0, lane);
+    int32_t(*buf)[WAVE] = stage[threadIdx.x / WAVE];
+    uint2 *wc = win_s[threadIdx.x / WAVE];
+    const int rows = d.rows;
+    const int32_t *cstart = d.cell_start, *cend = d.cell_end;
+    int row = 0;  // 32-bit words of the list used so far
+    int total = 0;
+    int2 kpart = make_int2(0, 0), bpart = make_int2(-1, -1);  // per part: entries, base
+    int n16 = 0;
+#pragma unroll 1
+    for (int tj = 0; tj < 2; ++tj) {
+        const SegInfo &SJ = d.seg[R.seg[tj]];
+        const int r2c = R.r2c[S.type + tj];
+        const int cell0 = SJ.cell0;
+        // base slot of 16-bit entries (the part of the own type), or -1
+        int base = -1;
+        if (tj == S.type && SJ.n > 0) {
+            int lo = s, hi = s + 1;
+            if (real) {
+                int z0 = cz + oz0, z1 = cz + oz0 + nz - 1;
+                if (z0 < 0 || z1 >= nc) z0 = 0, z1 = nc - 1;
+                int y0 = cy - 1, y1 = cy - 1 + noff - 1;
+                if (y0 < 0 || y1 >= nc) y0 = 0, y1 = nc - 1;
+                lo = min(lo, cstart[CELL_SUBX * (cell0 + (z0 * nc + y0) * nc)]);
+                hi = max(hi, cend[CELL_SUBX * (cell0 + (z1 * nc + y1) * nc + nc) - 1]);
+            }
+            lo = -wave_max_all(-lo);
+            hi = wave_max_all(hi);
+            if (hi - lo <= 65536) base = lo;
+        }
+        const bool half = base >= 0;
+        const int group = half ? 8 : 4;    // entries per 16-byte store
+        const int sub = half ? base : 0;   // entries are held as the list stores them
+        int cnt = 0;   // entries accepted
+        int done = 0;  // entries written to the list (a multiple of group)
+        auto store = [&](const int e[8]) __attribute__((always_inline)) {  // the next group
+            const int k = row + (half ? done / 2 : done);  // 32-bit word of the list
+            const int4 q = half ? make_int4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16))
+                                : make_int4(e[0], e[1], e[2], e[3]);
+            if (k < rows) *reinterpret_cast<int4 *>(col + (k >> 2) * 256) = q;
+            done += group;
+        };
+        auto flush = [&]() __attribute__((always_inline)) {  // every complete group of staged entries
+            while (done + group <= cnt) {
+                int e[8];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) e[t] = buf[(done + t) & (LIST_STAGE - 1)][lane];
+                if (half) {
+#pragma unroll
+                    for (int t = 4; t < 8; ++t) e[t] = buf[(done + t) & (LIST_STAGE - 1)][lane];
+                }
+                store(e);
+            }
+        };
+        // slot ranges of one stencil row: main run and wrapped end cell
+        auto bounds = [&](int oz, int oy) __attribute__((always_inline)) {
+            int4 b = make_int4(0, 0, 0, 0);
+            if (real) {
+                const int rowc = CELL_SUBX * (cell0 + (ring_cell(cz, oz, nc) * nc + ring_cell(cy, oy, nc)) * nc);
+                b.x = cstart[rowc + m0];
+                b.y = cend[rowc + m1];
+                if (wraps) {
+                    b.z = cstart[rowc + e0];
+                    b.w = cend[rowc + e1];
+                }
+            }
+            return b;
+        };
+        // lowest start and highest end of the lanes' non-empty ranges
+        // (x = INT_MAX when no lane has one); all lanes take part
+        auto span = [&](int st, int en) __attribute__((always_inline)) {
+            const bool has = st < en;
+            return make_int2(-wave_max_all(has ? -st : INT_MIN + 1), wave_max_all(has ? en : -1));
+        };
+        auto piece = [&](int st, int en, int2 sp) __attribute__((always_inline)) {
+            const int lo = sp.x, n = sp.y - sp.x;
+            if (lo == INT_MAX) return;
+            const bool staged = n <= LIST_WIN;
+            if (staged) {
+                // up to three loads per lane in flight at once
+                for (int q0 = 0; q0 < n; q0 += 3 * WAVE) {
+                    uint2 m[3];
+#pragma unroll
+                    for (int t = 0; t < 3; ++t)
+                        if (t == 0 || q0 + t * WAVE < n) m[t] = d.scoarse[lo + min(q0 + t * WAVE + lane, n - 1)];
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) {
+                        const int q = q0 + t * WAVE + lane;
+                        if (q < n) wc[q] = m[t];
+                    }
+                    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): none of this pass is left in flight
+                }
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+#pragma unroll 1
+            for (int j = st; __any(j < en); j += 32) {
+                const int left = min(en - j, 32);        // candidates of the lane's mask
+                const int jj = left > 0 ? j : lo;
+                const int ng = 1 + (__any(left > 8) ? 1 : 0) + (__any(left > 16) ? 1 : 0) + (__any(left > 24) ? 1 : 0);
+                uint32_t m = 0;
+                if (staged) {
+                    const uint2 *v = wc + (jj - lo);
+#pragma unroll 1
+                    for (int g = 0; g < ng; ++g, v += 8)
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) m = push_sign(m, r2_coarse_below(ixy, iz, v[i].x, v[i].y, r2c));
+                } else {
+                    const uint2 *v = d.scoarse + jj;  // with spare entries past its end
+#pragma unroll 1
+                    for (int g = 0; g < ng; ++g, v += 8) {
+                        uint2 q[8];
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) q[i] = v[i];
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) m = push_sign(m, r2_coarse_below(ixy, iz, q[i].x, q[i].y, r2c));
+                    }
+                }
+                m <<= 32 - 8 * ng;  // candidate i in bit 31 - i
+                m = left > 0 ? m & (0xffffffffu << (32 - left)) : 0u;
+                const int ent = jj - sub;
+                // At most LIST_STAGE - 8 entries are pending before a burst of
+                // eight.  The particle's own slot passes the test (zero
+                // separation) and stays in its list, where the force kernels
+                // skip it like the padding.
+                while (__any(m != 0)) {
+#pragma unroll
+                    for (int b = 0; b < 8; ++b)
+                        if (m) {
+                            const int i = __clz((int)m);
+                            m &= ~(0x80000000u >> i);
+                            buf[cnt & (LIST_STAGE - 1)][lane] = ent + i;
+                            ++cnt;
+                        }
+                    if (__any(cnt - done > LIST_STAGE - 8)) flush();
+                }
+            }
+            if (staged) {
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+        };
+        if (SJ.n > 0) {
+            // rows are read one step ahead of their scan, so that the loads of
+            // a row's bounds overlap the staging loads of the row before
+            int oz = oz0, oy = -1;
+            int4 next = bounds(oz, oy);
+#pragma unroll 1
+            for (int r = 0; r < nrow; ++r) {
+                const int4 cur = next;
+                const int2 sp1 = span(cur.x, cur.y);
+                const int2 sp2 = any_wrap ? span(cur.z, cur.w) : make_int2(INT_MAX, 0);
+                __builtin_amdgcn_sched_barrier(0);  // these bounds are used before the next row's loads are issued
+                // the next row; after the last one, row 0 again (read, not used)
+                if (++oy == -1 + noff) {
+                    oy = -1;
+                    if (++oz == oz0 + nz) oz = oz0;
+                }
+                next = bounds(oz, oy);
+                piece(cur.x, cur.y, sp1);
+                if (sp2.x != INT_MAX) piece(cur.z, cur.w, sp2);
+            }
+        }
+        flush();
+        total += cnt;
+        int kmax = wave_max_all(cnt);
+        const int align = half ? 2 * LIST_ROW_ALIGN : LIST_ROW_ALIGN;  // whole 16-byte words
+        kmax = (kmax + align - 1) & -align;
+        const int padv = s - sub;  // padding: the own slot
+        if (done < cnt) {          // the last partial group
+            int e[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) e[t] = done + t < cnt ? buf[(done + t) & (LIST_STAGE - 1)][lane] : padv;
+            store(e);
+        }
+        const int words = half ? kmax / 2 : kmax;  // 32-bit words the part occupies
+        const int pad = half ? padv | (padv << 16) : padv;
+        for (int k = row + (half ? done / 2 : done); k < row + words && k < rows; k += 4)
+            *reinterpret_cast<int4 *>(col + (k >> 2) * 256) = make_int4(pad, pad, pad, pad);
+        if (row + words > rows && lane == 0) set_err(d.err, KAMD_DEV_LIST_OVERFLOW);
+        kpart.x = tj == 0 ? kmax : kpart.x;
+        kpart.y = tj == 1 ? kmax : kpart.y;
+        bpart.x = tj == 0 ? base : bpart.x;
+        bpart.y = tj == 1 ? base : bpart.y;
+        if (half) n16 += cnt - 1;  // 16-bit partner entries (not the own slot)
+        row += words;
+    }
+    if (row > rows) {  // keep the force kernels inside the list
+        if (lane == 0) atomicMax(&d.counters[3], row);  // the rows a healing rebuild must provide
+        const bool h0 = bpart.x >= 0, h1 = bpart.y >= 0;  // 16-bit parts
+        const int w0 = min(h0 ? kpart.x / 2 : kpart.x, rows);
+        const int w1 = min(h1 ? kpart.y / 2 : kpart.y, rows - w0);
+        kpart.x = h0 ? 2 * w0 : w0;
+        kpart.y = h1 ? 2 * w1 : w1;
+    }
+    if (lane == 0) {
+        d.kmax[w] = kpart;
+        d.lbase[w] = bpart;
+        d.pcount[w] = make_int2(0, 0);
+    }
+    // partners (without the own slot) in the low 16 bits, those of them
+    // stored as 16-bit entries in the high 16 bits
+    d.nlen[s] = real ? (total - 1) | (n16 << 16) : 0;
+    copy_back(d, s, real, mi);
+}
+
 // Neighbour lists, a block of LIST_ROWS wavefronts per listed wave: wavefront r
 // takes stencil row r of both partner types.  The lists are those of k_rb_list
 // (one cell per list radius, no windows, coarse test), entry for entry.
@@ -1132,9 +1411,6 @@ constexpr int WIDE_WIN = 432;     // candidates staged per wavefront
 constexpr int WIDE_CHUNKS = 8;    // masks per wavefront
 constexpr int WIDE_LIST = 192;    // entries of the list image
 constexpr int WIDE_BLOCKS = 512;  // two blocks of nine wavefronts per compute unit
-
-// {m, d} shifted left by one: m with the sign bit of d appended.
-__device__ inline uint32_t push_sign(uint32_t m, int d) { return __builtin_amdgcn_alignbit(m, (uint32_t)d, 31); }
 
 __global__ __launch_bounds__(WAVE * LIST_ROWS) void k_rb_list_wide(Dev d, int max_waves)
 {
@@ -1179,7 +1455,7 @@ __global__ __launch_bounds__(WAVE * LIST_ROWS) void k_rb_list_wide(Dev d, int ma
         const int fx = fix_cell(mi.x, CELL_SUBX * nc);  // x in quarter cells
         const int cx = fx / CELL_SUBX, qx = fx % CELL_SUBX;
         const int cy = fix_cell(mi.y, nc), cz = d.dim == 2 ? 0 : fix_cell(mi.z, nc);
-        const uint32_t ixy = (mi.x >> 16) | (mi.y & 0xffff0000u), iz = mi.z >> 16;
+        const uint32_t ixy = coarse_of(mi).x, iz = coarse_of(mi).y;
         const int32_t *cstart = d.cell_start, *cend = d.cell_end;
         // pieces of the lane's row: per partner type the main run of cells and
         // the end cell that wraps around (see k_rb_list); [st, en) in slots
@@ -1255,11 +1531,11 @@ __global__ __launch_bounds__(WAVE * LIST_ROWS) void k_rb_list_wide(Dev d, int ma
             int next = used;  // where the next staged piece starts
             for (int q = 3; q > p; --q) next = sel(off, q) >= 0 ? sel(off, q) : next;
             const int len = next - o;
-            const uint4 *src = d.smirror + sel(lo, p);
+            const uint2 *src = d.scoarse + sel(lo, p);
             for (int e = lane; e < len; e += 2 * WAVE) {
-                const uint4 a = src[e], b = src[min(e + WAVE, len - 1)];
-                wc[o + e] = make_uint2((a.x >> 16) | (a.y & 0xffff0000u), a.z >> 16);
-                if (e + WAVE < len) wc[o + e + WAVE] = make_uint2((b.x >> 16) | (b.y & 0xffff0000u), b.z >> 16);
+                const uint2 a = src[e], b = src[min(e + WAVE, len - 1)];
+                wc[o + e] = a;
+                if (e + WAVE < len) wc[o + e + WAVE] = b;
             }
         }
         const bool masked = chunks <= WIDE_CHUNKS;
@@ -1273,8 +1549,8 @@ __global__ __launch_bounds__(WAVE * LIST_ROWS) void k_rb_list_wide(Dev d, int ma
                 const int r2c = R.r2c[S.type + (p >> 1)], e = sel(en, p);
 #pragma unroll 1
                 for (int j = sel(st, p); j < e; ++j) {
-                    const uint4 v = d.smirror[j];
-                    if (r2_coarse_below(ixy, iz, (v.x >> 16) | (v.y & 0xffff0000u), v.z >> 16, r2c) < 0) take(p >> 1, j);
+                    const uint2 v = d.scoarse[j];
+                    if (r2_coarse_below(ixy, iz, v.x, v.y, r2c) < 0) take(p >> 1, j);
                 }
             }
         };
@@ -1298,15 +1574,14 @@ __global__ __launch_bounds__(WAVE * LIST_ROWS) void k_rb_list_wide(Dev d, int ma
 #pragma unroll
                             for (int i = 0; i < 8; ++i) m = push_sign(m, r2_coarse_below(ixy, iz, v[i].x, v[i].y, r2c));
                     } else {
-                        const uint4 *v = d.smirror + j;
+                        const uint2 *v = d.scoarse + j;  // with spare entries past its end
 #pragma unroll 1
-                        for (int g = 0; g < ng; ++g) {
-                            uint4 q[8];  // clamped: a chunk may pass the end of the array
+                        for (int g = 0; g < ng; ++g, v += 8) {
+                            uint2 q[8];
 #pragma unroll
-                            for (int i = 0; i < 8; ++i) q[i] = v[min(8 * g + i, max(n - 1, 0))];
+                            for (int i = 0; i < 8; ++i) q[i] = v[i];
 #pragma unroll
-                            for (int i = 0; i < 8; ++i)
-                                m = push_sign(m, r2_coarse_below(ixy, iz, (q[i].x >> 16) | (q[i].y & 0xffff0000u), q[i].z >> 16, r2c));
+                            for (int i = 0; i < 8; ++i) m = push_sign(m, r2_coarse_below(ixy, iz, q[i].x, q[i].y, r2c));
                         }
                     }
                     m <<= 32 - 8 * ng;  // candidate i of the chunk in bit 31 - i
@@ -1510,7 +1785,9 @@ hipError_t launch_rb_list(const Dev &d, int cell_div, hipStream_t s)
                            0, s, d, WIDE_WAVES);
     if (rest) {
         const int least = wide ? WIDE_WAVES + 1 : 1;
-        if (d.stage_ok)
+        if (cell_div == 1 && !d.stage_ok && d.box_max <= COARSE_MAX_BOX)
+            hipLaunchKernelGGL(k_rb_list_masks, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, least);
+        else if (d.stage_ok)
             hipLaunchKernelGGL(k_rb_list<true>, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, cell_div, least);
         else
             hipLaunchKernelGGL(k_rb_list<false>, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, cell_div, least);

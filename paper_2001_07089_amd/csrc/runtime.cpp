@@ -402,6 +402,7 @@ static void carve_fixed(Dev &d, CtxBufs &b, const Shape &z, Carve &k)
     d.mirror = k.take<uint4>(np);
     d.mbuild = k.take<uint4>(np);
     d.smirror = k.take<uint4>(np + LIST_UNROLL);  // the list scan reads up to 7 past a range
+    d.scoarse = k.take<uint2>(np + 32);           // and a mask of candidates up to 31
     b.mirror_alt = k.take<uint4>(np);
     d.pos4 = z.fp64 ? k.take<double4>(np) : nullptr;
     b.pos4_alt = z.fp64 ? k.take<double4>(np) : nullptr;
@@ -585,6 +586,7 @@ static int init_fixed(kamd_ctx *c)
     HIPCHK(c, launch_zero_i32((int32_t *)d.mirror, 4 * np, c->stream));
     HIPCHK(c, launch_zero_i32((int32_t *)d.mbuild, 4 * np, c->stream));
     HIPCHK(c, launch_zero_i32((int32_t *)d.smirror, 4 * (np + LIST_UNROLL), c->stream));
+    HIPCHK(c, launch_zero_i32((int32_t *)d.scoarse, 2 * (np + 32), c->stream));
     HIPCHK(c, launch_zero_i32((int32_t *)c->mirror_alt, 4 * np, c->stream));
     HIPCHK(c, launch_zero_i32(d.nlen, np, c->stream));
     HIPCHK(c, launch_zero_i32(d.rb_force, nr, c->stream));

@@ -210,3 +210,38 @@ def test_explicit_build_is_not_repeated_by_the_next_call():
         assert np.array_equal(a[q], c[q])
     s.close()
     b.close()
+
+
+@pytest.mark.parametrize("count,n,L,skin,dim", [
+    (500, 140, 5.3, 0.2, 3),    # one cell per edge
+    (300, 330, 6.5, 0.3, 3),    # two: every row is whole
+    (100, 1000, 9.41, 0.3, 3),  # three: every row wraps
+    (1, 120000, 46.4, 1.3, 3),  # long rows: several masks per piece, pieces past the window
+    (1, 90001, 273.4, 0.3, 2),  # planar, cells as 3-D ones but one layer
+    (2, 70000, 38.8, 0.3, 3),   # replicas of more than 2^16 slots
+])
+def test_mask_list_builder_equals_the_window_builder(count, n, L, skin, dim):
+    """Worklists too long for the block-per-wave builder: the mask builder
+    against the window variant's, as above."""
+    print(f"case mask lists {count} x {n} skin={skin} dim={dim}", flush=True)
+    if dim == 2:
+        pos, v = W.planar_lattice_config(n, L, 5), W.gaussian_velocities(n, 0.5, 3)
+        vel = (v[0], v[1], np.zeros(n))
+    else:
+        pos, vel = W.lattice_config(n, L, 5, 0.12), W.gaussian_velocities(n, 0.5, 3)
+    pos, vel = [np.tile(p, count) for p in pos], [np.tile(p, count) for p in vel]
+    out = []
+    for windows in (0, 1):
+        s = md.System([(n, W.n_a_for(n), L, 1.0, 3)] * count, precision="mixed", positions=pos, velocities=vel,
+                      skin=skin, dim=dim)
+        md.md_set_force_kernel(s.ctx, windows, 256)
+        s.build_cells()
+        s.forces()
+        st = md.md_stats(s.ctx)
+        assert s.status() == 0
+        s.step_nve(3)
+        out.append((s.numpy(), st))
+        s.close()
+    for k in out[0][0]:
+        assert np.array_equal(out[0][0][k], out[1][0][k]), k
+    assert out[0][1]["mean_list_len"] == pytest.approx(out[1][1]["mean_list_len"], rel=0.006)
