@@ -50,22 +50,38 @@ __device__ inline int wave_max_i(int v)
     return v;
 }
 
-// Runs of consecutive lanes with the same cell c (padding lanes: real false,
-// distinct negative c): the first lane of a run reserves the whole run in
-// cell_count with one atomic.  Returns the run's first rank in its cell and
-// the run's first lane.  All lanes of the wavefront take part.
+// Runs of consecutive lanes with the same value c: whether this lane starts
+// its run, and the run's length.  All lanes of the wavefront take part.
+__device__ inline uint64_t run_heads(int c, bool &head)
+{
+    const int prev = __shfl_up(c, 1, 64);
+    head = (lane_id() == 0) || (prev != c);
+    return __ballot(head);
+}
+// Lane after the last one of the run that starts at this lane.
+__device__ inline int run_end(uint64_t heads)
+{
+    const int lane = lane_id();
+    const uint64_t above = lane == 63 ? 0ull : heads >> (lane + 1);
+    return above ? lane + __ffsll((long long)above) : 64;
+}
+__device__ inline int run_length(int c, bool &head)  // of the lanes that start a run
+{
+    return run_end(run_heads(c, head)) - lane_id();
+}
+
+// The first lane of a run of equal cells (padding lanes: real false, distinct
+// negative c) reserves the whole run in cell_count with one atomic.  Returns
+// the run's first rank in its cell and the run's first lane.
 __device__ inline int run_reserve(int32_t *cell_count, int c, bool real, int &first)
 {
     const int lane = lane_id();
-    const int prev = __shfl_up(c, 1, 64);
-    const bool head = (lane == 0) || (prev != c);
-    const uint64_t heads = __ballot(head);
+    bool head;
+    const uint64_t heads = run_heads(c, head);
     const uint64_t below = lane == 63 ? ~0ull : ((1ull << (lane + 1)) - 1ull);
     first = 63 - __clzll((long long)(heads & below));  // head of my run
-    const uint64_t above = heads & ~below;
-    const int next = above ? __ffsll((long long)above) - 1 : 64;  // head of the next run
     int base = 0;
-    if (head && real) base = atomicAdd(&cell_count[c], next - lane);
+    if (head && real) base = atomicAdd(&cell_count[c], run_end(heads) - lane);
     return __shfl(base, first, 64);
 }
 

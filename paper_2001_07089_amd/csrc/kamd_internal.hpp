@@ -123,10 +123,11 @@ struct Dev {
     const RepInfo *rep;
     const int32_t *wave_seg;
     // cells and lists
-    int32_t *cell_of, *rank, *cell_count, *cell_start, *cell_end, *order;
+    int32_t *cell_of, *cell_count, *cell_start, *cell_end;
+    int32_t *cell_head, *order, *rank;  // counting sort: chains of slot runs (k_rb_assign); rank also k_rb_gather's slots
     int32_t *rb_force;    // per replica: rebuild at the next check regardless
-    int32_t *rb_any;      // [2]: [0] the number of waves that rebuild this step (gate kernel)
-    int32_t *rb_wlist;    // [nwaves]: those waves, replica by replica (gate kernel)
+    int32_t *rb_any;      // [2]: [0] the number of waves that rebuild this step (gate)
+    int32_t *rb_wlist;    // [nwaves]: those waves, replica by replica (gate)
     uint32_t *maxdisp;    // per replica: max |r - r_build|^2 (float bits) since the last check
     int32_t *nbr;         // per wave: rows x 64 entries, see list_index
     int2 *kmax;           // per wave: entries of the A part, entries of the B part
@@ -171,7 +172,7 @@ struct Dev {
     int32_t rep_waves_max; // wavefronts of the largest replica
     int32_t sort_small;   // every replica within SORT_SLOTS and SORT_CELLS
     int32_t scan_cps;     // scan chunks (SCAN_CHUNK cells) of the largest segment
-    int32_t *chunk_sum;   // [nseg][scan_cps]: particles of each scan chunk (segments of several chunks)
+    int32_t *chunk_sum;   // [nseg][scan_cps]: particles of each scan chunk (segments of many chunks)
 };
 
 
@@ -187,7 +188,6 @@ hipError_t launch_rb_sort_small(const Dev &d, hipStream_t s);  // plans with sor
 hipError_t launch_rb_gate(const Dev &d, hipStream_t s);
 hipError_t launch_rb_assign(const Dev &d, hipStream_t s);
 hipError_t launch_rb_scan(const Dev &d, int nseg, hipStream_t s);
-hipError_t launch_rb_scatter(const Dev &d, hipStream_t s);
 hipError_t launch_rb_sortgather(const Dev &d, hipStream_t s);
 hipError_t launch_rb_list(const Dev &d, int cell_div, hipStream_t s);
 

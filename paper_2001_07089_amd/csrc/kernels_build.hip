@@ -11,18 +11,18 @@
 // rebuilt when some particle of the replica has moved more than skin/2 since
 // the last build (so no pair can enter the cutoff unseen).
 //
-// A rebuild runs as a gate and five (six) kernels, all launched on every
-// step, so that the decision stays on the device and the step loop can be
-// captured in a HIP graph:
+// A rebuild runs as a few kernels, all launched on every step, so that the
+// decision stays on the device and the step loop can be captured in a HIP
+// graph:
 //   rb_gate       one block: rebuild flag of every replica (rebuild_flag),
-//                 worklist of the waves of the replicas that rebuild
-//   rb_assign     per listed wave: sub-cell index and rank inside the
-//                 sub-cell of its particles (one atomic per run of lanes that
-//                 share a sub-cell)
-//   rb_scan_sum   per chunk of a segment's cells (segments of several chunks
+//                 worklist of the waves of the replicas that rebuild (several
+//                 replicas only: a single one's flag is decided in rb_assign)
+//   rb_assign     per listed wave: sub-cell index of its particles; runs of
+//                 lanes that share a sub-cell are counted and linked
+//   rb_scan_sum   per chunk of a segment's cells (segments of many chunks
 //                 only): the particles of the chunk
-//   rb_scan       per chunk: exclusive scan of the counters -> cell ranges
-//   rb_scatter    per listed wave: provisional destination slot
+//   rb_scan       per chunk of a segment's cells: exclusive scan of the
+//                 counters -> cell ranges
 //   rb_sortgather per listed particle: its rank by previous slot inside its
 //                 sub-cell (a stable sort: the result does not depend on
 //                 atomic timing), its state gathered into the scratch
@@ -177,6 +177,13 @@ __device__ inline int rb_work_wave(const Dev &d)
 
 // The per-particle kernels of the chain walk the worklist with a grid
 // stride over a capped grid (their work per unit is small).
+//
+// Lanes of one sub-cell are mostly consecutive (the slots are still in the
+// order of the previous build).  The first lane of such a run counts the whole
+// run and links it into the sub-cell's chain of runs: order[first slot] is the
+// run before it, rank[first slot] its length, cell_head the last one linked.
+// The chain needs no end mark and cell_head no clearing: the sub-cell's count
+// says when all of its runs are found.
 __device__ inline void assign_wave(const Dev &d, int w)
 {
     const SegInfo &S = d.seg[d.wave_seg[w]];
@@ -192,33 +199,51 @@ __device__ inline void assign_wave(const Dev &d, int w)
         c = CELL_SUBX * (S.cell0 + (cz * nc + fix_cell(m.y, nc)) * nc) + fix_cell(m.x, CELL_SUBX * nc);
         d.cell_of[s] = c;
     }
-    // the slots are still in the order of the previous build, so most
-    // neighbours share a cell
-    int first;
-    const int base = run_reserve(d.cell_count, c, real, first);
-    if (real) d.rank[s] = base + (lane - first);
+    bool head;
+    const int len = run_length(c, head);
+    if (head && real) {
+        atomicAdd(&d.cell_count[c], len);
+        d.order[s] = atomicExch(&d.cell_head[c], s);
+        d.rank[s] = len;
+    }
 }
 
+// Chains without the gate (a single replica) decide here: each block by
+// itself, the first one for the kernels after it.
 __global__ __launch_bounds__(BLOCK) void k_rb_assign(Dev d)
 {
-    const int nact = d.rb_any[0];
-    if (nact == 0) return;
+    const bool gate = d.nrep == 1;
+    int nact;
+    if (gate) {
+        nact = rebuild_flag(d, 0, false) ? d.nwaves : 0;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            d.rb_any[0] = nact;
+            d.rb_any[1] = 0;
+        }
+    } else {
+        nact = d.rb_any[0];
+    }
     const int stride = gridDim.x * WAVES_PER_BLOCK;
-    for (int i = blockIdx.x * WAVES_PER_BLOCK + (threadIdx.x >> 6); i < nact; i += stride)
-        assign_wave(d, d.rb_wlist[i]);
+    for (int i = blockIdx.x * WAVES_PER_BLOCK + (threadIdx.x >> 6); i < nact; i += stride) {
+        if (gate && lane_id() == 0) d.rb_wlist[i] = i;
+        assign_wave(d, gate ? i : d.rb_wlist[i]);
+    }
 }
 
 // Exclusive scan of each segment's sub-cell counters into absolute slot
 // ranges [cell_start, cell_end).  A segment's cells come in chunks of
 // SCAN_CHUNK (8 consecutive cells per thread of a SCAN_THREADS block; block
-// (segment, chunk) of a two-dimensional grid).  A segment of more than one
-// chunk first has each chunk's total written by k_rb_scan_sum; k_rb_scan then
-// starts each chunk at the segment's first slot plus the totals of the chunks
-// before it (at most d.scan_cps - 1 of them), so that the chunks of a large
-// system are scanned in parallel instead of one after another.  A cell's
-// CELL_SUBX = 4 sub-cell counters are read as one int4 and its ranges written
-// as int4s, so a pass moves no more loads and stores than a scan of the cells
-// alone would.
+// (segment, chunk) of a two-dimensional grid).  Each chunk starts at the
+// segment's first slot plus the totals of the chunks before it, so that the
+// chunks of a large system are scanned in parallel instead of one after
+// another.  Segments of up to SCAN_DIRECT chunks have them summed by each
+// chunk itself, larger ones by k_rb_scan_sum: a launch on every step (2 us)
+// against some microseconds on the steps that rebuild.  (Totals counted by
+// atomics in k_rb_assign: 15 -> 190 us at 2^20, whose wavefronts queue for
+// 150 addresses.)  A cell's CELL_SUBX = 4 sub-cell counters are read as one
+// int4 and its ranges written as int4s, so a pass moves no more loads and
+// stores than a scan of the cells alone would.
+constexpr int SCAN_DIRECT = 8;
 static_assert(CELL_SUBX == 4, "the scan reads the sub-cells of a cell as one int4");
 
 __device__ inline int chunk_cells(const SegInfo &S, int c)
@@ -229,6 +254,19 @@ __device__ inline int chunk_cells(const SegInfo &S, int c)
 constexpr int SCAN_THREADS = SCAN_CHUNK / 8;
 constexpr int SCAN_WAVES = SCAN_THREADS / WAVE;
 
+// Particles of the cells cnt[8 t .. 8 t + 7] (of n).
+__device__ inline int scan_sum8(const int4 *cnt, int n, int4 v[8])
+{
+    int sum = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int i = 8 * threadIdx.x + k;
+        v[k] = i < n ? cnt[i] : make_int4(0, 0, 0, 0);
+        sum += v[k].x + v[k].y + v[k].z + v[k].w;
+    }
+    return sum;
+}
+
 __global__ __launch_bounds__(SCAN_THREADS) void k_rb_scan_sum(Dev d)
 {
     __shared__ int wtot[SCAN_WAVES];
@@ -237,21 +275,12 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_rb_scan_sum(Dev d)
     const int c = blockIdx.y;
     const int n = chunk_cells(S, c);
     if (n <= 0 || !rebuild_flag(d, S.rep, d.rb_any[1] != 0)) return;
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    int4 v[8];
     const int4 *cnt = reinterpret_cast<const int4 *>(d.cell_count + CELL_SUBX * (S.cell0 + c * SCAN_CHUNK));
-    int sum = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const int i = 8 * t + k;
-        if (i < n) {
-            const int4 v = cnt[i];
-            sum += v.x + v.y + v.z + v.w;
-        }
-    }
-    sum = wave_sum_i(sum);
-    if (lane == 0) wtot[wv] = sum;
+    const int sum = wave_sum_i(scan_sum8(cnt, n, v));
+    if (lane_id() == 0) wtot[threadIdx.x >> 6] = sum;
     __syncthreads();
-    if (t == 0) {
+    if (threadIdx.x == 0) {
         int tot = 0;
         for (int k = 0; k < SCAN_WAVES; ++k) tot += wtot[k];
         d.chunk_sum[blockIdx.x * d.scan_cps + c] = tot;
@@ -260,31 +289,29 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_rb_scan_sum(Dev d)
 
 __global__ __launch_bounds__(SCAN_THREADS) void k_rb_scan(Dev d)
 {
-    __shared__ int wtot[SCAN_WAVES];
-    __shared__ int carry_s;
+    __shared__ int wtot[SCAN_WAVES], wcarry[SCAN_WAVES];
     if (d.rb_any[0] == 0) return;
     const SegInfo &S = d.seg[blockIdx.x];
     const int c = blockIdx.y;
     const int n = chunk_cells(S, c);
     if (n <= 0 || !rebuild_flag(d, S.rep, d.rb_any[1] != 0)) return;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    if (t == 0) {
-        int carry = 0;  // the particles of the segment's chunks before this one
-        for (int k = 0; k < c; ++k) carry += d.chunk_sum[blockIdx.x * d.scan_cps + k];
-        carry_s = carry;
-        if (S.type == 0 && c == 0) atomicAdd(&d.counters[0], 1);
+    int carry = 0;  // the particles of the segment's chunks before this one
+    int4 v[8];
+    if (d.scan_cps <= SCAN_DIRECT) {
+        for (int k = 0; k < c; ++k)
+            carry += scan_sum8(reinterpret_cast<const int4 *>(d.cell_count + CELL_SUBX * (S.cell0 + k * SCAN_CHUNK)),
+                               SCAN_CHUNK, v);
+    } else {
+        for (int k = t; k < c; k += SCAN_THREADS) carry += d.chunk_sum[blockIdx.x * d.scan_cps + k];
     }
+    carry = wave_sum_i(carry);
+    if (lane == 0) wcarry[wv] = carry;
+    if (t == 0 && S.type == 0 && c == 0) atomicAdd(&d.counters[0], 1);
     const int4 *cnt = reinterpret_cast<const int4 *>(d.cell_count + CELL_SUBX * (S.cell0 + c * SCAN_CHUNK));
     int4 *cst = reinterpret_cast<int4 *>(d.cell_start + CELL_SUBX * (S.cell0 + c * SCAN_CHUNK));
     int4 *cen = reinterpret_cast<int4 *>(d.cell_end + CELL_SUBX * (S.cell0 + c * SCAN_CHUNK));
-    int4 v[8];
-    int sum = 0;
-    const int i0 = 8 * t;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        v[k] = (i0 + k < n) ? cnt[i0 + k] : make_int4(0, 0, 0, 0);
-        sum += v[k].x + v[k].y + v[k].z + v[k].w;
-    }
+    const int i0 = 8 * t, sum = scan_sum8(cnt, n, v);
     int inc = sum;  // inclusive scan over the wavefront
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -295,10 +322,11 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_rb_scan(Dev d)
     __syncthreads();
     if (t == 0) {
         int run = 0;
+        for (int k = 0; k < SCAN_WAVES; ++k) run += wcarry[k];
         for (int k = 0; k < SCAN_WAVES; ++k) { const int x = wtot[k]; wtot[k] = run; run += x; }
     }
     __syncthreads();
-    int run = S.slot0 + carry_s + wtot[wv] + inc - sum;
+    int run = S.slot0 + wtot[wv] + inc - sum;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         if (i0 + k < n) {
@@ -310,19 +338,6 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_rb_scan(Dev d)
             cst[i0 + k] = a;
             cen[i0 + k] = b;
         }
-    }
-}
-
-__global__ __launch_bounds__(BLOCK) void k_rb_scatter(Dev d)
-{
-    const int nact = d.rb_any[0];
-    if (nact == 0) return;
-    const int stride = gridDim.x * WAVES_PER_BLOCK;
-    for (int i = blockIdx.x * WAVES_PER_BLOCK + (threadIdx.x >> 6); i < nact; i += stride) {
-        const int w = d.rb_wlist[i];
-        const SegInfo &S = d.seg[d.wave_seg[w]];
-        const int s = w * WAVE + lane_id();
-        if (s - S.slot0 < S.n) d.order[d.cell_start[d.cell_of[s]] + d.rank[s]] = s;
     }
 }
 
@@ -361,13 +376,19 @@ __device__ inline void gather_one(const Dev &d, int v, int t)
     d.scoarse[t] = coarse_of(m);
 }
 
-// One thread per particle of the replicas that rebuild.  The scatter put the
-// members of each sub-cell together in `order`, in the order of the atomics
-// that counted them; a particle's destination is its sub-cell's start plus
-// its rank by previous slot among those members (a loop over the sub-cell, a
-// few particles), which makes the counting sort stable.  Each member also
-// clears its sub-cell's counter for the next rebuild (a sub-cell without
-// members was never counted).
+// One thread per particle of the replicas that rebuild.  A particle's
+// destination is its sub-cell's start plus its rank by previous slot among the
+// sub-cell's members, which makes the counting sort stable: the walk over the
+// sub-cell's chain of runs (a few runs of a few particles, in the order of the
+// atomics that linked them) adds what each run holds below the particle's slot.
+// Each member also clears its sub-cell's counter for the next rebuild (a
+// sub-cell without members was never counted).
+//
+// The chain ran two kernels more, one that scattered slot numbers into their
+// sub-cells for this one to rank and, for a single replica, the gate: between
+// rebuilds each is an empty launch of 2 us.  Measured (us per step, with the
+// direct scan offsets): 32,000 particles MIXED NVE 29.1 -> 26.1, 64,000 41.6 ->
+// 36.8, 32,000 FP64 Nose-Hoover 53.0 -> 49.6, 2^20 MIXED 297 -> 293.
 __global__ __launch_bounds__(BLOCK) void k_rb_sortgather(Dev d)
 {
     const int nact = d.rb_any[0];
@@ -379,9 +400,15 @@ __global__ __launch_bounds__(BLOCK) void k_rb_sortgather(Dev d)
         const int s = w * WAVE + lane_id();
         if (s - S.slot0 < S.n) {
             const int sc = d.cell_of[s];
-            const int st = d.cell_start[sc], en = d.cell_end[sc];
-            int rank = 0;
-            for (int e = st; e < en; ++e) rank += d.order[e] < s ? 1 : 0;
+            int f = d.cell_head[sc];
+            const int st = d.cell_start[sc];
+            int left = d.cell_end[sc] - st, rank = 0;
+            while (left > 0) {
+                const int len = d.rank[f], before = d.order[f];
+                rank += min(max(s - f, 0), len);
+                left -= len;
+                f = before;
+            }
             gather_one(d, s, st + rank);
             d.cell_count[sc] = 0;
         }
@@ -396,7 +423,12 @@ __global__ __launch_bounds__(BLOCK) void k_rb_sortgather(Dev d)
 // flags of all replicas by itself (the rule of k_rb_gate), from which follow the
 // worklist's length and the place of its own replica in it.  The result is that
 // of the other chain: a stable sort by sub-cell.
-// @@MEASURED@@
+//
+// Bound by latency: on a step that rebuilds, the passes over the counters and
+// particles of one replica by one block (12 us at 1000 particles); otherwise by
+// its launch.  Measured (us per MIXED step, the chain of kernels, then this):
+// 1000 particles NVE 23.7 -> 17.4, 64 replicas of 1000 under the bath 68 -> 60,
+// 256 replicas 415 -> 402.
 constexpr int SORT_THREADS = 1024;
 constexpr int SORT_PER = SORT_SLOTS / SORT_THREADS;
 
@@ -1734,9 +1766,9 @@ hipError_t launch_rb_sort_small(const Dev &d, hipStream_t s)
     }
     return hipGetLastError();
 }
-hipError_t launch_rb_gate(const Dev &d, hipStream_t s)
+hipError_t launch_rb_gate(const Dev &d, hipStream_t s)  // a single replica: k_rb_assign decides
 {
-    hipLaunchKernelGGL(k_rb_gate, dim3(1), dim3(GATE_THREADS), 0, s, d);
+    if (d.nrep > 1) hipLaunchKernelGGL(k_rb_gate, dim3(1), dim3(GATE_THREADS), 0, s, d);
     return hipGetLastError();
 }
 hipError_t launch_rb_assign(const Dev &d, hipStream_t s)
@@ -1747,13 +1779,8 @@ hipError_t launch_rb_assign(const Dev &d, hipStream_t s)
 hipError_t launch_rb_scan(const Dev &d, int nseg, hipStream_t s)
 {
     const dim3 grid(nseg, d.scan_cps);
-    if (d.scan_cps > 1) hipLaunchKernelGGL(k_rb_scan_sum, grid, dim3(SCAN_THREADS), 0, s, d);
+    if (d.scan_cps > SCAN_DIRECT) hipLaunchKernelGGL(k_rb_scan_sum, grid, dim3(SCAN_THREADS), 0, s, d);
     hipLaunchKernelGGL(k_rb_scan, grid, dim3(SCAN_THREADS), 0, s, d);
-    return hipGetLastError();
-}
-hipError_t launch_rb_scatter(const Dev &d, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_rb_scatter, dim3(nblk_capped(d.nwaves)), dim3(BLOCK), 0, s, d);
     return hipGetLastError();
 }
 hipError_t launch_rb_sortgather(const Dev &d, hipStream_t s)

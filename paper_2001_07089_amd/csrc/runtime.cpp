@@ -452,6 +452,7 @@ static void carve_list(Dev &d, const Plan &P, Carve &k)
 {
     const size_t nsub = (size_t)CELL_SUBX * P.ncells;
     d.cell_count = k.take<int32_t>(nsub);
+    d.cell_head = k.take<int32_t>(nsub);
     d.cell_start = k.take<int32_t>(nsub);
     d.cell_end = k.take<int32_t>(nsub);
     d.chunk_sum = k.take<int32_t>(P.segs.size() * (size_t)P.scan_cps);
@@ -748,7 +749,6 @@ static int rebuild_chain(kamd_ctx *c, const Dev &d)
     HIPCHK(c, launch_rb_gate(d, c->stream));
     HIPCHK(c, launch_rb_assign(d, c->stream));
     HIPCHK(c, launch_rb_scan(d, (int)c->segs.size(), c->stream));
-    HIPCHK(c, launch_rb_scatter(d, c->stream));
     HIPCHK(c, launch_rb_sortgather(d, c->stream));
     HIPCHK(c, launch_rb_list(d, c->cell_div, c->stream));
     return KAMD_OK;

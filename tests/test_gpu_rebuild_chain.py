@@ -245,3 +245,36 @@ def test_mask_list_builder_equals_the_window_builder(count, n, L, skin, dim):
     for k in out[0][0]:
         assert np.array_equal(out[0][0][k], out[1][0][k]), k
     assert out[0][1]["mean_list_len"] == pytest.approx(out[1][1]["mean_list_len"], rel=0.006)
+
+
+@pytest.mark.parametrize("n,L,dim", [
+    (9000, 19.6, 3),      # the first sizes past the one-block sort
+    (50000, 34.7, 3),     # eight scan chunks: each sums the ones before it
+    (64000, 37.7, 3),     # nine: their totals come from a kernel of their own
+    (140000, 341.0, 2),
+])
+def test_chain_of_a_single_replica_equals_the_gated_one(n, L, dim):
+    """A single replica decides its rebuild in the assignment; beside a copy of
+    itself it goes through the gate and its worklist.  The same rebuilds, order
+    and lists: MIXED sums, which follow the list order, agree in every bit."""
+    print(f"case chain {n} dim={dim}", flush=True)
+    if dim == 2:
+        pos, v = W.planar_lattice_config(n, L, 5), W.gaussian_velocities(n, 0.5, 3)
+        vel = (v[0], v[1], np.zeros(n))
+    else:
+        pos, vel = W.lattice_config(n, L, 5, 0.12), W.gaussian_velocities(n, 0.5, 3)
+    out = []
+    for count in (1, 2):
+        s = md.System([(n, W.n_a_for(n), L, 1.0, 3)] * count, precision="mixed", skin=0.1, dim=dim, dt=0.004,
+                      positions=[np.tile(p, count) for p in pos], velocities=[np.tile(p, count) for p in vel])
+        md.md_set_force_kernel(s.ctx, 0, 256)
+        s.build_cells()
+        s.forces()
+        for _ in range(3):
+            s.step_nve(8)
+        assert s.status() == 0
+        assert md.md_stats(s.ctx)["rebuilds"] >= 4 * count
+        out.append({k: a[..., s.replica_slice(count - 1)] for k, a in s.numpy().items()})
+        s.close()
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k]), k
