@@ -128,6 +128,13 @@ __device__ inline int4 ld_stream(const int4 *p)
     return make_int4(v.x, v.y, v.z, v.w);
 }
 
+__device__ inline void st_stream(uint4 v, uint4 *p)
+{
+    typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+    const v4u w = {v.x, v.y, v.z, v.w};
+    __builtin_nontemporal_store(w, reinterpret_cast<v4u *>(p));
+}
+
 // ------------------------------------------------ integration helpers
 __device__ inline double wrap_img(double u, double L, double invL, int32_t &img)
 {

@@ -225,6 +225,13 @@ hipError_t launch_ke_partial(const Dev &d, hipStream_t s);
 
 hipError_t launch_import(const Dev &d, const double *const *arr, const int32_t *img, hipStream_t s);
 hipError_t launch_export(const Dev &d, double *const *arr, int32_t *img, hipStream_t s);
+constexpr int COPY_RANGES = 5;
+struct CopyRanges {
+    const uint4 *src[COPY_RANGES];
+    uint4 *dst[COPY_RANGES];
+    int64_t words[COPY_RANGES];  // of 16 bytes
+};
+hipError_t launch_copy_ranges(const CopyRanges &r, hipStream_t s);
 hipError_t launch_mirror(const Dev &d, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_zero_i32(int32_t *p, int64_t n, hipStream_t s);

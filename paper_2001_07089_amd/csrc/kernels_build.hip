@@ -341,14 +341,6 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_rb_scan(Dev d)
     }
 }
 
-// Non-temporal 16-byte store (the build mirror, read once per step).
-__device__ inline void st_stream(uint4 v, uint4 *p)
-{
-    typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-    v4u w = {v.x, v.y, v.z, v.w};
-    __builtin_nontemporal_store(w, reinterpret_cast<v4u *>(p));
-}
-
 // A position reduced to its high 16 bits per axis: x and y packed (x low), z.
 __device__ inline uint2 coarse_of(const uint4 &m) { return make_uint2((m.x >> 16) | (m.y & 0xffff0000u), m.z >> 16); }
 

@@ -69,8 +69,9 @@ struct kamd_ctx {
     double *Q_dev = nullptr;
     double *rep_arg = nullptr;        // per-replica host arguments staged for a kernel
     double *obs_stage = nullptr;      // device [n_rep][4]
-    double *state_tmp = nullptr;      // device caller-order staging: checkpoints, list-heal snapshots
+    double *state_tmp = nullptr;      // device staging: checkpoints (caller order), list-heal snapshots (slot order)
     int32_t *img_tmp = nullptr;
+    int32_t *id_snap = nullptr;       // particles of the slots of a list-heal snapshot
     RepDyn *dyn_snap = nullptr;       // thermostat scalars of a list-heal snapshot
     int32_t *cnt_snap = nullptr;      // device counters of a list-heal snapshot
     int64_t step = 0;
@@ -380,7 +381,7 @@ struct CtxBufs {
     double4 *pos4_alt = nullptr;
     uint32_t *md_base = nullptr;
     double *Q_dev = nullptr, *rep_arg = nullptr, *obs_stage = nullptr, *state_tmp = nullptr;
-    int32_t *img_tmp = nullptr;
+    int32_t *img_tmp = nullptr, *id_snap = nullptr;
     RepDyn *dyn_snap = nullptr;
     int32_t *cnt_snap = nullptr;
 };
@@ -440,8 +441,9 @@ static void carve_fixed(Dev &d, CtxBufs &b, const Shape &z, Carve &k)
     d.rdf_start = k.take<int32_t>(z.rdf_cells);
     d.rdf_grid = k.take<int4>(z.nrep);
     d.rdf_plan = k.take<int4>(z.nrep);
-    b.state_tmp = k.take<double>(9 * nt);
-    b.img_tmp = k.take<int32_t>(3 * nt);
+    b.state_tmp = k.take<double>(9 * np);
+    b.img_tmp = k.take<int32_t>(3 * np);
+    b.id_snap = k.take<int32_t>(np);
     b.dyn_snap = k.take<RepDyn>(z.nrep);
     b.cnt_snap = k.take<int32_t>(8);
 }
@@ -546,6 +548,7 @@ static void bind_workspace(kamd_ctx *c, const Plan &P)
     c->obs_stage = b.obs_stage;
     c->state_tmp = b.state_tmp;
     c->img_tmp = b.img_tmp;
+    c->id_snap = b.id_snap;
     c->dyn_snap = b.dyn_snap;
     c->cnt_snap = b.cnt_snap;
     Carve kl;
@@ -915,26 +918,46 @@ static int apply_list_params(kamd_ctx *c, double skin, int cell_div, bool first)
 // from.  Graph replays cannot heal: the bit stays for md_status, and
 // md_build_cells then grows the list (the caller recaptures).
 
-// The dynamical state at the start of an eager step call, in caller order.
+// The dynamical state at the start of an eager step call, as the slots hold it.
 static int snapshot_save(kamd_ctx *c)
 {
     const Dev &d = c->d;
-    const size_t nt = d.n_total;
-    double *a[9];
-    for (int k = 0; k < 9; ++k) a[k] = c->state_tmp + k * nt;
-    HIPCHK(c, launch_export(d, a, c->img_tmp, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->dyn_snap, d.dyn, sizeof(RepDyn) * c->reps.size(), hipMemcpyDeviceToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->cnt_snap, d.counters, 32, hipMemcpyDeviceToDevice, c->stream));
+    const size_t np = d.npad_total;  // a multiple of 64
+    CopyRanges r;
+    auto range = [&r](int k, const void *src, void *dst, size_t bytes) {
+        r.src[k] = static_cast<const uint4 *>(src);
+        r.dst[k] = static_cast<uint4 *>(dst);
+        r.words[k] = (int64_t)(bytes / 16);
+    };
+    static_assert(sizeof(RepDyn) % 16 == 0, "copied in 16-byte words");
+    range(0, d.x, c->state_tmp, 9 * 8 * np);  // x .. az are one array
+    range(1, d.img, c->img_tmp, 3 * 4 * np);
+    range(2, d.id, c->id_snap, 4 * np);
+    range(3, d.dyn, c->dyn_snap, sizeof(RepDyn) * c->reps.size());
+    range(4, d.counters, c->cnt_snap, 32);
+    HIPCHK(c, launch_copy_ranges(r, c->stream));
     return KAMD_OK;
 }
 
+// The particles keep the slots that they have now: the saved state goes by
+// particle through the sort's scratch arrays, which hold nothing between steps.
 static int snapshot_restore(kamd_ctx *c)
 {
     const Dev &d = c->d;
-    const size_t nt = d.n_total;
-    const double *a[9];
-    for (int k = 0; k < 9; ++k) a[k] = c->state_tmp + k * nt;
-    HIPCHK(c, launch_import(d, a, c->img_tmp, c->stream));
+    const size_t np = d.npad_total, nt = d.n_total;
+    Dev snap = d;
+    double **f[9] = {&snap.x, &snap.y, &snap.z, &snap.vx, &snap.vy, &snap.vz, &snap.ax, &snap.ay, &snap.az};
+    double *to[9];
+    const double *from[9];
+    for (int k = 0; k < 9; ++k) {
+        *f[k] = c->state_tmp + k * np;
+        to[k] = d.sx + k * nt;  // sx .. saz are one array of 9 np
+        from[k] = to[k];
+    }
+    snap.img = c->img_tmp;
+    snap.id = c->id_snap;
+    HIPCHK(c, launch_export(snap, to, d.simg, c->stream));
+    HIPCHK(c, launch_import(d, from, d.simg, c->stream));
     HIPCHK(c, hipMemcpyAsync(d.dyn, c->dyn_snap, sizeof(RepDyn) * c->reps.size(), hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(d.counters, c->cnt_snap, 32, hipMemcpyDeviceToDevice, c->stream));
     return force_rebuild_all(c);
