@@ -23,7 +23,7 @@ constexpr int BLOCK = 256;               // threads per block for slot kernels
 constexpr int WAVES_PER_BLOCK = BLOCK / WAVE;
 constexpr int LIST_ROW_ALIGN = 4;        // neighbour rows are padded to this multiple
 constexpr int CELL_SUBX = 4;             // list cells are sorted in sub-cells of a quarter
-                                         // cell edge along x (cell_count/start/end per sub-cell)
+                                         // cell edge along x (cell_count/start per sub-cell)
 constexpr int VH_MAX_BINS = 1024;       // bins of the self van Hove histogram
 constexpr int SCAN_CHUNK = 2048;         // cells per block of the cell-range scan
 constexpr int SORT_SLOTS = 8192;         // slots and sub-cells per replica up to which
@@ -123,7 +123,7 @@ struct Dev {
     const RepInfo *rep;
     const int32_t *wave_seg;
     // cells and lists
-    int32_t *cell_of, *cell_count, *cell_start, *cell_end;
+    int32_t *cell_of, *cell_count, *cell_start;  // sub-cell c holds the slots [cell_start[c], cell_start[c + 1])
     int32_t *cell_head, *order, *rank;  // counting sort: chains of slot runs (k_rb_assign); rank also k_rb_gather's slots
     int32_t *rb_force;    // per replica: rebuild at the next check regardless
     int32_t *rb_any;      // [2]: [0] the number of waves that rebuild this step (gate)

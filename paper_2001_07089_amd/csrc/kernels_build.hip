@@ -231,7 +231,8 @@ __global__ __launch_bounds__(BLOCK) void k_rb_assign(Dev d)
 }
 
 // Exclusive scan of each segment's sub-cell counters into absolute slot
-// ranges [cell_start, cell_end).  A segment's cells come in chunks of
+// numbers; a sub-cell ends where the next one starts (the last one at an entry of
+// the segment's spare cell).  A segment's cells come in chunks of
 // SCAN_CHUNK (8 consecutive cells per thread of a SCAN_THREADS block; block
 // (segment, chunk) of a two-dimensional grid).  Each chunk starts at the
 // segment's first slot plus the totals of the chunks before it, so that the
@@ -310,7 +311,6 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_rb_scan(Dev d)
     if (t == 0 && S.type == 0 && c == 0) atomicAdd(&d.counters[0], 1);
     const int4 *cnt = reinterpret_cast<const int4 *>(d.cell_count + CELL_SUBX * (S.cell0 + c * SCAN_CHUNK));
     int4 *cst = reinterpret_cast<int4 *>(d.cell_start + CELL_SUBX * (S.cell0 + c * SCAN_CHUNK));
-    int4 *cen = reinterpret_cast<int4 *>(d.cell_end + CELL_SUBX * (S.cell0 + c * SCAN_CHUNK));
     const int i0 = 8 * t, sum = scan_sum8(cnt, n, v);
     int inc = sum;  // inclusive scan over the wavefront
 #pragma unroll
@@ -330,13 +330,13 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_rb_scan(Dev d)
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         if (i0 + k < n) {
-            int4 a, b;
-            a.x = run; run += v[k].x; b.x = run;
-            a.y = run; run += v[k].y; b.y = run;
-            a.z = run; run += v[k].z; b.z = run;
-            a.w = run; run += v[k].w; b.w = run;
+            int4 a;
+            a.x = run; run += v[k].x;
+            a.y = run; run += v[k].y;
+            a.z = run; run += v[k].z;
+            a.w = run; run += v[k].w;
             cst[i0 + k] = a;
-            cen[i0 + k] = b;
+            if (c * SCAN_CHUNK + i0 + k + 1 == S.ncell) d.cell_start[CELL_SUBX * (S.cell0 + S.ncell)] = run;
         }
     }
 }
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(BLOCK) void k_rb_sortgather(Dev d)
             const int sc = d.cell_of[s];
             int f = d.cell_head[sc];
             const int st = d.cell_start[sc];
-            int left = d.cell_end[sc] - st, rank = 0;
+            int left = d.cell_start[sc + 1] - st, rank = 0;
             while (left > 0) {
                 const int len = d.rank[f], before = d.order[f];
                 rank += min(max(s - f, 0), len);
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_rb_sort_small(Dev d)
     const SegInfo &A = d.seg[R.seg[0]], &B = d.seg[R.seg[1]];
     const int base = R.wave0 * WAVE, nc = R.nc, nslot = (R.wave1 - R.wave0) * WAVE;
     const int b0 = B.slot0 - base;                            // the replica's first B slot
-    const int sub0 = CELL_SUBX * A.cell0, nsub = CELL_SUBX * (A.ncell + B.ncell);
+    const int sub0 = CELL_SUBX * A.cell0, nsub = CELL_SUBX * (A.ncell + 1 + B.ncell);  // A's spare cell between
     for (int i = t; i < R.wave1 - R.wave0; i += SORT_THREADS) d.rb_wlist[before + i] = R.wave0 + i;
     if (t == 0) atomicAdd(&d.counters[0], 1);
     for (int i = t; i < nsub; i += SORT_THREADS) start[i] = 0;
@@ -521,14 +521,14 @@ __global__ __launch_bounds__(SORT_THREADS) void k_rb_sort_small(Dev d)
     int run = inc - sum;
     for (int k = 0; k < t / WAVE; ++k) run += part[k];
     const int nsubA = CELL_SUBX * A.ncell, shift = b0 - A.n;  // B's slots start at the next wavefront
+    if (t == 0) d.cell_start[sub0 + nsub] = base + b0 + B.n;
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
         const int c = t * per + k;
         if (k < per && c < nsub) {
-            const int at = run + (c < nsubA ? 0 : shift);
+            const int at = run + (c < nsubA + CELL_SUBX ? 0 : shift);
             start[c] = at;
             d.cell_start[sub0 + c] = base + at;
-            d.cell_end[sub0 + c] = base + at + cnt[k];
         }
         run += cnt[k];
     }
@@ -542,9 +542,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_rb_sort_small(Dev d)
     for (int k = 0; k < SORT_PER; ++k)
         if (cell[k] >= 0) {
             const int l = k * SORT_THREADS + t, c = cell[k], st = start[c];
-            // the sub-cell ends where the next one starts (segments end apart)
-            const int last = c < nsubA ? A.n : b0 + B.n;
-            const int en = c + 1 == nsubA || c + 1 == nsub ? last : start[c + 1];
+            const int en = c + 1 == nsub ? b0 + B.n : start[c + 1];
             int at = st;
             for (int e = st; e < en; ++e) at += order[e] < l ? 1 : 0;
             if (GATHER) gather_one(d, base + l, base + at);
@@ -714,7 +712,7 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach, int min_wav
     const int cy = fix_cell(mi.y, nc), cz = d.dim == 2 ? 0 : fix_cell(mi.z, nc);
     // slot range [cs(c), ce(c)) of cell c (its sub-cells together)
     auto cs = [&](int c) __attribute__((always_inline)) { return d.cell_start[CELL_SUBX * c]; };
-    auto ce = [&](int c) __attribute__((always_inline)) { return d.cell_end[CELL_SUBX * c + CELL_SUBX - 1]; };
+    auto ce = [&](int c) __attribute__((always_inline)) { return d.cell_start[CELL_SUBX * (c + 1)]; };
     // a planar system has every particle in its single (z = 0) layer of cells
     const int oz0 = d.dim == 2 ? 0 : -reach, nz = d.dim == 2 ? 1 : noff;
     const double cw = 4294967296.0 / (double)nc;  // cell edge in fixed units
@@ -757,7 +755,7 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach, int min_wav
         };
         // Slot ranges of one stencil row: the main run of cells, and the end
         // cell that wraps around the box where the row does.
-        const int32_t *cstart = d.cell_start, *cend = d.cell_end;
+        const int32_t *cstart = d.cell_start, *cend = d.cell_start + 1;
         const int cell0 = SJ.cell0;  // kept in a register across the list stores
         auto bounds = [&](int oz, int oy) __attribute__((always_inline)) {
             int4 b = make_int4(0, 0, 0, 0);
@@ -1207,7 +1205,7 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list_masks(Dev d, int min_waves)
     int32_t(*buf)[WAVE] = stage[threadIdx.x / WAVE];
     uint2 *wc = win_s[threadIdx.x / WAVE];
     const int rows = d.rows;
-    const int32_t *cstart = d.cell_start, *cend = d.cell_end;
+    const int32_t *cstart = d.cell_start, *cend = d.cell_start + 1;
     int row = 0;  // 32-bit words of the list used so far
     int total = 0;
     int2 kpart = make_int2(0, 0), bpart = make_int2(-1, -1);  // per part: entries, base
@@ -1480,7 +1478,7 @@ __global__ __launch_bounds__(WAVE * LIST_ROWS) void k_rb_list_wide(Dev d, int ma
         const int cx = fx / CELL_SUBX, qx = fx % CELL_SUBX;
         const int cy = fix_cell(mi.y, nc), cz = d.dim == 2 ? 0 : fix_cell(mi.z, nc);
         const uint32_t ixy = coarse_of(mi).x, iz = coarse_of(mi).y;
-        const int32_t *cstart = d.cell_start, *cend = d.cell_end;
+        const int32_t *cstart = d.cell_start, *cend = d.cell_start + 1;
         // pieces of the lane's row: per partner type the main run of cells and
         // the end cell that wraps around (see k_rb_list); [st, en) in slots
         int st_[4], en_[4];

@@ -299,7 +299,7 @@ static void make_plan(const kamd_config *cfg, const kamd_replica *reps, int n_re
             S.slot0 = slot;
             S.n = t == 0 ? K.n_a : K.n - K.n_a;
             S.npad = (S.n + WAVE - 1) / WAVE * WAVE;
-            S.cell0 = cell;
+            S.cell0 = cell + (int32_t)P.segs.size();  // one spare cell after each segment: the end of its last range
             // a planar system keeps every particle at z = 0: one layer of cells
             S.ncell = planar ? nc * nc : nc * nc * nc;
             R.seg[t] = (int32_t)P.segs.size();
@@ -327,7 +327,7 @@ static void make_plan(const kamd_config *cfg, const kamd_replica *reps, int n_re
     }
     P.npad = slot;
     P.nwaves = slot / WAVE;
-    P.ncells = cell;
+    P.ncells = cell + (int32_t)P.segs.size();
     int rows = std::max((int)std::ceil(cap * rows_need) + 32, rows_floor);
     rows = (rows + LIST_ROW_ALIGN - 1) / LIST_ROW_ALIGN * LIST_ROW_ALIGN;
     P.rows = rows;
@@ -448,15 +448,14 @@ static void carve_fixed(Dev &d, CtxBufs &b, const Shape &z, Carve &k)
     b.cnt_snap = k.take<int32_t>(8);
 }
 
-// The part that depends on the list parameters: per sub-cell counters and
-// ranges, the scan chunk totals and the neighbour list.
+// The part that depends on the list parameters: per sub-cell counters, chains
+// and ranges, the scan chunk totals and the neighbour list.
 static void carve_list(Dev &d, const Plan &P, Carve &k)
 {
     const size_t nsub = (size_t)CELL_SUBX * P.ncells;
     d.cell_count = k.take<int32_t>(nsub);
     d.cell_head = k.take<int32_t>(nsub);
     d.cell_start = k.take<int32_t>(nsub);
-    d.cell_end = k.take<int32_t>(nsub);
     d.chunk_sum = k.take<int32_t>(P.segs.size() * (size_t)P.scan_cps);
     d.nbr = k.take<int32_t>((size_t)P.rows * P.npad);
 }
@@ -567,7 +566,7 @@ static void bind_workspace(kamd_ctx *c, const Plan &P)
         d.rep_waves_max = std::max(d.rep_waves_max, R.wave1 - R.wave0);
     }
     d.sort_small = d.rep_waves_max <= SORT_SLOTS / WAVE;
-    for (const SegInfo &S : P.segs) d.sort_small = d.sort_small && 2 * (int64_t)CELL_SUBX * S.ncell <= SORT_CELLS;
+    for (const SegInfo &S : P.segs) d.sort_small = d.sort_small && (int64_t)CELL_SUBX * (2 * S.ncell + 1) <= SORT_CELLS;
     d.ncells = P.ncells;
     d.scan_cps = P.scan_cps;
     d.rdf_cells_cap = (int64_t)c->shape.rdf_cells;
