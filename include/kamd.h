@@ -410,7 +410,7 @@ int md_get_state(kamd_ctx *ctx, void *blob, size_t *bytes);
 int md_set_state(kamd_ctx *ctx, const void *blob, size_t bytes);
 
 /* Measurement: nsteps NVE steps run eagerly on the context stream with HIP
- * events around every force-kernel launch and every streaming (drift/kick)
+ * events around every force-kernel launch and every streaming (drift)
  * launch.  host_out (host, FP64 [8]) = {mean force-kernel ms, mean streaming
  * ms per step, total ms, list rebuilds during the run, ordered pairs inside
  * the cutoff per force launch (from a closing energy pass), steps, mean

@@ -201,15 +201,6 @@ __device__ inline void drift_core(const Dev &d, int s, const RepInfo &R, double 
     if (step2 * (dt * dt) > R.run2) set_err(d.err, KAMD_DEV_RUNAWAY);
 }
 
-__device__ inline void drift_one(const Dev &d, int s, int rep, double dt, double xi, double xia,
-                                 double c, uint4 *mirror_out, float &d2)
-{
-    const double v[3] = {d.vx[s], d.vy[s], d.vz[s]};
-    const double a[3] = {d.ax[s], d.ay[s], d.az[s]};
-    DriftIn in = drift_load(d, s);
-    drift_core(d, s, d.rep[rep], dt, xi, xia, c, v, a, in, mirror_out, d2);
-}
-
 // Raise a replica's displacement maximum to m.  Read first: the maximum only
 // grows during the step, so most blocks find it already larger and skip the
 // atomic.

@@ -192,8 +192,12 @@ hipError_t launch_rb_sortgather(const Dev &d, hipStream_t s);
 hipError_t launch_rb_list(const Dev &d, int cell_div, hipStream_t s);
 
 // The force kernel also closes the step's rebuild check (resets maxdisp and
-// rb_force) and, with step_inc, advances the device step counter.
-hipError_t launch_force(const Dev &d, const Model &m, int prec, bool energy, bool step_inc, hipStream_t s);
+// rb_force).  flags:
+constexpr int FORCE_STEP = 1;     // a step: advances the device step counter; FP64: d.pos4 holds the positions
+constexpr int FORCE_KICK = 2;     // closes the step with v += c a, c = dt/2
+constexpr int FORCE_KICK_NH = 4;  // (with FORCE_KICK) c = the replica's c_kick
+constexpr int FORCE_KE = 8;       // (with FORCE_KICK) per-wave sum v^2 into wred[0]
+hipError_t launch_force(const Dev &d, const Model &m, int prec, bool energy, int flags, double dt, hipStream_t s);
 // NVE: forces fused with the closing half kick and the next drift (new
 // mirror into mirror_out, displacement maximum into md_out; FP64 also the
 // packed positions into pos4_out, which must differ from d.pos4 and is
@@ -205,17 +209,14 @@ hipError_t launch_force_kd(const Dev &d, const Model &m, int prec, double dt, ui
                            double4 *pos4_out, bool energy, int wpb, hipStream_t s);
 // Close the running rebuild check as a force launch does.
 hipError_t launch_close_check(const Dev &d, hipStream_t s);
-// Pack d.x, d.y, d.z into d.pos4 (every slot, padding included).
-hipError_t launch_pack_pos(const Dev &d, hipStream_t s);
 
 hipError_t launch_drift(const Dev &d, double dt, hipStream_t s);
 hipError_t launch_drift_nh(const Dev &d, double dt, hipStream_t s);
-hipError_t launch_kick_nve(const Dev &d, double dt, bool want_ke, hipStream_t s);
-hipError_t launch_kick_nh(const Dev &d, hipStream_t s);
 hipError_t launch_rep_reduce(const Dev &d, int mask, hipStream_t s);
-hipError_t launch_nh_begin(const Dev &d, double dt, const double *Q, hipStream_t s);
-hipError_t launch_nh_end(const Dev &d, double dt, const double *Q, hipStream_t s);
-hipError_t launch_set_k2(const Dev &d, hipStream_t s);
+// The same with the Nose-Hoover scalars: K2 <- the sum of v^2 (NH_SET), those
+// of the end of a step (NH_END), then those of the start of the next (NH_BEGIN).
+constexpr int NH_SET = 1, NH_END = 2, NH_BEGIN = 4;
+hipError_t launch_rep_reduce_nh(const Dev &d, int mask, int nh, double dt, const double *Q, hipStream_t s);
 hipError_t launch_mb_draw(const Dev &d, uint32_t tag, hipStream_t s);
 hipError_t launch_mb_draw_dev(const Dev &d, hipStream_t s);
 hipError_t launch_mb_center(const Dev &d, hipStream_t s);

@@ -37,18 +37,31 @@ namespace kamd {
 // Close the rebuild check of the running step (every kernel of the rebuild
 // chain has finished reading it) and optionally advance the device step
 // counter.  Done by the first block of every force launch.
-__device__ inline void close_step(const Dev &d, int step_inc)
+__device__ inline void close_step(const Dev &d, int flags)
 {
     if (blockIdx.x != 0) return;
     for (int r = threadIdx.x; r < d.nrep; r += blockDim.x) {
         d.maxdisp[r] = 0u;
         d.rb_force[r] = 0;
     }
-    if (step_inc && threadIdx.x == 0) d.counters[1] += 1;
+    if ((flags & FORCE_STEP) && threadIdx.x == 0) d.counters[1] += 1;
 }
 
 // The same without a force launch (after an explicit list build).
 __global__ void k_close_check(Dev d) { close_step(d, 0); }
+
+// Closing half kick of slot s: v = v_h + c a, with c = dt/2 or the replica's
+// Nose-Hoover factor.  Returns v^2.
+__device__ inline double close_kick(const Dev &d, int s, int rep, int flags, double dt, const double v[3], double ax,
+                                    double ay, double az)
+{
+    const double c = flags & FORCE_KICK_NH ? d.dyn[rep].c_kick : 0.5 * dt;
+    const double vx = fma(c, ax, v[0]), vy = fma(c, ay, v[1]), vz = fma(c, az, v[2]);
+    d.vx[s] = vx;
+    d.vy[s] = vy;
+    d.vz[s] = vz;
+    return vx * vx + vy * vy + vz * vz;
+}
 
 __device__ inline double rcp_f64(double a)
 {
@@ -85,6 +98,7 @@ __device__ inline void list_quad16(const int4 *nb, int k, int base, int jj[4])
 // FP64 positions of every slot packed as (x, y, z, 0), so that the FP64 force
 // kernel gathers a neighbour with two 16-byte loads instead of three 8-byte
 // ones: the gathers bound that kernel, and their cost is per instruction.
+// (Steps have them from the drift, or from the step before.)
 __global__ __launch_bounds__(BLOCK) void k_pack_pos(Dev d)
 {
     const int s = blockIdx.x * BLOCK + threadIdx.x;
@@ -120,11 +134,11 @@ __device__ inline void wave_lds_sync()
 constexpr int WPE_STAGED = 5;
 
 template <bool FIXED, bool ENERGY, bool KD, bool STAGE, int WPB>
-__global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(STAGE && !ENERGY ? WPE_STAGED : 1))) void k_force_mixed(Dev d, Model m, int step_inc, double dt,
+__global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(STAGE && !ENERGY ? WPE_STAGED : 1))) void k_force_mixed(Dev d, Model m, int flags, double dt,
                                                              uint4 *mirror_out, uint32_t *md_out)
 {
     __shared__ uint32_t swin[STAGE ? WPB : 1][STAGE ? 3 * STAGE_SLOTS : 1];
-    close_step(d, step_inc);
+    close_step(d, flags);
     const int w = wave_id_remapped<WPB>();
     const bool valid = w < d.nwaves;
     float d2 = 0.0f;
@@ -286,6 +300,10 @@ __global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(STAG
         d.ax[s] = fx;
         d.ay[s] = fy;
         d.az[s] = fz;
+        if ((flags & FORCE_KICK) && (s - S.slot0) < S.n) {
+            const double v[3] = {ld_stream(&d.vx[s]), ld_stream(&d.vy[s]), ld_stream(&d.vz[s])};
+            ke2 = close_kick(d, s, S.rep, flags, dt, v, fx, fy, fz);
+        }
     } else if ((s - S.slot0) < S.n) {
         const double h = 0.5 * dt;
         const double a[3] = {fx, fy, fz};
@@ -294,13 +312,15 @@ __global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(STAG
         DriftIn in = drift_load(d, s);
         drift_core(d, s, R, dt, 0.0, 0.0, h, v, a, in, mirror_out, d2);
     }
+    if (KD ? ENERGY : (flags & FORCE_KE) != 0) {
+        ke2 = wave_sum(ke2);
+        if (lane_id() == 0) d.wred[4 * w + 0] = ke2;
+    }
     if (ENERGY) {
         pe = wave_sum(pe);
         vir = wave_sum(vir);
         npair = wave_sum(npair);
-        if (KD) ke2 = wave_sum(ke2);
         if (lane_id() == 0) {
-            if (KD) d.wred[4 * w + 0] = ke2;
             d.wred[4 * w + 1] = pe;
             d.wred[4 * w + 2] = vir;
             d.wred[4 * w + 3] = npair;
@@ -339,7 +359,7 @@ __global__ __launch_bounds__(WAVE * WPB) __attribute__((amdgpu_waves_per_eu(STAG
 constexpr int SPLIT_UNIT = 8;
 
 template <int PREC, bool ENERGY, bool KD, int P>
-__device__ __forceinline__ void force_split(const Dev &d, const Model &m, int step_inc, double dt, uint4 *mirror_out,
+__device__ __forceinline__ void force_split(const Dev &d, const Model &m, int flags, double dt, uint4 *mirror_out,
                                             uint32_t *md_out, double4 *pos4_out)
 {
     constexpr bool FP64 = PREC == 0, FIXED = PREC == 2;
@@ -353,7 +373,7 @@ __device__ __forceinline__ void force_split(const Dev &d, const Model &m, int st
     __shared__ float osum[ORD ? 2 : 1][ORD ? 5 : 1][ORD ? WAVE : 1];  // ordered sums per part: x, y, z, e, v
     __shared__ double psum[ORD_F ? 1 : P][ND][ORD_F ? 1 : WAVE];
     __shared__ int ncut[ENERGY ? P : 1][ENERGY ? 2 : 1][ENERGY ? WAVE : 1];
-    close_step(d, step_inc);
+    close_step(d, flags);
     const int w = xcd_block(blockIdx.x, gridDim.x);
     const int q = threadIdx.x >> 6, lane = lane_id();
     const SegInfo &S = d.seg[d.wave_seg[w]];
@@ -362,8 +382,8 @@ __device__ __forceinline__ void force_split(const Dev &d, const Model &m, int st
     const double L = R.L, invL = R.invL;
     double v0[3] = {0.0, 0.0, 0.0};
     DriftIn in;
-    if (KD && q == 0) {  // in flight during the walk
-        in = drift_load(d, s);
+    if (q == 0 && (KD || (flags & FORCE_KICK))) {  // in flight during the walk
+        if (KD) in = drift_load(d, s);
         v0[0] = ld_stream(&d.vx[s]);
         v0[1] = ld_stream(&d.vy[s]);
         v0[2] = ld_stream(&d.vz[s]);
@@ -615,6 +635,7 @@ __device__ __forceinline__ void force_split(const Dev &d, const Model &m, int st
         d.ax[s] = fx;
         d.ay[s] = fy;
         d.az[s] = fz;
+        if ((flags & FORCE_KICK) && (s - S.slot0) < S.n) ke2 = close_kick(d, s, S.rep, flags, dt, v0, fx, fy, fz);
     } else if ((s - S.slot0) < S.n) {
         const double h = 0.5 * dt;
         const double a[3] = {fx, fy, fz};
@@ -625,13 +646,15 @@ __device__ __forceinline__ void force_split(const Dev &d, const Model &m, int st
     } else if (FP64) {
         pos4_out[s] = make_double4(xi, yi, zi, 0.0);
     }
+    if (KD ? ENERGY : (flags & FORCE_KE) != 0) {
+        ke2 = wave_sum(ke2);
+        if (lane == 0) d.wred[4 * w + 0] = ke2;
+    }
     if (ENERGY) {
         pe = wave_sum(pe);
         vir = wave_sum(vir);
         npair = wave_sum(npair);
-        if (KD) ke2 = wave_sum(ke2);
         if (lane == 0) {
-            if (KD) d.wred[4 * w + 0] = ke2;
             d.wred[4 * w + 1] = pe;
             d.wred[4 * w + 2] = vir;
             d.wred[4 * w + 3] = npair;
@@ -644,17 +667,17 @@ __device__ __forceinline__ void force_split(const Dev &d, const Model &m, int st
 }
 
 template <bool ENERGY, bool KD, int P>
-__global__ __launch_bounds__(WAVE * P) void k_force_fp64(Dev d, Model m, int step_inc, double dt, uint4 *mirror_out,
+__global__ __launch_bounds__(WAVE * P) void k_force_fp64(Dev d, Model m, int flags, double dt, uint4 *mirror_out,
                                                          uint32_t *md_out, double4 *pos4_out)
 {
-    force_split<0, ENERGY, KD, P>(d, m, step_inc, dt, mirror_out, md_out, pos4_out);
+    force_split<0, ENERGY, KD, P>(d, m, flags, dt, mirror_out, md_out, pos4_out);
 }
 
 template <bool FIXED, bool ENERGY, bool KD, int P>
-__global__ __launch_bounds__(WAVE * P) void k_force_split(Dev d, Model m, int step_inc, double dt, uint4 *mirror_out,
+__global__ __launch_bounds__(WAVE * P) void k_force_split(Dev d, Model m, int flags, double dt, uint4 *mirror_out,
                                                           uint32_t *md_out)
 {
-    force_split<FIXED ? 2 : 1, ENERGY, KD, P>(d, m, step_inc, dt, mirror_out, md_out, nullptr);
+    force_split<FIXED ? 2 : 1, ENERGY, KD, P>(d, m, flags, dt, mirror_out, md_out, nullptr);
 }
 
 // Wavefronts that share a list, by the number of particle wavefronts.
@@ -680,97 +703,98 @@ constexpr int SPLIT8_WAVES = 512, SPLIT4_WAVES = 1024, SPLIT_ORD_WAVES = 1024, S
 constexpr int SPLIT_ORD_ENERGY_WAVES = 2048;
 
 template <bool ENERGY, bool KD, int P>
-static void launch_fp64(const Dev &d, const Model &m, int si, double dt, uint4 *mirror_out, uint32_t *md_out,
+static void launch_fp64(const Dev &d, const Model &m, int flags, double dt, uint4 *mirror_out, uint32_t *md_out,
                         double4 *pos4_out, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_force_fp64<ENERGY, KD, P>), dim3(d.nwaves), dim3(WAVE * P), 0, s, d, m, si, dt, mirror_out,
+    hipLaunchKernelGGL((k_force_fp64<ENERGY, KD, P>), dim3(d.nwaves), dim3(WAVE * P), 0, s, d, m, flags, dt, mirror_out,
                        md_out, pos4_out);
 }
 
 template <bool ENERGY, bool KD>
-static void launch_fp64(const Dev &d, const Model &m, int si, double dt, uint4 *mirror_out, uint32_t *md_out,
+static void launch_fp64(const Dev &d, const Model &m, int flags, double dt, uint4 *mirror_out, uint32_t *md_out,
                         double4 *pos4_out, hipStream_t s)
 {
-    if (d.nwaves <= SPLIT8_WAVES) launch_fp64<ENERGY, KD, 8>(d, m, si, dt, mirror_out, md_out, pos4_out, s);
-    else launch_fp64<ENERGY, KD, 4>(d, m, si, dt, mirror_out, md_out, pos4_out, s);
+    if (d.nwaves <= SPLIT8_WAVES) launch_fp64<ENERGY, KD, 8>(d, m, flags, dt, mirror_out, md_out, pos4_out, s);
+    else launch_fp64<ENERGY, KD, 4>(d, m, flags, dt, mirror_out, md_out, pos4_out, s);
 }
 
 template <bool FIXED, bool ENERGY, bool KD, int P>
-static bool launch_split(const Dev &d, const Model &m, int si, double dt, uint4 *mirror_out, uint32_t *md_out,
+static bool launch_split(const Dev &d, const Model &m, int flags, double dt, uint4 *mirror_out, uint32_t *md_out,
                          hipStream_t s)
 {
-    hipLaunchKernelGGL((k_force_split<FIXED, ENERGY, KD, P>), dim3(d.nwaves), dim3(WAVE * P), 0, s, d, m, si, dt,
+    hipLaunchKernelGGL((k_force_split<FIXED, ENERGY, KD, P>), dim3(d.nwaves), dim3(WAVE * P), 0, s, d, m, flags, dt,
                        mirror_out, md_out);
     return true;
 }
 
 // False: the rule leaves this launch to k_force_mixed.
 template <bool FIXED, bool ENERGY, bool KD>
-static bool launch_split(const Dev &d, const Model &m, int si, double dt, uint4 *mirror_out, uint32_t *md_out,
+static bool launch_split(const Dev &d, const Model &m, int flags, double dt, uint4 *mirror_out, uint32_t *md_out,
                          hipStream_t s)
 {
     const int nw = d.nwaves;
     if (d.stage_ok) return false;  // window lists
     if constexpr (ENERGY) {
-        return nw <= SPLIT_ORD_ENERGY_WAVES && launch_split<FIXED, ENERGY, KD, 4>(d, m, si, dt, mirror_out, md_out, s);
+        return nw <= SPLIT_ORD_ENERGY_WAVES && launch_split<FIXED, ENERGY, KD, 4>(d, m, flags, dt, mirror_out, md_out, s);
     } else if constexpr (FIXED) {
-        if (nw <= SPLIT8_WAVES) return launch_split<FIXED, ENERGY, KD, 8>(d, m, si, dt, mirror_out, md_out, s);
-        if (nw <= SPLIT4_WAVES) return launch_split<FIXED, ENERGY, KD, 4>(d, m, si, dt, mirror_out, md_out, s);
-        return launch_split<FIXED, ENERGY, KD, 2>(d, m, si, dt, mirror_out, md_out, s);
+        if (nw <= SPLIT8_WAVES) return launch_split<FIXED, ENERGY, KD, 8>(d, m, flags, dt, mirror_out, md_out, s);
+        if (nw <= SPLIT4_WAVES) return launch_split<FIXED, ENERGY, KD, 4>(d, m, flags, dt, mirror_out, md_out, s);
+        return launch_split<FIXED, ENERGY, KD, 2>(d, m, flags, dt, mirror_out, md_out, s);
     } else {
-        if (nw <= SPLIT_ORD_WAVES) return launch_split<FIXED, ENERGY, KD, 4>(d, m, si, dt, mirror_out, md_out, s);
-        return nw <= SPLIT1_WAVES && launch_split<FIXED, ENERGY, KD, 1>(d, m, si, dt, mirror_out, md_out, s);
+        if (nw <= SPLIT_ORD_WAVES) return launch_split<FIXED, ENERGY, KD, 4>(d, m, flags, dt, mirror_out, md_out, s);
+        return nw <= SPLIT1_WAVES && launch_split<FIXED, ENERGY, KD, 1>(d, m, flags, dt, mirror_out, md_out, s);
     }
 }
 
 // The unsplit mixed kernel, with windows (as the lists were built) or where
 // launch_split leaves it the launch, in blocks of WPB wavefronts.
 template <bool FIXED, bool ENERGY, bool KD, int WPB>
-static void launch_mixed_wpb(const Dev &d, const Model &m, int si, double dt, uint4 *mirror_out, uint32_t *md_out,
+static void launch_mixed_wpb(const Dev &d, const Model &m, int flags, double dt, uint4 *mirror_out, uint32_t *md_out,
                              hipStream_t s)
 {
     const int nb = (d.nwaves + WPB - 1) / WPB;
     if (d.stage_ok) {
-        hipLaunchKernelGGL((k_force_mixed<FIXED, ENERGY, KD, true, WPB>), dim3(nb), dim3(WAVE * WPB), 0, s, d, m, si,
+        hipLaunchKernelGGL((k_force_mixed<FIXED, ENERGY, KD, true, WPB>), dim3(nb), dim3(WAVE * WPB), 0, s, d, m, flags,
                            dt, mirror_out, md_out);
-    } else if (!launch_split<FIXED, ENERGY, KD>(d, m, si, dt, mirror_out, md_out, s)) {
+    } else if (!launch_split<FIXED, ENERGY, KD>(d, m, flags, dt, mirror_out, md_out, s)) {
         if constexpr (!FIXED || ENERGY)
             hipLaunchKernelGGL((k_force_mixed<FIXED, ENERGY, KD, false, WPB>), dim3(nb), dim3(WAVE * WPB), 0, s, d, m,
-                               si, dt, mirror_out, md_out);
+                               flags, dt, mirror_out, md_out);
     }
 }
 
 template <bool FIXED, bool ENERGY, bool KD>
-static void launch_mixed(const Dev &d, const Model &m, int si, double dt, uint4 *mirror_out, uint32_t *md_out,
+static void launch_mixed(const Dev &d, const Model &m, int flags, double dt, uint4 *mirror_out, uint32_t *md_out,
                          int wpb, hipStream_t s)
 {
-    if (wpb == 1) launch_mixed_wpb<FIXED, ENERGY, KD, 1>(d, m, si, dt, mirror_out, md_out, s);
-    else if (wpb == 2) launch_mixed_wpb<FIXED, ENERGY, KD, 2>(d, m, si, dt, mirror_out, md_out, s);
-    else launch_mixed_wpb<FIXED, ENERGY, KD, 4>(d, m, si, dt, mirror_out, md_out, s);
+    if (wpb == 1) launch_mixed_wpb<FIXED, ENERGY, KD, 1>(d, m, flags, dt, mirror_out, md_out, s);
+    else if (wpb == 2) launch_mixed_wpb<FIXED, ENERGY, KD, 2>(d, m, flags, dt, mirror_out, md_out, s);
+    else launch_mixed_wpb<FIXED, ENERGY, KD, 4>(d, m, flags, dt, mirror_out, md_out, s);
 }
 
-// Force-only launches (md_forces, the last step of a call, Nose-Hoover):
-// unsplit ones in blocks of WAVES_PER_BLOCK wavefronts.
-hipError_t launch_force(const Dev &d, const Model &m, int prec, bool energy, bool step_inc, hipStream_t s)
+// Launches that store the forces (md_forces; the last step of a call and the
+// steps under a thermostat, which kick): unsplit ones in blocks of
+// WAVES_PER_BLOCK wavefronts.
+hipError_t launch_force(const Dev &d, const Model &m, int prec, bool energy, int flags, double dt, hipStream_t s)
 {
-    const int si = step_inc ? 1 : 0;
     constexpr int W4 = WAVES_PER_BLOCK;
     if (prec == 0) {
-        hipLaunchKernelGGL(k_pack_pos, dim3((d.npad_total + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, d);
+        if (!(flags & FORCE_STEP))
+            hipLaunchKernelGGL(k_pack_pos, dim3((d.npad_total + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, d);
         if (energy)
-            launch_fp64<true, false>(d, m, si, 0.0, nullptr, nullptr, nullptr, s);
+            launch_fp64<true, false>(d, m, flags, dt, nullptr, nullptr, nullptr, s);
         else
-            launch_fp64<false, false>(d, m, si, 0.0, nullptr, nullptr, nullptr, s);
+            launch_fp64<false, false>(d, m, flags, dt, nullptr, nullptr, nullptr, s);
     } else if (prec == 1) {
         if (energy)
-            launch_mixed_wpb<false, true, false, W4>(d, m, si, 0.0, nullptr, nullptr, s);
+            launch_mixed_wpb<false, true, false, W4>(d, m, flags, dt, nullptr, nullptr, s);
         else
-            launch_mixed_wpb<false, false, false, W4>(d, m, si, 0.0, nullptr, nullptr, s);
+            launch_mixed_wpb<false, false, false, W4>(d, m, flags, dt, nullptr, nullptr, s);
     } else {
         if (energy)
-            launch_mixed_wpb<true, true, false, W4>(d, m, si, 0.0, nullptr, nullptr, s);
+            launch_mixed_wpb<true, true, false, W4>(d, m, flags, dt, nullptr, nullptr, s);
         else
-            launch_mixed_wpb<true, false, false, W4>(d, m, si, 0.0, nullptr, nullptr, s);
+            launch_mixed_wpb<true, false, false, W4>(d, m, flags, dt, nullptr, nullptr, s);
     }
     return hipGetLastError();
 }
@@ -781,12 +805,6 @@ hipError_t launch_close_check(const Dev &d, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_pack_pos(const Dev &d, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_pack_pos, dim3((d.npad_total + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, d);
-    return hipGetLastError();
-}
-
 hipError_t launch_force_kd(const Dev &d, const Model &m, int prec, double dt, uint4 *mirror_out, uint32_t *md_out,
                            double4 *pos4_out, bool energy, int wpb, hipStream_t s)
 {
@@ -794,19 +812,19 @@ hipError_t launch_force_kd(const Dev &d, const Model &m, int prec, double dt, ui
     if (prec == 0) {
         if (!d.pos4 || !pos4_out || pos4_out == d.pos4) return hipErrorInvalidValue;
         if (energy)
-            launch_fp64<true, true>(d, m, 1, dt, mirror_out, md_out, pos4_out, s);
+            launch_fp64<true, true>(d, m, FORCE_STEP, dt, mirror_out, md_out, pos4_out, s);
         else
-            launch_fp64<false, true>(d, m, 1, dt, mirror_out, md_out, pos4_out, s);
+            launch_fp64<false, true>(d, m, FORCE_STEP, dt, mirror_out, md_out, pos4_out, s);
     } else if (prec == 1) {
         if (energy)
-            launch_mixed<false, true, true>(d, m, 1, dt, mirror_out, md_out, wpb, s);
+            launch_mixed<false, true, true>(d, m, FORCE_STEP, dt, mirror_out, md_out, wpb, s);
         else
-            launch_mixed<false, false, true>(d, m, 1, dt, mirror_out, md_out, wpb, s);
+            launch_mixed<false, false, true>(d, m, FORCE_STEP, dt, mirror_out, md_out, wpb, s);
     } else if (prec == 2) {
         if (energy)
-            launch_mixed<true, true, true>(d, m, 1, dt, mirror_out, md_out, wpb, s);
+            launch_mixed<true, true, true>(d, m, FORCE_STEP, dt, mirror_out, md_out, wpb, s);
         else
-            launch_mixed<true, false, true>(d, m, 1, dt, mirror_out, md_out, wpb, s);
+            launch_mixed<true, false, true>(d, m, FORCE_STEP, dt, mirror_out, md_out, wpb, s);
     } else {
         return hipErrorInvalidValue;
     }

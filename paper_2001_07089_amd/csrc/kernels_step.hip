@@ -7,7 +7,7 @@
 //           wrap into [0, L) counting images; refresh the u32 mirror and the
 //           displacement since the last list build
 //   force:  a = F(r)
-//   kick:   v = v_h + c a
+//   kick:   v = v_h + c a  (in the force kernel)
 // With xi = xi_a = 0 and c = dt/2 this is the NVE step exactly
 // (r += v dt + a dt^2/2, v += a dt/2 twice).  With the Nose-Hoover values of
 // Appendix B (c = dt/2 (1 - dt/2 xi_a)) the two velocity halves add up to
@@ -41,6 +41,8 @@ __device__ inline bool slot_ctx(const Dev &d, SlotCtx &c)
     return true;
 }
 
+// FP64: also the packed positions that the force kernel gathers (padding slots:
+// their own, which keeps their list entry at zero separation).
 __global__ __launch_bounds__(BLOCK) void k_drift(Dev d, double dt, int nh)
 {
     SlotCtx c;
@@ -52,37 +54,33 @@ __global__ __launch_bounds__(BLOCK) void k_drift(Dev d, double dt, int nh)
             const RepDyn &D = d.dyn[c.rep];
             xi = D.xi; xia = D.xia; ck = D.c_kick;
         }
-        drift_one(d, c.s, c.rep, dt, xi, xia, ck, d.mirror, d2);
+        const int s = c.s;
+        const double v[3] = {d.vx[s], d.vy[s], d.vz[s]};
+        const double a[3] = {d.ax[s], d.ay[s], d.az[s]};
+        DriftIn in = drift_load(d, s);
+        drift_core(d, s, d.rep[c.rep], dt, xi, xia, ck, v, a, in, d.mirror, d2);
+        if (d.pos4) d.pos4[s] = make_double4(in.r[0], in.r[1], in.r[2], 0.0);
+    } else if (valid && d.pos4) {
+        d.pos4[c.s] = make_double4(d.x[c.s], d.y[c.s], d.z[c.s], 0.0);
     }
     block_disp_max(d.maxdisp, valid, valid ? c.rep : -1, d2);
-}
-
-// v = v_h + c a, with c the replica's kick factor; optional per-wave sum v^2.
-__global__ __launch_bounds__(BLOCK) void k_kick(Dev d, double c_nve, int nh, int want_ke)
-{
-    SlotCtx c;
-    if (!slot_ctx(d, c)) return;
-    double k2 = 0.0;
-    if (c.real) {
-        const double ck = nh ? d.dyn[c.rep].c_kick : c_nve;
-        const int s = c.s;
-        const double vx = fma(ck, d.ax[s], d.vx[s]);
-        const double vy = fma(ck, d.ay[s], d.vy[s]);
-        const double vz = fma(ck, d.az[s], d.vz[s]);
-        d.vx[s] = vx; d.vy[s] = vy; d.vz[s] = vz;
-        k2 = vx * vx + vy * vy + vz * vz;
-    }
-    if (want_ke) {
-        k2 = wave_sum(k2);
-        if (lane_id() == 0) d.wred[4 * c.w + 0] = k2;
-    }
 }
 
 // Per-replica sum of the 4 per-wave partials (fixed order).  what: 0 -> rsum.
 // Each thread reads a wave's four partials as one 32-byte load, four waves
 // (BLOCK apart) per pass, so that a replica of many waves (16,384 at N =
 // 2^20) is read in a quarter of the dependent passes.
-__global__ __launch_bounds__(BLOCK) void k_rep_reduce(Dev d, int mask)
+//
+// Nose-Hoover (Appendix B; X = d N degrees of freedom), with K = sum v(t)^2
+// before the drift and G = (K - X T) / Q: ln s += xi dt + G dt^2/2
+// (Eq. (Noseupdate_lns)), xi_a = xi + G dt (Eq. (Noseupdate_xiapprox)), c =
+// dt/2 (1 - dt/2 xi_a); after the closing kick xi(t+dt) = xi + dt/2 (G + G'),
+// G' from the new velocities (Eq. (FoxAndersen_ydottplush) for y = ln s), and K
+// <- sum v(t+dt)^2.  The end of a step and the start of the next follow from
+// the sum that this kernel has, so it does both.  Measured, with the kick in the
+// force kernel and the packed positions from the drift (11 -> 7 launches): 32,000
+// particles in FP64 49.5 -> 39.5 us per step.
+__global__ __launch_bounds__(BLOCK) void k_rep_reduce(Dev d, int mask, int nh, double dt, const double *Q)
 {
     __shared__ double red[4][BLOCK];
     const int r = blockIdx.x;
@@ -114,46 +112,24 @@ __global__ __launch_bounds__(BLOCK) void k_rep_reduce(Dev d, int mask)
         __syncthreads();
     }
     if (threadIdx.x < 4 && (mask & (1 << threadIdx.x))) d.rsum[4 * r + threadIdx.x] = red[threadIdx.x][0];
-}
-
-// Nose-Hoover scalars before the drift (Appendix B): with K = sum v(t)^2,
-// G = (K - d N T) / Q: ln s += xi dt + G dt^2/2 (Eq. (Noseupdate_lns)),
-// xi_a = xi + G dt (Eq. (Noseupdate_xiapprox)), c = dt/2 (1 - dt/2 xi_a).
-__global__ void k_nh_begin(Dev d, double dt, const double *Q)
-{
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= d.nrep) return;
-    const RepInfo &R = d.rep[r];
-    RepDyn &D = d.dyn[r];
-    const double X = (double)d.dim * (double)R.n;  // degrees of freedom d N
-    const double G = (D.K2 - X * R.T) / Q[r];
-    D.lns += D.xi * dt + 0.5 * G * dt * dt;
-    D.xia = D.xi + G * dt;
-    D.c_kick = 0.5 * dt * (1.0 - 0.5 * dt * D.xia);
-}
-
-// After the closing kick: xi(t+dt) = xi + dt/2 (G + G'), G' from the new
-// velocities (Eq. (FoxAndersen_ydottplush) for y = ln s); K <- sum v(t+dt)^2.
-__global__ void k_nh_end(Dev d, double dt, const double *Q)
-{
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= d.nrep) return;
-    const RepInfo &R = d.rep[r];
-    RepDyn &D = d.dyn[r];
-    const double X = (double)d.dim * (double)R.n;  // degrees of freedom d N
-    const double K1 = d.rsum[4 * r + 0];
-    const double G = (D.K2 - X * R.T) / Q[r];
-    const double G1 = (K1 - X * R.T) / Q[r];
-    D.xi = D.xi + 0.5 * dt * (G + G1);
-    D.K2 = K1;
-}
-
-// K <- rsum[0] (after a sum-v^2 reduction).
-__global__ void k_set_k2(Dev d)
-{
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= d.nrep) return;
-    d.dyn[r].K2 = d.rsum[4 * r + 0];
+    if (nh && threadIdx.x == 0) {
+        RepDyn &D = d.dyn[r];
+        const double X = (double)d.dim * (double)R.n, K1 = red[0][0];
+        const double G1 = (K1 - X * R.T) / Q[r];
+        double xi = D.xi;
+        if (nh & NH_END) {
+            const double G = (D.K2 - X * R.T) / Q[r];
+            xi = xi + 0.5 * dt * (G + G1);
+            D.xi = xi;
+        }
+        D.K2 = K1;
+        if (nh & NH_BEGIN) {
+            const double xia = xi + G1 * dt;
+            D.lns += xi * dt + 0.5 * G1 * dt * dt;
+            D.xia = xia;
+            D.c_kick = 0.5 * dt * (1.0 - 0.5 * dt * xia);
+        }
+    }
 }
 
 __global__ __launch_bounds__(BLOCK) void k_ke_partial(Dev d)
@@ -429,34 +405,14 @@ hipError_t launch_drift_nh(const Dev &d, double dt, hipStream_t s)
     hipLaunchKernelGGL(k_drift, dim3(nblk(d)), dim3(BLOCK), 0, s, d, dt, 1);
     return hipGetLastError();
 }
-hipError_t launch_kick_nve(const Dev &d, double dt, bool want_ke, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_kick, dim3(nblk(d)), dim3(BLOCK), 0, s, d, 0.5 * dt, 0, want_ke ? 1 : 0);
-    return hipGetLastError();
-}
-hipError_t launch_kick_nh(const Dev &d, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_kick, dim3(nblk(d)), dim3(BLOCK), 0, s, d, 0.0, 1, 1);
-    return hipGetLastError();
-}
 hipError_t launch_rep_reduce(const Dev &d, int mask, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_rep_reduce, dim3(d.nrep), dim3(BLOCK), 0, s, d, mask);
+    hipLaunchKernelGGL(k_rep_reduce, dim3(d.nrep), dim3(BLOCK), 0, s, d, mask, 0, 0.0, nullptr);
     return hipGetLastError();
 }
-hipError_t launch_nh_begin(const Dev &d, double dt, const double *Q, hipStream_t s)
+hipError_t launch_rep_reduce_nh(const Dev &d, int mask, int nh, double dt, const double *Q, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_nh_begin, dim3((d.nrep + 63) / 64), dim3(64), 0, s, d, dt, Q);
-    return hipGetLastError();
-}
-hipError_t launch_nh_end(const Dev &d, double dt, const double *Q, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_nh_end, dim3((d.nrep + 63) / 64), dim3(64), 0, s, d, dt, Q);
-    return hipGetLastError();
-}
-hipError_t launch_set_k2(const Dev &d, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_set_k2, dim3((d.nrep + 63) / 64), dim3(64), 0, s, d);
+    hipLaunchKernelGGL(k_rep_reduce, dim3(d.nrep), dim3(BLOCK), 0, s, d, mask, nh, dt, Q);
     return hipGetLastError();
 }
 hipError_t launch_ke_partial(const Dev &d, hipStream_t s)

@@ -767,7 +767,7 @@ static int force_rebuild_all(kamd_ctx *c)
 static int forces(kamd_ctx *c, bool energy)
 {
     TRY(rebuild_chain(c, c->d));
-    HIPCHK(c, launch_force(c->d, c->model, c->cfg.precision, energy, false, c->stream));
+    HIPCHK(c, launch_force(c->d, c->model, c->cfg.precision, energy, 0, 0.0, c->stream));
     return KAMD_OK;
 }
 
@@ -808,17 +808,15 @@ static int enqueue_steps(kamd_ctx *c, int nsteps, int ensemble, int mode, int nb
     const int prec = c->cfg.precision;
     if (ensemble == 1 && mode == KAMD_NVT_NOSE_HOOVER) {
         HIPCHK(c, launch_ke_partial(d, c->stream));
-        HIPCHK(c, launch_rep_reduce(d, 1, c->stream));
-        HIPCHK(c, launch_set_k2(d, c->stream));
+        HIPCHK(c, launch_rep_reduce_nh(d, 1, NH_SET | (nsteps > 0 ? NH_BEGIN : 0), dt, c->Q_dev, c->stream));
         for (int s = 1; s <= nsteps; ++s) {
             const bool smp = sample_step(c, c->step + s);
-            HIPCHK(c, launch_nh_begin(d, dt, c->Q_dev, c->stream));
             HIPCHK(c, launch_drift_nh(d, dt, c->stream));
             TRY(rebuild_chain(c, c->d));
-            HIPCHK(c, launch_force(d, c->model, prec, smp, true, c->stream));
-            HIPCHK(c, launch_kick_nh(d, c->stream));
-            HIPCHK(c, launch_rep_reduce(d, smp ? 7 : 1, c->stream));
-            HIPCHK(c, launch_nh_end(d, dt, c->Q_dev, c->stream));
+            HIPCHK(c, launch_force(d, c->model, prec, smp, FORCE_STEP | FORCE_KICK | FORCE_KICK_NH | FORCE_KE, dt,
+                                   c->stream));
+            HIPCHK(c, launch_rep_reduce_nh(d, smp ? 7 : 1, NH_END | (s < nsteps ? NH_BEGIN : 0), dt, c->Q_dev,
+                                           c->stream));
             if (smp) HIPCHK(c, launch_sample(d, 7, c->stream));
         }
         return KAMD_OK;
@@ -842,7 +840,7 @@ static int enqueue_steps(kamd_ctx *c, int nsteps, int ensemble, int mode, int nb
     double4 *p4[2] = {c->d.pos4, c->pos4_alt};
     int cur = nf & 1, par = nf & 1;
     Dev dd = c->d;
-    bool need_drift = true, p4_ok = false;
+    bool need_drift = true;
     for (int s = 1; s <= nsteps; ++s) {
         dd.mirror = mir[cur];
         dd.maxdisp = c->md_base + par * c->d.nrep;
@@ -853,9 +851,6 @@ static int enqueue_steps(kamd_ctx *c, int nsteps, int ensemble, int mode, int nb
         const bool reassign = stoch && nb > 0 && (gstep % nb) == 0;
         const bool smp = sample_step(c, gstep);
         if (fused[s]) {
-            // the packed positions are current after a fused FP64 step (the
-            // list build reorders them with the rest); otherwise pack them
-            if (prec == KAMD_PREC_FP64 && !p4_ok) HIPCHK(c, launch_pack_pos(dd, c->stream));
             HIPCHK(c, launch_force_kd(dd, c->model, prec, dt, mir[1 - cur], c->md_base + (1 - par) * c->d.nrep,
                                       p4[1 - cur], smp, c->force_wpb, c->stream));
             if (smp) {
@@ -865,13 +860,10 @@ static int enqueue_steps(kamd_ctx *c, int nsteps, int ensemble, int mode, int nb
             cur = 1 - cur;
             par = 1 - par;
             need_drift = false;
-            p4_ok = true;
             continue;
         }
-        p4_ok = false;
-        HIPCHK(c, launch_force(dd, c->model, prec, smp, true, c->stream));
         // the last step, or one before a velocity redraw
-        HIPCHK(c, launch_kick_nve(dd, dt, smp, c->stream));
+        HIPCHK(c, launch_force(dd, c->model, prec, smp, FORCE_STEP | FORCE_KICK | (smp ? FORCE_KE : 0), dt, c->stream));
         if (reassign) {
             // a sample describes the end of the step: PE and W now, KE
             // after the redraw
@@ -1798,7 +1790,7 @@ extern "C" int md_profile(kamd_ctx *c, int32_t nsteps, double *host_out)
         fused[s] = 1;
         nf += fused[s];
     }
-    std::vector<hipEvent_t> ev(5 * (size_t)nsteps + 2);
+    std::vector<hipEvent_t> ev(4 * (size_t)nsteps + 2);
     for (auto &e : ev) HIPCHK(c, hipEventCreate(&e));
     int32_t cnt0[8], cnt1[8];
     HIPCHK(c, hipMemcpyAsync(cnt0, c->d.counters, 32, hipMemcpyDeviceToHost, c->stream));
@@ -1807,7 +1799,7 @@ extern "C" int md_profile(kamd_ctx *c, int32_t nsteps, double *host_out)
     double4 *p4[2] = {c->d.pos4, c->pos4_alt};
     int cur = nf & 1, par = nf & 1;
     Dev dd = c->d;
-    bool need_drift = true, p4_ok = false;
+    bool need_drift = true;
     size_t k = 0;
     HIPCHK(c, hipEventRecord(ev[k++], c->stream));
     for (int s = 1; s <= nsteps; ++s) {
@@ -1820,19 +1812,14 @@ extern "C" int md_profile(kamd_ctx *c, int32_t nsteps, double *host_out)
         TRY(rebuild_chain(c, dd));
         HIPCHK(c, hipEventRecord(ev[k++], c->stream));
         if (fused[s]) {
-            if (prec == KAMD_PREC_FP64 && !p4_ok) HIPCHK(c, launch_pack_pos(dd, c->stream));
             HIPCHK(c, launch_force_kd(dd, c->model, prec, dt, mir[1 - cur], c->md_base + (1 - par) * c->d.nrep,
                                       p4[1 - cur], false, c->force_wpb, c->stream));
             cur = 1 - cur;
             par = 1 - par;
             need_drift = false;
-            p4_ok = true;
         } else {
-            p4_ok = false;
-            HIPCHK(c, launch_force(dd, c->model, prec, false, true, c->stream));
+            HIPCHK(c, launch_force(dd, c->model, prec, false, FORCE_STEP | FORCE_KICK, dt, c->stream));
         }
-        HIPCHK(c, hipEventRecord(ev[k++], c->stream));
-        if (!fused[s]) HIPCHK(c, launch_kick_nve(dd, dt, false, c->stream));  // the last step
         HIPCHK(c, hipEventRecord(ev[k++], c->stream));
     }
     HIPCHK(c, hipEventRecord(ev[k++], c->stream));
@@ -1840,11 +1827,10 @@ extern "C" int md_profile(kamd_ctx *c, int32_t nsteps, double *host_out)
     double tf = 0.0, ts = 0.0, tr = 0.0;
     float ms = 0.0f;
     for (int s = 0; s < nsteps; ++s) {
-        const size_t q = 1 + 5 * (size_t)s;
+        const size_t q = 1 + 4 * (size_t)s;
         HIPCHK(c, hipEventElapsedTime(&ms, ev[q], ev[q + 1])); ts += ms;
         HIPCHK(c, hipEventElapsedTime(&ms, ev[q + 1], ev[q + 2])); tr += ms;
         HIPCHK(c, hipEventElapsedTime(&ms, ev[q + 2], ev[q + 3])); tf += ms;
-        HIPCHK(c, hipEventElapsedTime(&ms, ev[q + 3], ev[q + 4])); ts += ms;
     }
     HIPCHK(c, hipEventElapsedTime(&ms, ev[0], ev[k - 1]));
     const double total = ms;
