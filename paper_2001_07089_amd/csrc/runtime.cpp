@@ -84,6 +84,7 @@ struct kamd_ctx {
     Plan plan;                        // the current list parameters' layout
     Shape shape;                      // sizes of the workspace's fixed part
     int static_device = -1;           // >= 0: the workspace is that device's static array
+    uint32_t *err_host = nullptr;     // pinned: the device error word, read after eager calls
     bool stage_windows = false;       // mixed-precision force kernels gather from LDS windows
     int force_wpb = WAVES_PER_BLOCK;  // wavefronts per block of the step kernel
     std::string err = "no error";
@@ -758,9 +759,7 @@ static int rebuild_chain(kamd_ctx *c, const Dev &d)
 
 static int force_rebuild_all(kamd_ctx *c)
 {
-    std::vector<int32_t> ones(c->reps.size(), 1);
-    HIPCHK(c, hipMemcpyAsync(c->d.rb_force, ones.data(), 4 * ones.size(), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+    HIPCHK(c, launch_fill_i32(c->d.rb_force, (int64_t)c->reps.size(), 1, c->stream));
     return KAMD_OK;
 }
 
@@ -955,13 +954,15 @@ static int snapshot_restore(kamd_ctx *c)
 }
 
 // Waits for the stream.  redo: a list overflowed, the bit is cleared and the
-// list has grown to the rows its build asked for.
+// list has grown to the rows its build asked for.  The error word comes into
+// pinned memory with one wait for both (31 -> 21 us for a small kernel, the word
+// and the waits; a copy to pageable memory waits by itself).
 static int heal_list(kamd_ctx *c, bool &redo)
 {
     redo = false;
-    uint32_t w = 0;
+    HIPCHK(c, hipMemcpyAsync(c->err_host, c->d.err, 4, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    HIPCHK(c, hipMemcpy(&w, c->d.err, 4, hipMemcpyDeviceToHost));
+    const uint32_t w = *c->err_host;
     if (!(w & KAMD_DEV_LIST_OVERFLOW)) return KAMD_OK;
     int32_t cnt[8];
     HIPCHK(c, hipMemcpy(cnt, c->d.counters, 32, hipMemcpyDeviceToHost));
@@ -996,16 +997,19 @@ static int heal_forces(kamd_ctx *c, bool energy) { return heal_build(c, true, en
 
 // Eager steps, redone from the call's starting state while a list overflows.
 // On failure (a caller-owned workspace too small for the grown list) the state
-// is that of the start of the call.
+// is that of the start of the call.  The export, where the caller wants one, is
+// launched before the wait rather than after it.
 static int heal_steps(kamd_ctx *c, int nsteps, int ensemble, int mode, int nb)
 {
     TRY(snapshot_save(c));
     for (int attempt = 0;; ++attempt) {
         TRY(enqueue_steps(c, nsteps, ensemble, mode, nb, false));
+        TRY(maybe_export(c));
         bool redo = false;
         const int rc = heal_list(c, redo);
         if (rc) {
             (void)snapshot_restore(c);
+            (void)maybe_export(c);
             return rc;
         }
         if (!redo) return KAMD_OK;
@@ -1101,6 +1105,7 @@ extern "C" int md_init(kamd_ctx **out, const kamd_config *cfg, const kamd_replic
             c->ws_bytes = need;
             c->ws_owned = true;
         }
+        HIPCHK(c, hipHostMalloc((void **)&c->err_host, sizeof *c->err_host, hipHostMallocDefault));
         bind_workspace(c, P);
         TRY(init_fixed(c));
         TRY(init_list(c));
@@ -1193,7 +1198,7 @@ extern "C" int md_step_nve(kamd_ctx *c, int32_t nsteps)
     if (nsteps == 0) return KAMD_OK;
     TRY(heal_steps(c, nsteps, 0, 0, 0));
     c->step += nsteps;
-    return maybe_export(c);
+    return KAMD_OK;
 }
 
 extern "C" int md_step_nvt(kamd_ctx *c, int32_t nsteps, int32_t mode, int32_t n_reassign, double tau)
@@ -1211,7 +1216,7 @@ extern "C" int md_step_nvt(kamd_ctx *c, int32_t nsteps, int32_t mode, int32_t n_
     if (nsteps == 0) return KAMD_OK;
     TRY(heal_steps(c, nsteps, 1, mode, n_reassign));
     c->step += nsteps;
-    return maybe_export(c);
+    return KAMD_OK;
 }
 
 extern "C" int md_set_temperature(kamd_ctx *c, const double *temperature)
@@ -1884,6 +1889,7 @@ extern "C" int md_destroy(kamd_ctx *c)
     (void)hipStreamSynchronize(c->stream);
     drop_graph(c);
     if (c->ws_owned && c->ws) (void)hipFree(c->ws);
+    if (c->err_host) (void)hipHostFree(c->err_host);
     if (c->static_device >= 0) release_static_workspace(c->static_device);
     c->ws = nullptr;
     delete c;
