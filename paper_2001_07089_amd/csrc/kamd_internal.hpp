@@ -225,14 +225,19 @@ hipError_t launch_scale_v(const Dev &d, const double *f, hipStream_t s);
 hipError_t launch_ke_partial(const Dev &d, hipStream_t s);
 
 hipError_t launch_import(const Dev &d, const double *const *arr, const int32_t *img, hipStream_t s);
+// Export and restore use the sort's scratch arrays (sx ..., simg).
+constexpr int EXPORT_RECORD_BYTES = 96;  // per particle
 hipError_t launch_export(const Dev &d, double *const *arr, int32_t *img, hipStream_t s);
-constexpr int COPY_RANGES = 5;
-struct CopyRanges {
-    const uint4 *src[COPY_RANGES];
-    uint4 *dst[COPY_RANGES];
-    int64_t words[COPY_RANGES];  // of 16 bytes
+// A state kept by slot, without the padding.
+struct Snapshot {
+    double *state;         // [9][n_total]
+    int32_t *img, *id;     // [3][n_total]; the particles of the entries
+    RepDyn *dyn;
+    int32_t *counters;     // [8]
 };
-hipError_t launch_copy_ranges(const CopyRanges &r, hipStream_t s);
+hipError_t launch_snapshot(const Dev &d, const Snapshot &p, hipStream_t s);
+// Positions, velocities, forces and image counters back to their particles.
+hipError_t launch_restore(const Dev &d, const Snapshot &p, hipStream_t s);
 hipError_t launch_mirror(const Dev &d, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_zero_i32(int32_t *p, int64_t n, hipStream_t s);

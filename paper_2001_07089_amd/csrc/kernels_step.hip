@@ -27,9 +27,9 @@ struct SlotCtx {
     int rep;
 };
 
-__device__ inline bool slot_ctx(const Dev &d, SlotCtx &c)
+__device__ inline bool slot_ctx(const Dev &d, SlotCtx &c, int block)
 {
-    c.w = blockIdx.x * WAVES_PER_BLOCK + (threadIdx.x >> 6);
+    c.w = block * WAVES_PER_BLOCK + (threadIdx.x >> 6);
     c.s = 0;
     c.real = false;
     c.rep = -1;
@@ -40,6 +40,7 @@ __device__ inline bool slot_ctx(const Dev &d, SlotCtx &c)
     c.rep = S.rep;
     return true;
 }
+__device__ inline bool slot_ctx(const Dev &d, SlotCtx &c) { return slot_ctx(d, c, blockIdx.x); }
 
 // FP64: also the packed positions that the force kernel gathers (padding slots:
 // their own, which keeps their list entry at zero separation).
@@ -299,7 +300,42 @@ struct Arr9w {
     double *p[9];
 };
 
+// Blocks remapped: the particles of a replica are written from one XCD, whose L2
+// puts their scattered words together (64 replicas of 16,384: 138 -> 64 us).
 __global__ __launch_bounds__(BLOCK) void k_export(Dev d, Arr9w a, int32_t *img)
+{
+    SlotCtx c;
+    if (!slot_ctx(d, c, xcd_block(blockIdx.x, gridDim.x))) return;
+    if (!c.real) return;
+    const int s = c.s;
+    const int np = d.npad_total;
+    const int g = d.id[s];
+    const double v[9] = {d.x[s], d.y[s], d.z[s], d.vx[s], d.vy[s], d.vz[s], d.ax[s], d.ay[s], d.az[s]};
+    const int32_t im[3] = {d.img[s], d.img[np + s], d.img[2 * np + s]};
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+        if (a.p[k]) a.p[k][g] = v[k];
+    if (img) {
+        img[g] = im[0];
+        img[d.n_total + g] = im[1];
+        img[2 * d.n_total + g] = im[2];
+    }
+}
+
+// The same for large replicas in two passes: a particle's words scattered to the
+// caller's arrays one by one reach memory as partial sectors.  The first pass
+// puts them together in one record of 96 bytes (three whole sectors) per
+// particle, the second reads the records in order.  The records lie in the
+// sort's scratch arrays, which hold nothing between steps.  Bound by HBM: 2^20
+// particles 155 -> 69 us for 370 MB (records of 72 bytes and the image counters
+// apart, which share sectors: 123).
+struct ExportRecord {
+    double2 q[5];  // x y, z vx, vy vz, ax ay, az and the first two image counters
+    int4 i;        // the third image counter
+};
+static_assert(sizeof(ExportRecord) == EXPORT_RECORD_BYTES, "the scratch is sized for it");
+
+__global__ __launch_bounds__(BLOCK) void k_export_records(Dev d)
 {
     SlotCtx c;
     if (!slot_ctx(d, c)) return;
@@ -307,26 +343,69 @@ __global__ __launch_bounds__(BLOCK) void k_export(Dev d, Arr9w a, int32_t *img)
     const int s = c.s;
     const int np = d.npad_total;
     const int g = d.id[s];
-    const double *src[9] = {d.x, d.y, d.z, d.vx, d.vy, d.vz, d.ax, d.ay, d.az};
+    ExportRecord r;
+    r.q[0] = make_double2(d.x[s], d.y[s]);
+    r.q[1] = make_double2(d.z[s], d.vx[s]);
+    r.q[2] = make_double2(d.vy[s], d.vz[s]);
+    r.q[3] = make_double2(d.ax[s], d.ay[s]);
+    const uint32_t i0 = (uint32_t)d.img[s], i1 = (uint32_t)d.img[np + s];
+    r.q[4] = make_double2(d.az[s], __longlong_as_double((long long)(((uint64_t)i1 << 32) | i0)));
+    r.i = make_int4(d.img[2 * np + s], 0, 0, 0);
+    reinterpret_cast<ExportRecord *>(d.sx)[g] = r;
+}
+
+__global__ __launch_bounds__(BLOCK) void k_export_arrays(Dev d, Arr9w a, int32_t *img)
+{
+    const int g = blockIdx.x * BLOCK + threadIdx.x;
+    if (g >= d.n_total) return;
+    const ExportRecord r = reinterpret_cast<const ExportRecord *>(d.sx)[g];
+    const double v[9] = {r.q[0].x, r.q[0].y, r.q[1].x, r.q[1].y, r.q[2].x, r.q[2].y, r.q[3].x, r.q[3].y, r.q[4].x};
+#pragma unroll
     for (int k = 0; k < 9; ++k)
-        if (a.p[k]) a.p[k][g] = src[k][s];
+        if (a.p[k]) st_stream(v[k], &a.p[k][g]);
     if (img) {
-        img[g] = d.img[s];
-        img[d.n_total + g] = d.img[np + s];
-        img[2 * d.n_total + g] = d.img[2 * np + s];
+        const uint64_t w = (uint64_t)__double_as_longlong(r.q[4].y);
+        img[g] = (int32_t)(uint32_t)w;
+        img[d.n_total + g] = (int32_t)(uint32_t)(w >> 32);
+        img[2 * d.n_total + g] = r.i.x;
     }
 }
 
-// Up to five ranges copied in 16-byte words with one launch: what an eager call
-// keeps of the state it starts from, in slot order, so that every access is
-// contiguous (bound by HBM: 190 MB at 2^20 particles).  It was an export, which
-// scatters to the caller's order, and two device copies.  Measured (us per eager
-// call of one step): 2^20 MIXED 947 -> 738, 100,000 151 -> 135, 1000 FP64 82 -> 64.
-__global__ __launch_bounds__(BLOCK) void k_copy_ranges(CopyRanges r)
+// What an eager call keeps of the state it starts from, in slot order without
+// the padding, so that every access is contiguous (bound by HBM: 190 MB at 2^20
+// particles).  It was an export, which scatters to the caller's order, and two
+// device copies.  Measured (us per eager call of one step): 2^20 MIXED 947 ->
+// 738, 100,000 151 -> 135, 1000 FP64 82 -> 64.
+__global__ __launch_bounds__(BLOCK) void k_snapshot(Dev d, Snapshot p)
 {
-    const int64_t stride = (int64_t)gridDim.x * BLOCK, i0 = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-    for (int k = 0; k < COPY_RANGES; ++k)
-        for (int64_t i = i0; i < r.words[k]; i += stride) st_stream(r.src[k][i], r.dst[k] + i);
+    for (int r = blockIdx.x * BLOCK + threadIdx.x; r < d.nrep; r += gridDim.x * BLOCK) p.dyn[r] = d.dyn[r];
+    if (blockIdx.x == 0 && threadIdx.x < 8) p.counters[threadIdx.x] = d.counters[threadIdx.x];
+    SlotCtx c;
+    if (!slot_ctx(d, c) || !c.real) return;
+    const SegInfo &S = d.seg[d.wave_seg[c.w]];
+    const RepInfo &R = d.rep[c.rep];
+    const int s = c.s, np = d.npad_total;
+    const size_t nt = d.n_total;
+    const size_t i = (size_t)R.caller_off + (S.type ? d.seg[R.seg[0]].n : 0) + (s - S.slot0);
+    const double v[9] = {d.x[s], d.y[s], d.z[s], d.vx[s], d.vy[s], d.vz[s], d.ax[s], d.ay[s], d.az[s]};
+    const int32_t im[3] = {d.img[s], d.img[np + s], d.img[2 * np + s]};
+    const int32_t g = d.id[s];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) st_stream(v[k], &p.state[k * nt + i]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) st_stream(im[k], &p.img[k * nt + i]);
+    st_stream(g, &p.id[i]);
+}
+
+// The saved state in caller order, into the sort's scratch arrays.
+__global__ __launch_bounds__(BLOCK) void k_unpack_snapshot(Dev d, Snapshot p)
+{
+    const int i = blockIdx.x * BLOCK + threadIdx.x;
+    if (i >= d.n_total) return;
+    const size_t nt = d.n_total;
+    const int g = p.id[i];
+    for (int k = 0; k < 9; ++k) d.sx[k * nt + g] = p.state[k * nt + i];
+    for (int k = 0; k < 3; ++k) d.simg[k * nt + g] = p.img[k * nt + i];
 }
 
 __global__ __launch_bounds__(BLOCK) void k_mirror(Dev d)
@@ -452,20 +531,33 @@ hipError_t launch_import(const Dev &d, const double *const *arr, const int32_t *
     hipLaunchKernelGGL(k_import, dim3(nblk(d)), dim3(BLOCK), 0, s, d, a, img);
     return hipGetLastError();
 }
+// Where the two passes win (us per export, one pass / two): one replica of 64,000
+// particles 8.9 / 10.2, 100,000 14.2 / 13.2, 262,144 40 / 21, 2^20 155 / 69; 64
+// replicas of 16,384 64 / 68, eight of 131,072 136 / 67.
+constexpr int EXPORT_RECORD_WAVES = 1500;
 hipError_t launch_export(const Dev &d, double *const *arr, int32_t *img, hipStream_t s)
 {
     Arr9w a;
     for (int k = 0; k < 9; ++k) a.p[k] = arr[k];
-    hipLaunchKernelGGL(k_export, dim3(nblk(d)), dim3(BLOCK), 0, s, d, a, img);
+    if (d.rep_waves_max >= EXPORT_RECORD_WAVES) {
+        hipLaunchKernelGGL(k_export_records, dim3(nblk(d)), dim3(BLOCK), 0, s, d);
+        hipLaunchKernelGGL(k_export_arrays, dim3((d.n_total + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, d, a, img);
+    } else {
+        hipLaunchKernelGGL(k_export, dim3(nblk(d)), dim3(BLOCK), 0, s, d, a, img);
+    }
     return hipGetLastError();
 }
-hipError_t launch_copy_ranges(const CopyRanges &r, hipStream_t s)
+hipError_t launch_snapshot(const Dev &d, const Snapshot &p, hipStream_t s)
 {
-    int64_t most = 1;
-    for (int k = 0; k < COPY_RANGES; ++k) most = std::max(most, r.words[k]);
-    const int nb = (int)std::min<int64_t>((most + BLOCK - 1) / BLOCK, 4096);
-    hipLaunchKernelGGL(k_copy_ranges, dim3(nb), dim3(BLOCK), 0, s, r);
+    hipLaunchKernelGGL(k_snapshot, dim3(nblk(d)), dim3(BLOCK), 0, s, d, p);
     return hipGetLastError();
+}
+hipError_t launch_restore(const Dev &d, const Snapshot &p, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_unpack_snapshot, dim3((d.n_total + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, d, p);
+    const double *a[9];
+    for (int k = 0; k < 9; ++k) a[k] = d.sx + (size_t)k * d.n_total;
+    return launch_import(d, a, d.simg, s);
 }
 hipError_t launch_mirror(const Dev &d, hipStream_t s)
 {

@@ -69,9 +69,9 @@ struct kamd_ctx {
     double *Q_dev = nullptr;
     double *rep_arg = nullptr;        // per-replica host arguments staged for a kernel
     double *obs_stage = nullptr;      // device [n_rep][4]
-    double *state_tmp = nullptr;      // device staging: checkpoints (caller order), list-heal snapshots (slot order)
+    double *state_tmp = nullptr;      // device staging: checkpoints, list-heal snapshots
     int32_t *img_tmp = nullptr;
-    int32_t *id_snap = nullptr;       // particles of the slots of a list-heal snapshot
+    int32_t *id_snap = nullptr;       // particles of the entries of a list-heal snapshot
     RepDyn *dyn_snap = nullptr;       // thermostat scalars of a list-heal snapshot
     int32_t *cnt_snap = nullptr;      // device counters of a list-heal snapshot
     int64_t step = 0;
@@ -395,7 +395,9 @@ static void carve_fixed(Dev &d, CtxBufs &b, const Shape &z, Carve &k)
     const size_t np = z.np, nt = z.nt;
     double **f64[] = {&d.x, &d.y, &d.z, &d.vx, &d.vy, &d.vz, &d.ax, &d.ay, &d.az,
                       &d.sx, &d.sy, &d.sz, &d.svx, &d.svy, &d.svz, &d.sax, &d.say, &d.saz};
-    double *state = k.take<double>(9 * np), *scratch = k.take<double>(9 * np);
+    // the scratch: the sort's state copies, between steps the records of an
+    // export or the cell order of an RDF
+    double *state = k.take<double>(9 * np), *scratch = k.take<double>(std::max(9 * np, EXPORT_RECORD_BYTES / 8 * nt));
     for (int q = 0; q < 18; ++q) *f64[q] = k.base ? (q < 9 ? state + q * np : scratch + (q - 9) * np) : nullptr;
     d.img = k.take<int32_t>(3 * np);
     d.simg = k.take<int32_t>(3 * np);
@@ -435,16 +437,17 @@ static void carve_fixed(Dev &d, CtxBufs &b, const Shape &z, Carve &k)
     b.obs_stage = k.take<double>(4 * z.nrep);
     d.ring = z.ring ? k.take<double>(6 * z.ring) : nullptr;
     d.origin = k.take<double>(z.msd_slots * 3 * nt);
-    d.rdf_cell_of = k.take<int32_t>(np);
-    d.rdf_rank = k.take<int32_t>(np);
-    d.rdf_pos = k.take<double4>(nt);
+    d.rdf_pos = reinterpret_cast<double4 *>(scratch);
+    d.rdf_cell_of = d.simg;
+    d.rdf_rank = k.base ? d.simg + np : nullptr;
+    // 40 n_total + 256 n_rep bytes of the scratch's 72 np: every replica has 64 slots or more
+    d.rdf_start = reinterpret_cast<int32_t *>(k.base ? scratch + 4 * nt : nullptr);
     d.rdf_count = k.take<int32_t>(z.rdf_cells);
-    d.rdf_start = k.take<int32_t>(z.rdf_cells);
     d.rdf_grid = k.take<int4>(z.nrep);
     d.rdf_plan = k.take<int4>(z.nrep);
-    b.state_tmp = k.take<double>(9 * np);
-    b.img_tmp = k.take<int32_t>(3 * np);
-    b.id_snap = k.take<int32_t>(np);
+    b.state_tmp = k.take<double>(9 * nt);
+    b.img_tmp = k.take<int32_t>(3 * nt);
+    b.id_snap = k.take<int32_t>(nt);
     b.dyn_snap = k.take<RepDyn>(z.nrep);
     b.cnt_snap = k.take<int32_t>(8);
 }
@@ -908,46 +911,19 @@ static int apply_list_params(kamd_ctx *c, double skin, int cell_div, bool first)
 // from.  Graph replays cannot heal: the bit stays for md_status, and
 // md_build_cells then grows the list (the caller recaptures).
 
-// The dynamical state at the start of an eager step call, as the slots hold it.
+// The dynamical state at the start of an eager step call.
+static Snapshot snapshot_of(kamd_ctx *c) { return {c->state_tmp, c->img_tmp, c->id_snap, c->dyn_snap, c->cnt_snap}; }
+
 static int snapshot_save(kamd_ctx *c)
 {
-    const Dev &d = c->d;
-    const size_t np = d.npad_total;  // a multiple of 64
-    CopyRanges r;
-    auto range = [&r](int k, const void *src, void *dst, size_t bytes) {
-        r.src[k] = static_cast<const uint4 *>(src);
-        r.dst[k] = static_cast<uint4 *>(dst);
-        r.words[k] = (int64_t)(bytes / 16);
-    };
-    static_assert(sizeof(RepDyn) % 16 == 0, "copied in 16-byte words");
-    range(0, d.x, c->state_tmp, 9 * 8 * np);  // x .. az are one array
-    range(1, d.img, c->img_tmp, 3 * 4 * np);
-    range(2, d.id, c->id_snap, 4 * np);
-    range(3, d.dyn, c->dyn_snap, sizeof(RepDyn) * c->reps.size());
-    range(4, d.counters, c->cnt_snap, 32);
-    HIPCHK(c, launch_copy_ranges(r, c->stream));
+    HIPCHK(c, launch_snapshot(c->d, snapshot_of(c), c->stream));
     return KAMD_OK;
 }
 
-// The particles keep the slots that they have now: the saved state goes by
-// particle through the sort's scratch arrays, which hold nothing between steps.
 static int snapshot_restore(kamd_ctx *c)
 {
     const Dev &d = c->d;
-    const size_t np = d.npad_total, nt = d.n_total;
-    Dev snap = d;
-    double **f[9] = {&snap.x, &snap.y, &snap.z, &snap.vx, &snap.vy, &snap.vz, &snap.ax, &snap.ay, &snap.az};
-    double *to[9];
-    const double *from[9];
-    for (int k = 0; k < 9; ++k) {
-        *f[k] = c->state_tmp + k * np;
-        to[k] = d.sx + k * nt;  // sx .. saz are one array of 9 np
-        from[k] = to[k];
-    }
-    snap.img = c->img_tmp;
-    snap.id = c->id_snap;
-    HIPCHK(c, launch_export(snap, to, d.simg, c->stream));
-    HIPCHK(c, launch_import(d, from, d.simg, c->stream));
+    HIPCHK(c, launch_restore(d, snapshot_of(c), c->stream));
     HIPCHK(c, hipMemcpyAsync(d.dyn, c->dyn_snap, sizeof(RepDyn) * c->reps.size(), hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(d.counters, c->cnt_snap, 32, hipMemcpyDeviceToDevice, c->stream));
     return force_rebuild_all(c);

@@ -140,3 +140,35 @@ def test_van_hove_across_replicas_and_block_runs():
             assert np.array_equal(h[r, t], np.bincount(part[part < nb], minlength=nb)), (r, t)
         o += n
     s.close()
+
+
+@pytest.mark.parametrize("n,count,prec", [(1000, 3, "fp64"), (96000, 1, "mixed"), (97000, 1, "mixed"),
+                                          (97000, 2, "mixed_fixed")])
+def test_export_in_one_and_two_passes(n, count, prec):
+    """Replicas of 1500 wavefronts are where the export goes through records
+    instead of straight to the caller's arrays.  What comes out is what went
+    in, by particle, image counters included, also after an RDF and a rebuild
+    have used the scratch arrays that hold the records."""
+    print(f"case export {count} x {n} {prec}", flush=True)
+    L = W.box_for(n, 1.2)
+    rng = np.random.default_rng(4)
+    pos = W.lattice_config(n, L, 17, 0.08)
+    turns = rng.integers(-3, 4, size=(3, n * count))
+    p0 = [np.tile(p, count) for p in pos]
+    v0 = [np.tile(u, count) * rng.choice([0.5, 1.0], n * count) for u in W.gaussian_velocities(n, 1.0, 5)]
+    s = md.System([(n, W.n_a_for(n), L, 1.0, 3)] * count, precision=prec, positions=p0, velocities=v0)
+    with s.torch.cuda.stream(s.stream):
+        s.img.copy_(s.torch.from_numpy(turns.astype(np.int32).reshape(s.img.shape)))
+    md.md_import(s.ctx)
+    s.rdf(0.1, 20)
+    s.build_cells()
+    with s.torch.cuda.stream(s.stream):
+        for k in ("x", "y", "z", "vx", "vy", "vz"):
+            s.t[k].zero_()
+        s.img.zero_()
+    s.sync()
+    out = s.numpy(("x", "y", "z", "vx", "vy", "vz"))
+    for k, u in zip(("x", "y", "z", "vx", "vy", "vz"), p0 + v0):
+        assert np.array_equal(out[k], u), k
+    assert np.array_equal(np.asarray(s.images()).reshape(3, -1), turns)
+    s.close()
