@@ -648,6 +648,7 @@ constexpr int LIST_STAGE = 16;
 // by under 0.6%.
 constexpr double COARSE_MAX_BOX = 220.0;
 constexpr int LIST_WIN = 384;
+constexpr int LIST_QUEUE = 10;  // k_rb_list_masks: entries of 64 candidates per lane
 
 // The sorted state of slot s back into place, with the mirror (mi) and the
 // build position.
@@ -1153,27 +1154,34 @@ __device__ inline int ring_cell(int x, int o, int nc)
 }
 
 // The list builder of k_rb_list for one cell per list radius, boxes of the
-// coarse test and no windows: the same rows, unions, staging and entries, but a
-// row piece's candidates are tested 32 at a time into a bit mask per lane, and
-// only the accepted ones, about a sixth, are then taken out of the mask into the
-// lane's stage.  A test costs five vector operations (two subtractions, two dot
-// products, one shift that appends the sign) where k_rb_list's, with an
-// unconditional stage write per candidate, costs ten; an accepted candidate
-// costs eight more.  Cells of a row are found without divisions, the wrapped
-// piece is looked at only where a lane has one, entries are stored in the
-// stage as the list holds them, and the state is copied back last, so that no
-// wait for loaded data waits for its stores.  Candidates come from an 8-byte
-// copy of the sorted mirror that the sort writes (scoarse); a union too long
-// for the window (most of the B wavefronts', which span several grid rows) is
-// read from it directly at the same cost per test.
+// coarse test and no windows: the same rows and entries, but a row's candidates
+// are tested 32 at a time into a bit mask per lane (five vector operations each:
+// two subtractions, two dot products, one shift that appends the sign; k_rb_list
+// spends ten, with a stage write per candidate).  Only the accepted ones, about a
+// sixth, are then taken out of the masks, and not as they come: the masks of 64
+// candidates go into a queue in LDS per lane, and at the end of the part (or when
+// the queue is full) every lane takes its next entries from its own queue, all
+// lanes in step.  A 16-byte piece of every list is thus complete in registers
+// at the same time, and the steps are those of the longest list, 110, where
+// emptying each mask before the next tests took 350 at a quarter of the lanes.
 //
-// Bound by the vector ALU: 12,300 instructions per wavefront, 14,800 before, and
-// 87 registers instead of 123 (five wavefronts per SIMD).  Measured: 2^20 MIXED
-// 310 -> 298 us per step, 400,000 140 -> 133, the 256-replica batch 400 -> 372.
-__global__ __launch_bounds__(BLOCK) void k_rb_list_masks(Dev d, int min_waves)
+// Candidates are read from an 8-byte copy of the sorted mirror that the sort
+// writes (scoarse), two per load.  Staging the rows' unions in LDS first costs
+// more (the unions, the copies, and the LDS that limits the occupancy) than it
+// takes off the vector cache: 511 us per build against 469.  Cells of a row are
+// found without divisions, and the wrapped piece is looked at only where a lane
+// has one.  Queues of 8 / 10 / 12 entries: 490 / 482 / 487 us.  Five wavefronts
+// per SIMD (96 registers; the particle's own position is read again at the end
+// for that): 482 -> 469.
+//
+// Bound by the vector ALU (9,200 instructions per wavefront; 14,800 in k_rb_list)
+// and the candidate loads (430 per wavefront).  Measured, a build (sort and
+// lists, k_rb_list / masks emptied at once / this): 2^20 particles - / 537 / 469
+// us, 100,000 - / 143 / 121, 256 replicas of 4096 - / 600 / 503; the 2^20 MIXED
+// step 310 / 287 / 276.
+__global__ __launch_bounds__(BLOCK, 5) void k_rb_list_masks(Dev d, int min_waves)
 {
-    __shared__ int32_t stage[WAVES_PER_BLOCK][LIST_STAGE][WAVE];
-    __shared__ uint2 win_s[WAVES_PER_BLOCK][LIST_WIN + 32];  // a mask reads up to 31 past a range
+    __shared__ uint32_t queue[WAVES_PER_BLOCK][LIST_QUEUE][3][WAVE];  // two masks, the entry of the first bit
     if (d.rb_any[0] < min_waves) return;  // nothing to do, or k_rb_list_wide's
     const int w = rb_work_wave(d);        // each XCD walks a contiguous part of the worklist
     if (w < 0) return;
@@ -1202,8 +1210,7 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list_masks(Dev d, int min_waves)
     const bool wraps = lw || rw;
     const bool any_wrap = __any(real && wraps);
     int32_t *col = d.nbr + list_index(w, d.rows, 0, lane);
-    int32_t(*buf)[WAVE] = stage[threadIdx.x / WAVE];
-    uint2 *wc = win_s[threadIdx.x / WAVE];
+    uint32_t(*q)[3][WAVE] = queue[threadIdx.x / WAVE];
     const int rows = d.rows;
     const int32_t *cstart = d.cell_start, *cend = d.cell_start + 1;
     int row = 0;  // 32-bit words of the list used so far
@@ -1234,26 +1241,54 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list_masks(Dev d, int min_waves)
         const bool half = base >= 0;
         const int group = half ? 8 : 4;    // entries per 16-byte store
         const int sub = half ? base : 0;   // entries are held as the list stores them
-        int cnt = 0;   // entries accepted
-        int done = 0;  // entries written to the list (a multiple of group)
-        auto store = [&](const int e[8]) __attribute__((always_inline)) {  // the next group
-            const int k = row + (half ? done / 2 : done);  // 32-bit word of the list
-            const int4 q = half ? make_int4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16))
-                                : make_int4(e[0], e[1], e[2], e[3]);
-            if (k < rows) *reinterpret_cast<int4 *>(col + (k >> 2) * 256) = q;
-            done += group;
-        };
-        auto flush = [&]() __attribute__((always_inline)) {  // every complete group of staged entries
-            while (done + group <= cnt) {
-                int e[8];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) e[t] = buf[(done + t) & (LIST_STAGE - 1)][lane];
-                if (half) {
-#pragma unroll
-                    for (int t = 4; t < 8; ++t) e[t] = buf[(done + t) & (LIST_STAGE - 1)][lane];
+        const int padv = s - sub;          // padding: the own slot
+        int cnt = 0;                       // entries accepted
+        int taken = 0;                     // of those, taken out of the queue
+        int emitted = 0;                   // entries of the list written (every lane's: a multiple of group)
+        int qh = 0, qn = 0;                // queue: first entry, entries
+        uint32_t ma = 0, mb = 0;           // the queue entry being taken apart
+        int ent = 0;
+        auto take = [&]() __attribute__((always_inline)) {
+            if (ma == 0) {
+                if (mb) {
+                    ma = mb;
+                    ent += 32;
+                    mb = 0;
+                } else if (qn) {
+                    ma = q[qh][0][lane];
+                    mb = q[qh][1][lane];
+                    ent = (int)q[qh][2][lane];
+                    qh = qh == LIST_QUEUE - 1 ? 0 : qh + 1;
+                    --qn;
                 }
-                store(e);
             }
+            const int e = ma ? ent + __builtin_ctz(ma) : padv;
+            ma &= ma - 1;
+            return e;
+        };
+        auto write = [&](int4 v) __attribute__((always_inline)) {
+            const int k = row + (half ? emitted / 2 : emitted);  // 32-bit word of the list
+            if (k < rows) *reinterpret_cast<int4 *>(col + (k >> 2) * 256) = v;
+            emitted += group;
+        };
+        auto emit = [&](int n) __attribute__((always_inline)) {  // n more entries of every lane's list
+#pragma unroll 1
+            for (int k = 0; k < n; k += group) {
+                int e[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    e[t] = take();
+                    if (half) e[t] |= take() << 16;
+                }
+                write(make_int4(e[0], e[1], e[2], e[3]));
+            }
+        };
+        // The queue of some lane is full: as many entries as every lane has, or
+        // where one has none, all that there are (that lane's list is padded).
+        auto make_room = [&]() __attribute__((always_inline)) {
+            const int have = -wave_max_all(real ? taken - cnt : -INT_MAX) & -group;
+            emit(have > 0 ? have : wave_max_all(cnt - taken));
+            taken = have > 0 ? taken + have : cnt;
         };
         // slot ranges of one stencil row: main run and wrapped end cell
         auto bounds = [&](int oz, int oy) __attribute__((always_inline)) {
@@ -1269,78 +1304,42 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list_masks(Dev d, int min_waves)
             }
             return b;
         };
-        // lowest start and highest end of the lanes' non-empty ranges
-        // (x = INT_MAX when no lane has one); all lanes take part
-        auto span = [&](int st, int en) __attribute__((always_inline)) {
-            const bool has = st < en;
-            return make_int2(-wave_max_all(has ? -st : INT_MIN + 1), wave_max_all(has ? en : -1));
+        // two candidates with one load (their address is a multiple of 8 only)
+        typedef uint32_t pair8 __attribute__((ext_vector_type(4), aligned(8)));
+        // 32 candidates from slot j, candidate i's bit in bit i; left: how many are the lane's
+        auto test32 = [&](int j, int left) __attribute__((always_inline)) {
+            const int ng = 1 + (__any(left > 8) ? 1 : 0) + (__any(left > 16) ? 1 : 0) + (__any(left > 24) ? 1 : 0);
+            const uint2 *v = d.scoarse + (left > 0 ? j : s);  // with spare entries past its end
+            uint32_t m = 0;
+#pragma unroll 1
+            for (int g = 0; g < ng; ++g, v += 8) {
+                pair8 c[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c[i] = *reinterpret_cast<const pair8 *>(v + 2 * i);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    m = push_sign(m, r2_coarse_below(ixy, iz, c[i].x, c[i].y, r2c));
+                    m = push_sign(m, r2_coarse_below(ixy, iz, c[i].z, c[i].w, r2c));
+                }
+            }
+            m = __brev(m << (32 - 8 * ng));
+            return left >= 32 ? m : left > 0 ? m & ~(0xffffffffu << left) : 0u;
         };
-        auto piece = [&](int st, int en, int2 sp) __attribute__((always_inline)) {
-            const int lo = sp.x, n = sp.y - sp.x;
-            if (lo == INT_MAX) return;
-            const bool staged = n <= LIST_WIN;
-            if (staged) {
-                // up to three loads per lane in flight at once
-                for (int q0 = 0; q0 < n; q0 += 3 * WAVE) {
-                    uint2 m[3];
-#pragma unroll
-                    for (int t = 0; t < 3; ++t)
-                        if (t == 0 || q0 + t * WAVE < n) m[t] = d.scoarse[lo + min(q0 + t * WAVE + lane, n - 1)];
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) {
-                        const int q = q0 + t * WAVE + lane;
-                        if (q < n) wc[q] = m[t];
-                    }
-                    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): none of this pass is left in flight
-                }
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-            }
+        auto piece = [&](int st, int en) __attribute__((always_inline)) {
 #pragma unroll 1
-            for (int j = st; __any(j < en); j += 32) {
-                const int left = min(en - j, 32);        // candidates of the lane's mask
-                const int jj = left > 0 ? j : lo;
-                const int ng = 1 + (__any(left > 8) ? 1 : 0) + (__any(left > 16) ? 1 : 0) + (__any(left > 24) ? 1 : 0);
-                uint32_t m = 0;
-                if (staged) {
-                    const uint2 *v = wc + (jj - lo);
-#pragma unroll 1
-                    for (int g = 0; g < ng; ++g, v += 8)
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) m = push_sign(m, r2_coarse_below(ixy, iz, v[i].x, v[i].y, r2c));
-                } else {
-                    const uint2 *v = d.scoarse + jj;  // with spare entries past its end
-#pragma unroll 1
-                    for (int g = 0; g < ng; ++g, v += 8) {
-                        uint2 q[8];
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) q[i] = v[i];
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) m = push_sign(m, r2_coarse_below(ixy, iz, q[i].x, q[i].y, r2c));
-                    }
+            for (int j = st; __any(j < en); j += 64) {
+                uint32_t a = test32(j, en - j), b = 0;
+                if (__any(j + 32 < en)) b = test32(j + 32, en - j - 32);
+                while (__any(qn == LIST_QUEUE)) make_room();
+                if (a | b) {
+                    int at = qh + qn;
+                    at -= at >= LIST_QUEUE ? LIST_QUEUE : 0;
+                    q[at][0][lane] = a ? a : b;
+                    q[at][1][lane] = a ? b : 0u;
+                    q[at][2][lane] = (uint32_t)(j - sub + (a ? 0 : 32));
+                    ++qn;
+                    cnt += __popc(a) + __popc(b);
                 }
-                m <<= 32 - 8 * ng;  // candidate i in bit 31 - i
-                m = left > 0 ? m & (0xffffffffu << (32 - left)) : 0u;
-                const int ent = jj - sub;
-                // At most LIST_STAGE - 8 entries are pending before a burst of
-                // eight.  The particle's own slot passes the test (zero
-                // separation) and stays in its list, where the force kernels
-                // skip it like the padding.
-                while (__any(m != 0)) {
-#pragma unroll
-                    for (int b = 0; b < 8; ++b)
-                        if (m) {
-                            const int i = __clz((int)m);
-                            m &= ~(0x80000000u >> i);
-                            buf[cnt & (LIST_STAGE - 1)][lane] = ent + i;
-                            ++cnt;
-                        }
-                    if (__any(cnt - done > LIST_STAGE - 8)) flush();
-                }
-            }
-            if (staged) {
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                __builtin_amdgcn_wave_barrier();
             }
         };
         if (SJ.n > 0) {
@@ -1351,35 +1350,23 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list_masks(Dev d, int min_waves)
 #pragma unroll 1
             for (int r = 0; r < nrow; ++r) {
                 const int4 cur = next;
-                const int2 sp1 = span(cur.x, cur.y);
-                const int2 sp2 = any_wrap ? span(cur.z, cur.w) : make_int2(INT_MAX, 0);
-                __builtin_amdgcn_sched_barrier(0);  // these bounds are used before the next row's loads are issued
                 // the next row; after the last one, row 0 again (read, not used)
                 if (++oy == -1 + noff) {
                     oy = -1;
                     if (++oz == oz0 + nz) oz = oz0;
                 }
                 next = bounds(oz, oy);
-                piece(cur.x, cur.y, sp1);
-                if (sp2.x != INT_MAX) piece(cur.z, cur.w, sp2);
+                piece(cur.x, cur.y);
+                if (any_wrap) piece(cur.z, cur.w);
             }
         }
-        flush();
+        emit(wave_max_all(cnt - taken));
         total += cnt;
-        int kmax = wave_max_all(cnt);
         const int align = half ? 2 * LIST_ROW_ALIGN : LIST_ROW_ALIGN;  // whole 16-byte words
-        kmax = (kmax + align - 1) & -align;
-        const int padv = s - sub;  // padding: the own slot
-        if (done < cnt) {          // the last partial group
-            int e[8];
-#pragma unroll
-            for (int t = 0; t < 8; ++t) e[t] = done + t < cnt ? buf[(done + t) & (LIST_STAGE - 1)][lane] : padv;
-            store(e);
-        }
+        const int kmax = (emitted + align - 1) & -align;
         const int words = half ? kmax / 2 : kmax;  // 32-bit words the part occupies
         const int pad = half ? padv | (padv << 16) : padv;
-        for (int k = row + (half ? done / 2 : done); k < row + words && k < rows; k += 4)
-            *reinterpret_cast<int4 *>(col + (k >> 2) * 256) = make_int4(pad, pad, pad, pad);
+        while (emitted < kmax) write(make_int4(pad, pad, pad, pad));
         if (row + words > rows && lane == 0) set_err(d.err, KAMD_DEV_LIST_OVERFLOW);
         kpart.x = tj == 0 ? kmax : kpart.x;
         kpart.y = tj == 1 ? kmax : kpart.y;
@@ -1404,6 +1391,8 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list_masks(Dev d, int min_waves)
     // partners (without the own slot) in the low 16 bits, those of them
     // stored as 16-bit entries in the high 16 bits
     d.nlen[s] = real ? (total - 1) | (n16 << 16) : 0;
+    mi = d.smirror[s];  // again: its registers are worth more in between
+    if (!real) mi = make_uint4(0, 0, 0, 0);
     copy_back(d, s, real, mi);
 }
 
@@ -1787,9 +1776,12 @@ hipError_t launch_rb_sortgather(const Dev &d, hipStream_t s)
 // Measured (us per MIXED NVE step, k_rb_list, then wide): N = 1000 35.1, 23.7;
 // 32,000 (501 waves) 39.4, 30.9; 50,000 (782) 42.4, 39.0; 62,000 (970) 45.4,
 // 42.4; 64 replicas of 1000 under the bath (worklists of up to 1088) 101, 68.
-// Larger worklists keep k_rb_list's one wavefront per list: the 256-replica
-// batch, whose worklists reach 4500 waves, 416 with either limit up to 1600,
-// 496 with the wide kernel alone.
+// Larger worklists keep one wavefront per list (the 256-replica batch, whose
+// worklists reach 4500 waves, 416 with either limit up to 1600, 496 with the wide
+// kernel alone), where it can be k_rb_list_masks.  With that one the line lies
+// lower for a single system, but hardly matters there (us per step, masks, then
+// wide: 40,000 32.7, 31.2; 50,000 34.7, 34.8; 62,000 35.7, 36.5; the bath 61.0,
+// 59.2).
 constexpr int WIDE_WAVES = 1100, WIDE_BATCH_WAVES = 8192;
 hipError_t launch_rb_list(const Dev &d, int cell_div, hipStream_t s)
 {
