@@ -11,8 +11,9 @@
 // the number of (ordered) pairs inside the cutoff.
 //
 // One thread per particle (or one of P threads that share its list, see
-// force_split); a wavefront holds 64 particles of one replica and one type, so the parameters of each list part (A partners, then B partners,
-// the paper's type-split loops) are wavefront-uniform and live in scalar
+// force_split); a wavefront holds 64 particles of one replica and one type, so
+// the parameters of each list part (A partners, then B partners, the paper's
+// type-split loops) are wavefront-uniform and live in scalar
 // registers.  Work is plain vector ALU arithmetic: a pair force is not a dense
 // contraction, so there is nothing for the matrix cores here.
 //

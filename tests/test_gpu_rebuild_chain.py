@@ -278,3 +278,42 @@ def test_chain_of_a_single_replica_equals_the_gated_one(n, L, dim):
         s.close()
     for k in out[0]:
         assert np.array_equal(out[0][k], out[1][k]), k
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed", "mixed_fixed"])
+def test_mask_list_queues_of_uneven_lanes(prec):
+    """A dense block in a dilute gas, long list radius: lanes whose queue of
+    masks is full beside lanes that have nothing to write yet, whose lists get
+    padding in their middle.  Padding adds zeros wherever it stands, so the
+    mixed sums equal the window builder's bit for bit; FP64, which has no
+    windows, against the lists of a smaller skin (sums in another order:
+    1e-12 of the largest force)."""
+    print(f"case uneven lanes {prec}", flush=True)
+    side, L = 44.0, 66.0
+    dense = np.stack(W.lattice_config(100000, side, 5, 0.12))
+    g = np.arange(2.0, L - 2.0, 4.0)
+    gas = np.stack(np.meshgrid(g, g, g, indexing="ij")).reshape(3, -1)
+    gas = gas[:, (gas > side + 2.0).any(axis=0)]
+    pos = np.concatenate([dense, gas], axis=1)
+    n = pos.shape[1]
+    pos = [np.ascontiguousarray(p) for p in pos[:, np.random.default_rng(3).permutation(n)]]
+    vel = W.gaussian_velocities(n, 0.5, 3)
+    out = []
+    for skin, windows in ((1.3, 0), (0.3, 0) if prec == "fp64" else (1.3, 1)):
+        s = md.System([(n, W.n_a_for(n), L, 1.0, 3)], precision=prec, positions=pos, velocities=vel, skin=skin,
+                      list_capacity=6.0)
+        if prec != "fp64":
+            md.md_set_force_kernel(s.ctx, windows, 256)
+        s.build_cells()
+        s.forces()
+        assert s.status() == 0
+        out.append((s.numpy(("ax", "ay", "az")), md.md_stats(s.ctx)))
+        s.close()
+    top = max(np.abs(a).max() for a in out[1][0].values())
+    for k in out[0][0]:
+        if prec == "fp64":
+            assert np.abs(out[0][0][k] - out[1][0][k]).max() <= 1e-12 * top, k
+        else:
+            assert np.array_equal(out[0][0][k], out[1][0][k]), k
+    if prec != "fp64":
+        assert out[0][1]["mean_list_len"] == pytest.approx(out[1][1]["mean_list_len"], rel=0.006)
