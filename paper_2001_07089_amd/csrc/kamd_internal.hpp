@@ -25,6 +25,7 @@ constexpr int LIST_ROW_ALIGN = 4;        // neighbour rows are padded to this mu
 constexpr int CELL_SUBX = 4;             // list cells are sorted in sub-cells of a quarter
                                          // cell edge along x (cell_count/start per sub-cell)
 constexpr int VH_MAX_BINS = 1024;       // bins of the self van Hove histogram
+constexpr int DISP_STRIDE = 16;          // words between the displacement maxima of two replicas (disp_push)
 constexpr int SCAN_CHUNK = 2048;         // cells per block of the cell-range scan
 constexpr int SORT_SLOTS = 8192;         // slots and sub-cells per replica up to which
 constexpr int SORT_CELLS = 8192;         // one block sorts a replica (k_rb_sort_small)
@@ -128,7 +129,7 @@ struct Dev {
     int32_t *rb_force;    // per replica: rebuild at the next check regardless
     int32_t *rb_any;      // [2]: [0] the number of waves that rebuild this step (gate)
     int32_t *rb_wlist;    // [nwaves]: those waves, replica by replica (gate)
-    uint32_t *maxdisp;    // per replica: max |r - r_build|^2 (float bits) since the last check
+    uint32_t *maxdisp;    // [n_rep][DISP_STRIDE], first of each: max |r - r_build|^2 (float bits) since the last check
     int32_t *nbr;         // per wave: rows x 64 entries, see list_index
     int2 *kmax;           // per wave: entries of the A part, entries of the B part
     int2 *lbase;          // per wave and part: base slot of 16-bit entries, -1 for 32-bit entries,

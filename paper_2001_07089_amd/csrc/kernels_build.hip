@@ -62,7 +62,7 @@ constexpr int LIST_ALONG_WAVES = 4096;
 constexpr double REBUILD_ALONG = 0.8;
 __device__ inline bool rebuild_flag(const Dev &d, int r, bool along)
 {
-    const double m2 = (double)__uint_as_float(d.maxdisp[r]), t2 = d.rep[r].disp_thr2;
+    const double m2 = (double)__uint_as_float(d.maxdisp[DISP_STRIDE * r]), t2 = d.rep[r].disp_thr2;
     return d.rb_force[r] != 0 || m2 > t2 || (along && m2 > REBUILD_ALONG * REBUILD_ALONG * t2);
 }
 

@@ -42,7 +42,7 @@ __device__ inline void close_step(const Dev &d, int flags)
 {
     if (blockIdx.x != 0) return;
     for (int r = threadIdx.x; r < d.nrep; r += blockDim.x) {
-        d.maxdisp[r] = 0u;
+        d.maxdisp[DISP_STRIDE * r] = 0u;
         d.rb_force[r] = 0;
     }
     if ((flags & FORCE_STEP) && threadIdx.x == 0) d.counters[1] += 1;

@@ -65,7 +65,7 @@ struct kamd_ctx {
     int32_t rows_floor = 0;           // list rows a healed overflow asked for
     uint4 *mirror_alt = nullptr;      // second u32 mirror (fused force+drift steps)
     double4 *pos4_alt = nullptr;      // second packed FP64 position buffer (FP64 fused steps)
-    uint32_t *md_base = nullptr;      // [2][n_rep] displacement maxima
+    uint32_t *md_base = nullptr;      // [2][n_rep][DISP_STRIDE] displacement maxima
     double *Q_dev = nullptr;
     double *rep_arg = nullptr;        // per-replica host arguments staged for a kernel
     double *obs_stage = nullptr;      // device [n_rep][4]
@@ -420,7 +420,7 @@ static void carve_fixed(Dev &d, CtxBufs &b, const Shape &z, Carve &k)
     d.rb_force = k.take<int32_t>(z.nrep);
     d.rb_any = k.take<int32_t>(2);
     d.rb_wlist = k.take<int32_t>(z.nwaves);
-    b.md_base = k.take<uint32_t>(2 * z.nrep);
+    b.md_base = k.take<uint32_t>(2 * DISP_STRIDE * z.nrep);
     d.kmax = k.take<int2>(z.nwaves);
     d.lbase = k.take<int2>(z.nwaves);
     d.pieces = k.take<int2>(z.nwaves * 2 * STAGE_PIECES);
@@ -598,7 +598,7 @@ static int init_fixed(kamd_ctx *c)
     HIPCHK(c, launch_zero_i32(d.nlen, np, c->stream));
     HIPCHK(c, launch_zero_i32(d.rb_force, nr, c->stream));
     HIPCHK(c, launch_zero_i32(d.rb_any, 2, c->stream));
-    HIPCHK(c, launch_zero_i32((int32_t *)c->md_base, 2 * nr, c->stream));
+    HIPCHK(c, launch_zero_i32((int32_t *)c->md_base, 2 * DISP_STRIDE * nr, c->stream));
     HIPCHK(c, launch_zero_i32((int32_t *)d.kmax, 2 * nw, c->stream));
     HIPCHK(c, launch_fill_i32((int32_t *)d.lbase, 2 * nw, -1, c->stream));
     HIPCHK(c, launch_zero_i32((int32_t *)d.pcount, 2 * nw, c->stream));
@@ -845,7 +845,7 @@ static int enqueue_steps(kamd_ctx *c, int nsteps, int ensemble, int mode, int nb
     bool need_drift = true;
     for (int s = 1; s <= nsteps; ++s) {
         dd.mirror = mir[cur];
-        dd.maxdisp = c->md_base + par * c->d.nrep;
+        dd.maxdisp = c->md_base + par * DISP_STRIDE * c->d.nrep;
         dd.pos4 = p4[cur];
         if (need_drift) HIPCHK(c, launch_drift(dd, dt, c->stream));
         TRY(rebuild_chain(c, dd));
@@ -853,7 +853,7 @@ static int enqueue_steps(kamd_ctx *c, int nsteps, int ensemble, int mode, int nb
         const bool reassign = stoch && nb > 0 && (gstep % nb) == 0;
         const bool smp = sample_step(c, gstep);
         if (fused[s]) {
-            HIPCHK(c, launch_force_kd(dd, c->model, prec, dt, mir[1 - cur], c->md_base + (1 - par) * c->d.nrep,
+            HIPCHK(c, launch_force_kd(dd, c->model, prec, dt, mir[1 - cur], c->md_base + (1 - par) * DISP_STRIDE * c->d.nrep,
                                       p4[1 - cur], smp, c->force_wpb, c->stream));
             if (smp) {
                 HIPCHK(c, launch_rep_reduce(dd, 7, c->stream));
@@ -1785,7 +1785,7 @@ extern "C" int md_profile(kamd_ctx *c, int32_t nsteps, double *host_out)
     HIPCHK(c, hipEventRecord(ev[k++], c->stream));
     for (int s = 1; s <= nsteps; ++s) {
         dd.mirror = mir[cur];
-        dd.maxdisp = c->md_base + par * c->d.nrep;
+        dd.maxdisp = c->md_base + par * DISP_STRIDE * c->d.nrep;
         dd.pos4 = p4[cur];
         HIPCHK(c, hipEventRecord(ev[k++], c->stream));
         if (need_drift) HIPCHK(c, launch_drift(dd, dt, c->stream));
@@ -1793,7 +1793,7 @@ extern "C" int md_profile(kamd_ctx *c, int32_t nsteps, double *host_out)
         TRY(rebuild_chain(c, dd));
         HIPCHK(c, hipEventRecord(ev[k++], c->stream));
         if (fused[s]) {
-            HIPCHK(c, launch_force_kd(dd, c->model, prec, dt, mir[1 - cur], c->md_base + (1 - par) * c->d.nrep,
+            HIPCHK(c, launch_force_kd(dd, c->model, prec, dt, mir[1 - cur], c->md_base + (1 - par) * DISP_STRIDE * c->d.nrep,
                                       p4[1 - cur], false, c->force_wpb, c->stream));
             cur = 1 - cur;
             par = 1 - par;
