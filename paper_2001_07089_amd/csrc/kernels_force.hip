@@ -691,6 +691,9 @@ __global__ __launch_bounds__(WAVE * P) void k_force_split(Dev d, Model m, int fl
 //                32,000       51.9,    -, 41.5, 38.1, 38.3
 //                100,000      70.7,    -, 58.0, 59.2, 63.9
 //                2^20          331,  328,  304,  329,  389
+//                80,000          -,    -, 42.1, 40.5     (these three with the later list
+//                120,000         -,    -, 50.1, 51.9     builders, chain and maxima apart)
+//                64 x 1000, bath -,    -, 51.6, 49.2
 //   MIXED        1000         43.3, 40.0,    -, 35.1
 //                64,000       54.9, 49.3,    -, 45.7
 //                100,000      67.6, 58.9,    -, 61.0
@@ -700,7 +703,7 @@ __global__ __launch_bounds__(WAVE * P) void k_force_split(Dev d, Model m, int fl
 // -> 104 / 155 -> 154 us, MIXED_FIXED 114 -> 108 / 144 -> 139 us (2^20: slower).
 // Two wavefronts that share the lists of two (each closing one) measured 306
 // (MIXED_FIXED) and 460 us (FP64) at 2^20; units of 4 entries 326 and 434.
-constexpr int SPLIT8_WAVES = 512, SPLIT4_WAVES = 1024, SPLIT_ORD_WAVES = 1024, SPLIT1_WAVES = 8192;
+constexpr int SPLIT8_WAVES = 512, SPLIT4_WAVES = 1280, SPLIT_ORD_WAVES = 1024, SPLIT1_WAVES = 8192;
 constexpr int SPLIT_ORD_ENERGY_WAVES = 2048;
 
 template <bool ENERGY, bool KD, int P>

@@ -98,3 +98,10 @@ def test_the_force_kernel_closes_the_step(n, prec, windows):
         assert np.array_equal(out[0][k], out[2][k]), k
     for k in ("x", "y", "z", "vx", "vy", "vz"):
         assert np.abs(out[3][k] - out[0][k]).max() < 1e-6, k
+
+
+@pytest.mark.parametrize("n", [81800, 82000])
+def test_split_rule_of_mixed_fixed_at_1280_wavefronts(n):
+    """Four and two wavefronts per list, on either side of the line: the sums
+    are exact, so both equal the window variant's bit for bit."""
+    test_split_equals_unsplit_bit_for_bit(n, "mixed_fixed")
