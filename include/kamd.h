@@ -354,17 +354,19 @@ int md_graph_capture(kamd_ctx *ctx, int32_t nsteps, int32_t ensemble, int32_t mo
 int md_graph_launch(kamd_ctx *ctx);
 
 /* Tuning of the list and of the step kernel, on a copy of the current state
- * that is restored afterwards.  A candidate is timed as the median of three
- * runs of probe_steps NVE steps, or of as many as take about 10 ms if that is
- * more (after a timed warm-up of probe_steps / 4).  Stage
- * 1 times each skin (0.2 .. min(0.5, L/2 - r_c,max)) with each cell division
- * (1, 2) on the current step kernel; stage 2 times, at the list parameters
- * kept, the step kernel with 256, 128 and 64 threads per block and, in the
- * mixed precisions, with windows off and on (md_set_force_kernel).  In each
+ * that is restored afterwards.  A run of a candidate is probe_steps NVE steps,
+ * or as many as take about 10 ms if that is more, replayed from a graph of up
+ * to 100 steps after one warm-up replay.  Every candidate of a stage is run
+ * once, those within 5% of the fastest then twice more in turn, and their
+ * medians compared.  Stage 1 times each skin (0.2 .. min(0.5, L/2 - r_c,max))
+ * with each cell division (1, 2) on the current step kernel; stage 2 times, at
+ * the list parameters kept, in the mixed precisions windows off and on
+ * (md_set_force_kernel), and the step kernel with 256, 128 and 64 threads per
+ * block where that setting applies (256 stands for all elsewhere).  In each
  * stage the first candidate in that order within 1% of the stage's fastest is
  * kept (the smallest skin, the coarser grid, the direct kernel, the larger
  * block): ties are broken the same way on every run.  Candidates whose list
- * overflows are skipped.  Results in host_out (host, FP64 [5]): {skin,
+ * overflows are skipped.  Drops a captured graph.  Results in host_out (host, FP64 [5]): {skin,
  * cell_div, ms_per_step of the kept candidate, windows, threads per block};
  * the context keeps them.  KAMD_ENOMEM when a caller-owned workspace cannot
  * hold every candidate (md_workspace_needed then gives the size).  Syncs. */

@@ -208,6 +208,9 @@ hipError_t launch_force(const Dev &d, const Model &m, int prec, bool energy, int
 // wpb: wavefronts per block of the step kernel (1, 2 or 4; an autotuner axis).
 hipError_t launch_force_kd(const Dev &d, const Model &m, int prec, double dt, uint4 *mirror_out, uint32_t *md_out,
                            double4 *pos4_out, bool energy, int wpb, hipStream_t s);
+// Whether wpb makes a difference (plans whose lists several wavefronts share
+// have blocks of their own).
+bool step_blocks_matter(const Dev &d, int prec);
 // Close the running rebuild check as a force launch does.
 hipError_t launch_close_check(const Dev &d, hipStream_t s);
 

@@ -803,6 +803,11 @@ hipError_t launch_force(const Dev &d, const Model &m, int prec, bool energy, int
     return hipGetLastError();
 }
 
+bool step_blocks_matter(const Dev &d, int prec)
+{
+    return prec != 0 && (d.stage_ok || (prec == 1 && d.nwaves > SPLIT1_WAVES));
+}
+
 hipError_t launch_close_check(const Dev &d, hipStream_t s)
 {
     hipLaunchKernelGGL(k_close_check, dim3(1), dim3(BLOCK), 0, s, d);

@@ -1362,6 +1362,23 @@ extern "C" int md_import(kamd_ctx *c)
     return maybe_export(c);
 }
 
+// Record what enqueue_steps launches into a graph (nothing is executed).
+static int capture_steps(kamd_ctx *c, int nsteps, int ensemble, int mode, int nb)
+{
+    HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
+    int r = enqueue_steps(c, nsteps, ensemble, mode, nb, true);
+    hipGraph_t g = nullptr;
+    hipError_t e = hipStreamEndCapture(c->stream, &g);
+    if (r) {
+        if (g) (void)hipGraphDestroy(g);
+        return r;
+    }
+    if (e != hipSuccess) return fail(c, KAMD_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
+    c->graph = g;
+    HIPCHK(c, hipGraphInstantiate(&c->graph_exec, g, nullptr, nullptr, 0));
+    return KAMD_OK;
+}
+
 extern "C" int md_graph_capture(kamd_ctx *c, int32_t nsteps, int32_t ensemble, int32_t mode, int32_t n_reassign,
                                 double tau)
 {
@@ -1385,17 +1402,7 @@ extern "C" int md_graph_capture(kamd_ctx *c, int32_t nsteps, int32_t ensemble, i
     // the device step counter drives the draw tags inside the graph
     int32_t host_step = (int32_t)c->step;
     HIPCHK(c, hipMemcpy(c->d.counters + 1, &host_step, 4, hipMemcpyHostToDevice));
-    HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    int r = enqueue_steps(c, nsteps, ensemble, mode, n_reassign, true);
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamEndCapture(c->stream, &g);
-    if (r) {
-        if (g) (void)hipGraphDestroy(g);
-        return r;
-    }
-    if (e != hipSuccess) return fail(c, KAMD_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-    c->graph = g;
-    HIPCHK(c, hipGraphInstantiate(&c->graph_exec, g, nullptr, nullptr, 0));
+    TRY(capture_steps(c, nsteps, ensemble, mode, n_reassign));
     c->graph_steps = nsteps;
     return KAMD_OK;
 }
@@ -1615,6 +1622,9 @@ extern "C" int md_log_schedule(int32_t n_md, double t0, int32_t kmax, int32_t *o
     return KAMD_OK;
 }
 
+constexpr int TUNE_CHUNK = 100;  // steps per graph of a timed run
+constexpr int TUNE_ROUNDS = 3;
+
 extern "C" int md_autotune(kamd_ctx *c, int32_t probe_steps, double *host_out)
 {
     if (!c || !host_out) return fail(c, KAMD_EINVAL, "null argument");
@@ -1644,7 +1654,8 @@ extern "C" int md_autotune(kamd_ctx *c, int32_t probe_steps, double *host_out)
         int div;
         bool win;
         int wpb;
-        double ms;
+        double ms = -1.0;         // median of its runs; negative: none, or its list overflows
+        std::vector<double> run;  // ms per step
     };
     hipEvent_t e0, e1;
     HIPCHK(c, hipEventCreate(&e0));
@@ -1653,89 +1664,113 @@ extern "C" int md_autotune(kamd_ctx *c, int32_t probe_steps, double *host_out)
     const bool win0 = c->stage_windows;
     const int wpb0 = c->force_wpb;
     c->cfg.auto_sync = 0;
-    // One candidate from the saved state: a timed warm-up of a quarter of
-    // the probe, then the median of three timed runs of probe_steps steps,
-    // or of as many as take about 10 ms by the warm-up's rate if that is
-    // more (a run must see several list rebuilds, whose cost dominates the
-    // differences between candidates of a small system).  A candidate whose
-    // list overflows is skipped (ms stays negative).
+    const int chunk = std::min(probe_steps, TUNE_CHUNK);
+    auto timed = [&](int n, double &ms) -> int {  // n chunks of steps
+        float t = 0.0f;
+        HIPCHK(c, hipEventRecord(e0, c->stream));
+        for (int q = 0; q < n; ++q) {
+            if (c->graph_exec) HIPCHK(c, hipGraphLaunch(c->graph_exec, c->stream));
+            else TRY(enqueue_steps(c, chunk, 0, 0, 0, false));
+        }
+        HIPCHK(c, hipEventRecord(e1, c->stream));
+        HIPCHK(c, hipEventSynchronize(e1));
+        HIPCHK(c, hipEventElapsedTime(&t, e0, e1));
+        ms = t;
+        return KAMD_OK;
+    };
+    // One run of one candidate from the saved state, as replays of a graph of
+    // `chunk` steps: eager steps of a small system take about as long as the
+    // host needs to launch them, and would time the host.  (A stream that
+    // cannot be captured, the null stream, has its steps enqueued.)  The first
+    // chunk warms up and gives the rate; the timed ones make probe_steps
+    // steps, or as many as take about 10 ms if that is more (a run must see
+    // several list rebuilds, whose cost dominates the differences between
+    // candidates of a small system).  A candidate whose list overflows is
+    // skipped.
     auto probe = [&](Cand &k) -> int {
-        k.ms = -1.0;
         drop_graph(c);
         c->stage_windows = k.win;
         c->d.stage_ok = mixed && k.win;
         c->force_wpb = k.wpb;
         TRY(apply_list_params(c, k.skin, k.div, false));
         TRY(md_set_state(c, blob.data(), nb));
-        const int warm = std::max(1, probe_steps / 4);
-        float tw = 0.0f;
-        HIPCHK(c, hipEventRecord(e0, c->stream));
-        TRY(enqueue_steps(c, warm, 0, 0, 0, false));
-        HIPCHK(c, hipEventRecord(e1, c->stream));
-        HIPCHK(c, hipEventSynchronize(e1));
-        HIPCHK(c, hipEventElapsedTime(&tw, e0, e1));
-        const double per = std::max(1e-4, (double)tw / warm);
-        const int steps = (int)std::min(20000.0, std::max((double)probe_steps, std::ceil(10.0 / per)));
-        float t[3];
-        for (int r = 0; r < 3; ++r) {
-            HIPCHK(c, hipEventRecord(e0, c->stream));
-            TRY(enqueue_steps(c, steps, 0, 0, 0, false));
-            HIPCHK(c, hipEventRecord(e1, c->stream));
-            HIPCHK(c, hipEventSynchronize(e1));
-            HIPCHK(c, hipEventElapsedTime(&t[r], e0, e1));
+        if (!c->stream || capture_steps(c, chunk, 0, 0, 0)) {
+            drop_graph(c);
+            (void)hipGetLastError();
         }
+        double warm = 0.0, ms = 0.0;
+        TRY(timed(1, warm));
+        const double per = std::max(1e-4, warm / chunk);
+        const double steps = std::min(20000.0, std::max((double)probe_steps, std::ceil(10.0 / per)));
+        const int n = (int)std::ceil(steps / chunk);
+        TRY(timed(n, ms));
         uint32_t word = 0;
         HIPCHK(c, hipMemcpy(&word, c->d.err, 4, hipMemcpyDeviceToHost));
         if (word == 0) {
-            std::sort(t, t + 3);
-            k.ms = (double)t[1] / steps;
+            k.run.push_back(ms / ((double)n * chunk));
+            std::vector<double> t = k.run;
+            std::sort(t.begin(), t.end());
+            k.ms = t[t.size() / 2];
         } else if (word == KAMD_DEV_LIST_OVERFLOW) {  // this candidate's list is too short: skip it
             const uint32_t zero = 0;
             HIPCHK(c, hipMemcpy(c->d.err, &zero, 4, hipMemcpyHostToDevice));
+            k.ms = -1.0;
         } else {
             return fail(c, KAMD_EDEVICE, "device error word 0x%x while probing", word);
         }
         return KAMD_OK;
     };
-    // Within 1% of the fastest the timings are not told apart reliably; the
-    // first such candidate in the order tried is kept.  Stage 1 orders by
-    // skin, then grid (the smallest list first); stage 2 tries the direct
-    // kernel before the windows, and the larger blocks first.
-    auto pick = [](const std::vector<Cand> &v) -> int {
-        double fastest = 1e300;
+    auto fastest = [](const std::vector<Cand> &v) {
+        double f = 1e300;
         for (const Cand &k : v)
-            if (k.ms > 0.0) fastest = std::min(fastest, k.ms);
-        for (size_t i = 0; i < v.size(); ++i)
-            if (v[i].ms > 0.0 && v[i].ms <= 1.01 * fastest) return (int)i;
-        return -1;
+            if (k.ms > 0.0) f = std::min(f, k.ms);
+        return f;
     };
-    int rc = KAMD_OK;
+    // One stage: every candidate is run once, then those within 5% of the
+    // fastest in turn until each has TUNE_ROUNDS runs, so that a drift of the
+    // clocks falls on all of them alike.  Medians within 1% of the fastest are
+    // not told apart reliably; the first such candidate in the order given is
+    // kept: stage 1 orders by skin, then grid (the smallest list first); stage
+    // 2 has the direct kernel before the windows, and the larger blocks first.
+    auto contest = [&](std::vector<Cand> &v, int &pick) -> int {
+        pick = -1;
+        for (Cand &k : v) TRY(probe(k));
+        const double f1 = fastest(v);
+        for (Cand &k : v)
+            if (k.ms > 1.05 * f1) k.ms = -1.0;
+        for (int round = 1; round < TUNE_ROUNDS; ++round)
+            for (Cand &k : v)
+                if (k.ms > 0.0) TRY(probe(k));
+        const double f = fastest(v);
+        for (size_t i = 0; i < v.size() && pick < 0; ++i)
+            if (v[i].ms > 0.0 && v[i].ms <= 1.01 * f) pick = (int)i;
+        return KAMD_OK;
+    };
     // Stage 1: list parameters (skin x cell division) with the current kernel.
     std::vector<Cand> st1;
     for (double s : skins)
         for (int dv = 1; dv <= 2; ++dv) {
             Plan Pt;
             make_plan(&c->cfg, c->reps.data(), (int)c->reps.size(), s, dv, Pt, c->rows_floor);
-            if (Pt.ncells_wide <= MAX_PLAN_CELLS) st1.push_back({s, dv, win0, wpb0, -1.0});
+            if (Pt.ncells_wide <= MAX_PLAN_CELLS) st1.push_back({s, dv, win0, wpb0});
         }
-    for (Cand &k : st1)
-        if (!rc) rc = probe(k);
-    const int i1 = rc ? -1 : pick(st1);
-    Cand best = i1 >= 0 ? st1[i1] : Cand{c->skin, c->cell_div, win0, wpb0, -1.0};
-    // Stage 2: the force kernel at those list parameters: block size
-    // {256, 128, 64} threads, and (mixed precisions) windows off or on.
-    std::vector<Cand> st2;
-    if (i1 >= 0) {
-        for (int w = 0; w < (mixed ? 2 : 1); ++w)
-            for (int wpb : {4, 2, 1}) {
-                if ((w != 0) == best.win && wpb == best.wpb) {
-                    st2.push_back(best);  // already timed
-                } else {
-                    st2.push_back({best.skin, best.div, w != 0, wpb, -1.0});
-                    if (!rc) rc = probe(st2.back());
-                }
-            }
-        const int i2 = rc ? -1 : pick(st2);
+    int i1 = -1, i2 = -1;
+    int rc = contest(st1, i1);
+    Cand best = i1 >= 0 ? st1[i1] : Cand{c->skin, c->cell_div, win0, wpb0};
+    // Stage 2: the force kernel at those list parameters: windows off or on
+    // (mixed precisions), and the block sizes where they make a difference
+    // (elsewhere the default stands for all).
+    if (!rc && i1 >= 0) {
+        std::vector<Cand> st2;
+        for (int w = 0; w < (mixed ? 2 : 1); ++w) {
+            Dev d = c->d;
+            d.stage_ok = mixed && w;
+            const bool blocks = step_blocks_matter(d, c->cfg.precision);
+            for (int wpb : {4, 2, 1})
+                if (blocks || wpb == WAVES_PER_BLOCK) st2.push_back({best.skin, best.div, w != 0, wpb});
+        }
+        if (st2.size() > 1) rc = contest(st2, i2);
+        else best.wpb = st2[0].wpb;
         if (i2 >= 0) best = st2[i2];
     }
     (void)hipEventDestroy(e0);

@@ -1,0 +1,88 @@
+"""The autotuner times the device, not the host: with other processes on the
+tuner's only CPU, so that the host launches steps several times slower than the
+device runs them, the time of the pick is still that of a graph replay."""
+import multiprocessing
+import os
+import sys
+import time
+
+import pytest
+
+from paper_2001_07089_amd import md
+from paper_2001_07089_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _spin(cpu, stop):
+    os.sched_setaffinity(0, {cpu})
+    end = time.monotonic() + 60.0
+    while not stop.is_set() and time.monotonic() < end:
+        for _ in range(1000000):
+            pass
+
+
+def _system(n, precision):
+    L = W.box_for(n, 1.2)
+    s = md.System([(n, W.n_a_for(n), L, 0.5, 3)], precision=precision, positions=W.lattice_config(n, L, 5, 0.08),
+                  velocities=W.gaussian_velocities(n, 0.7, 3))
+    s.step_nvt(300, md.NVT_STOCHASTIC, n_reassign=10)
+    return s
+
+
+def _replay_ms(s):
+    """ms per step of a replayed graph at the context's list parameters."""
+    s.step_nve(100)
+    s.capture(100)
+    best = 1e300
+    for _ in range(4):
+        s.launch()
+        s.stream.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(6):
+            s.launch()
+        s.stream.synchronize()
+        best = min(best, (time.perf_counter() - t0) / 600)
+    return 1e3 * best
+
+
+def test_pick_is_timed_on_the_device():
+    """Four processes take turns of some milliseconds on one CPU: eager steps
+    would take about four times the launch time of one, 60 us or more; replays
+    21 us.  Half as much again is allowed for the clocks."""
+    print("case autotune under host load", flush=True)
+    s = _system(32000, "mixed_fixed")
+    before = os.sched_getaffinity(0)
+    cpu = min(before)
+    ctx = multiprocessing.get_context("spawn")
+    stop = ctx.Event()
+    load = [ctx.Process(target=_spin, args=(cpu, stop)) for _ in range(3)]
+    for p in load:
+        p.start()
+    time.sleep(2.0)
+    try:
+        os.sched_setaffinity(0, {cpu})
+        pick = s.autotune(50)
+    finally:
+        os.sched_setaffinity(0, before)
+        stop.set()
+        for p in load:
+            p.join()
+    ms = _replay_ms(s)
+    print(f"  pick {pick}, replay {ms:.4f} ms", flush=True)
+    sys.stdout.flush()
+    assert pick["ms_per_step"] <= 1.5 * ms
+    s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed", "mixed_fixed"])
+def test_block_size_is_the_default_where_it_means_nothing(precision):
+    """Several wavefronts share a list at this size, in blocks of their own:
+    whatever the setting was, the pick has the default."""
+    print(f"case autotune block size {precision}", flush=True)
+    s = _system(4000, precision)
+    md.md_set_force_kernel(s.ctx, 0, 64)
+    pick = s.autotune(20)
+    assert pick["windows"] or pick["wg_size"] == 256
+    assert md.md_stats(s.ctx)["wg_size"] == pick["wg_size"]
+    s.close()
