@@ -182,6 +182,9 @@ struct Dev {
 void release_static_workspace(int device);
 void set_init_error(const char *msg);
 void mark_static(kamd_ctx *c, int device);
+// md_init; with allocate false (and a workspace) it calls no allocating routine.
+int init_context(kamd_ctx **out, const kamd_config *cfg, const kamd_replica *reps, int32_t n_rep, const kamd_state *st,
+                 void *workspace, size_t ws_bytes, void *hip_stream, bool allocate);
 
 // ---------------------------------------------------------------- launchers
 // Each returns hipGetLastError() after its launch(es).

@@ -11,6 +11,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <random>
 #include <string>
 #include <thread>
@@ -84,7 +85,7 @@ struct kamd_ctx {
     Plan plan;                        // the current list parameters' layout
     Shape shape;                      // sizes of the workspace's fixed part
     int static_device = -1;           // >= 0: the workspace is that device's static array
-    uint32_t *err_host = nullptr;     // pinned: the device error word, read after eager calls
+    uint32_t *err_host = nullptr;     // pinned word the device error word is read into (null: none was free)
     bool stage_windows = false;       // mixed-precision force kernels gather from LDS windows
     int force_wpb = WAVES_PER_BLOCK;  // wavefronts per block of the step kernel
     std::string err = "no error";
@@ -929,6 +930,38 @@ static int snapshot_restore(kamd_ctx *c)
     return force_rebuild_all(c);
 }
 
+// Pinned words for the contexts of the process, one cache line apart, in one
+// page that the first md_init allocates and the process keeps: a context
+// neither allocates nor frees pinned memory of its own, which would wait for
+// the whole device.  Contexts beyond the page's words, and those of
+// md_init_static where there is no page yet, have none.
+constexpr int ERR_WORDS = 64, ERR_WORD_STRIDE = 64 / sizeof(uint32_t);
+static std::mutex g_err_mutex;
+static uint32_t *g_err_page = nullptr;
+static uint64_t g_err_used = 0;  // bit k: word k is a context's
+static_assert(ERR_WORDS == 64, "one bit each");
+
+static uint32_t *take_err_word(bool allocate)
+{
+    std::lock_guard<std::mutex> lock(g_err_mutex);
+    if (!g_err_page && allocate &&
+        hipHostMalloc((void **)&g_err_page, 4 * ERR_WORDS * ERR_WORD_STRIDE, hipHostMallocPortable) != hipSuccess) {
+        g_err_page = nullptr;
+        (void)hipGetLastError();
+    }
+    if (!g_err_page || g_err_used == ~0ull) return nullptr;
+    const int k = __builtin_ctzll(~g_err_used);
+    g_err_used |= 1ull << k;
+    return g_err_page + k * ERR_WORD_STRIDE;
+}
+
+static void give_err_word(uint32_t *p)
+{
+    if (!p) return;
+    std::lock_guard<std::mutex> lock(g_err_mutex);
+    g_err_used &= ~(1ull << ((p - g_err_page) / ERR_WORD_STRIDE));
+}
+
 // Waits for the stream.  redo: a list overflowed, the bit is cleared and the
 // list has grown to the rows its build asked for.  The error word comes into
 // pinned memory with one wait for both (31 -> 21 us for a small kernel, the word
@@ -936,9 +969,10 @@ static int snapshot_restore(kamd_ctx *c)
 static int heal_list(kamd_ctx *c, bool &redo)
 {
     redo = false;
-    HIPCHK(c, hipMemcpyAsync(c->err_host, c->d.err, 4, hipMemcpyDeviceToHost, c->stream));
+    uint32_t w = 0, *word = c->err_host ? c->err_host : &w;
+    HIPCHK(c, hipMemcpyAsync(word, c->d.err, 4, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    const uint32_t w = *c->err_host;
+    w = *word;
     if (!(w & KAMD_DEV_LIST_OVERFLOW)) return KAMD_OK;
     int32_t cnt[8];
     HIPCHK(c, hipMemcpy(cnt, c->d.counters, 32, hipMemcpyDeviceToHost));
@@ -1039,6 +1073,12 @@ static int apply_list_params(kamd_ctx *c, double skin, int cell_div, bool first)
 extern "C" int md_init(kamd_ctx **out, const kamd_config *cfg, const kamd_replica *reps, int32_t n_rep,
                        const kamd_state *st, void *workspace, size_t ws_bytes, void *hip_stream)
 {
+    return init_context(out, cfg, reps, n_rep, st, workspace, ws_bytes, hip_stream, true);
+}
+
+int kamd::init_context(kamd_ctx **out, const kamd_config *cfg, const kamd_replica *reps, int32_t n_rep,
+                       const kamd_state *st, void *workspace, size_t ws_bytes, void *hip_stream, bool allocate)
+{
     if (!out) return fail(nullptr, KAMD_EINVAL, "out is null");
     *out = nullptr;
     int rc = validate(nullptr, cfg, reps, n_rep);
@@ -1081,7 +1121,7 @@ extern "C" int md_init(kamd_ctx **out, const kamd_config *cfg, const kamd_replic
             c->ws_bytes = need;
             c->ws_owned = true;
         }
-        HIPCHK(c, hipHostMalloc((void **)&c->err_host, sizeof *c->err_host, hipHostMallocDefault));
+        c->err_host = take_err_word(allocate);
         bind_workspace(c, P);
         TRY(init_fixed(c));
         TRY(init_list(c));
@@ -1900,7 +1940,7 @@ extern "C" int md_destroy(kamd_ctx *c)
     (void)hipStreamSynchronize(c->stream);
     drop_graph(c);
     if (c->ws_owned && c->ws) (void)hipFree(c->ws);
-    if (c->err_host) (void)hipHostFree(c->err_host);
+    give_err_word(c->err_host);
     if (c->static_device >= 0) release_static_workspace(c->static_device);
     c->ws = nullptr;
     delete c;

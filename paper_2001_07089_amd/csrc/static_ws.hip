@@ -77,7 +77,7 @@ extern "C" int md_init_static(kamd_ctx **out, const kamd_config *cfg, const kamd
         }
         g_addr[dev] = p;
     }
-    rc = md_init(out, cfg, reps, n_rep, st, g_addr[dev], STATIC_WS_BYTES, hip_stream);
+    rc = kamd::init_context(out, cfg, reps, n_rep, st, g_addr[dev], STATIC_WS_BYTES, hip_stream, false);
     if (rc == KAMD_OK) {
         g_in_use[dev] = true;
         kamd::mark_static(*out, dev);
