@@ -411,10 +411,12 @@ __global__ __launch_bounds__(BLOCK) void k_rb_sortgather(Dev d)
 // sub-cells): the gate and the whole counting sort in one kernel, one block per
 // replica, with the counters, their scan and the order in LDS.  A step without
 // a rebuild then launches two chain kernels instead of six, and a rebuild's sort
-// is one pass over its replica instead of five kernels.  Every block decides the
-// flags of all replicas by itself (the rule of k_rb_gate), from which follow the
-// worklist's length and the place of its own replica in it.  The result is that
-// of the other chain: a stable sort by sub-cell.
+// is one pass over its replica instead of five kernels.  Up to SORT_ALONE_REPS
+// replicas every block decides the flags of all of them by itself (the rule of
+// k_rb_gate), from which follow the worklist's length and the place of its own
+// replica in it; beyond, where that would be quadratic work, the gate runs
+// first (GATED).  The result is that of the other chain: a stable sort by
+// sub-cell.
 //
 // Bound by latency: on a step that rebuilds, the passes over the counters and
 // particles of one replica by one block (12 us at 1000 particles); otherwise by
@@ -436,7 +438,7 @@ __device__ inline int block_sum(int v, int *part)  // all threads of a SORT_THRE
     return t;
 }
 
-template <bool GATHER>
+template <bool GATHER, bool GATED>
 __global__ __launch_bounds__(SORT_THREADS) void k_rb_sort_small(Dev d)
 {
     __shared__ int start[SORT_CELLS];         // counters, then the sub-cells' first slots
@@ -444,10 +446,11 @@ __global__ __launch_bounds__(SORT_THREADS) void k_rb_sort_small(Dev d)
     __shared__ int part[SORT_THREADS / WAVE];
     const int me = blockIdx.x, t = threadIdx.x, lane = lane_id();
     // the gate
-    bool along = false, mine;
     int before = 0;
-    if (d.nrep == 1) {
-        mine = rebuild_flag(d, 0, false);
+    if (GATED) {
+        if (d.rb_any[0] == 0 || !rebuild_flag(d, me, d.rb_any[1] != 0)) return;
+    } else if (d.nrep == 1) {
+        const bool mine = rebuild_flag(d, 0, false);
         if (t == 0) {
             d.rb_any[0] = mine ? d.nwaves : 0;
             d.rb_any[1] = 0;
@@ -458,7 +461,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_rb_sort_small(Dev d)
         for (int r = t; r < d.nrep; r += SORT_THREADS)
             if (rebuild_flag(d, r, false)) must += d.rep[r].wave1 - d.rep[r].wave0;
         must = block_sum(must, part);
-        along = must > 0 && must < LIST_ALONG_WAVES;
+        const bool along = must > 0 && must < LIST_ALONG_WAVES;
         int total = 0;
         if (must > 0) {
             for (int r = t; r < d.nrep; r += SORT_THREADS)
@@ -481,7 +484,8 @@ __global__ __launch_bounds__(SORT_THREADS) void k_rb_sort_small(Dev d)
     const int base = R.wave0 * WAVE, nc = R.nc, nslot = (R.wave1 - R.wave0) * WAVE;
     const int b0 = B.slot0 - base;                            // the replica's first B slot
     const int sub0 = CELL_SUBX * A.cell0, nsub = CELL_SUBX * (A.ncell + 1 + B.ncell);  // A's spare cell between
-    for (int i = t; i < R.wave1 - R.wave0; i += SORT_THREADS) d.rb_wlist[before + i] = R.wave0 + i;
+    if (!GATED)
+        for (int i = t; i < R.wave1 - R.wave0; i += SORT_THREADS) d.rb_wlist[before + i] = R.wave0 + i;
     if (t == 0) atomicAdd(&d.counters[0], 1);
     for (int i = t; i < nsub; i += SORT_THREADS) start[i] = 0;
     __syncthreads();
@@ -1735,12 +1739,27 @@ constexpr int CHAIN_MAX_BLOCKS = 1024;  // grid cap of the grid-stride chain ker
 static inline int nblk_capped(int waves) { return std::min((waves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK, CHAIN_MAX_BLOCKS); }
 
 constexpr int SORT_GATHER_WAVES = 48;  // N = 3000: equal either way
+// Measured (us per MIXED step, each block for itself / the gate first / the other
+// chain): 256 replicas of 100 19.6 / 20.5 / 24.2, 512 32.9 / 32.0 / 35.7, 1024
+// 50.5 / 44.3 / 47.4, 4096 215 / 104 / 104, 16,384 2352 / 388 / 379; 256 of 1000
+// 86.5 / 88.0 / 91.5, 700 184.4 / 183.3 / 186.1.
+constexpr int SORT_ALONE_REPS = 384;
+template <bool GATHER>
+static void launch_sort_small(const Dev &d, hipStream_t s)
+{
+    if (d.nrep <= SORT_ALONE_REPS) {
+        hipLaunchKernelGGL((k_rb_sort_small<GATHER, false>), dim3(d.nrep), dim3(SORT_THREADS), 0, s, d);
+    } else {
+        hipLaunchKernelGGL(k_rb_gate, dim3(1), dim3(GATE_THREADS), 0, s, d);
+        hipLaunchKernelGGL((k_rb_sort_small<GATHER, true>), dim3(d.nrep), dim3(SORT_THREADS), 0, s, d);
+    }
+}
 hipError_t launch_rb_sort_small(const Dev &d, hipStream_t s)
 {
     if (d.rep_waves_max <= SORT_GATHER_WAVES) {
-        hipLaunchKernelGGL(k_rb_sort_small<true>, dim3(d.nrep), dim3(SORT_THREADS), 0, s, d);
+        launch_sort_small<true>(d, s);
     } else {
-        hipLaunchKernelGGL(k_rb_sort_small<false>, dim3(d.nrep), dim3(SORT_THREADS), 0, s, d);
+        launch_sort_small<false>(d, s);
         hipLaunchKernelGGL(k_rb_gather, dim3(nblk_capped(d.nwaves)), dim3(BLOCK), 0, s, d);
     }
     return hipGetLastError();
