@@ -405,7 +405,8 @@ __global__ __launch_bounds__(RDF_THREADS) void k_rdf_hist(Dev d, double dr, int 
 }
 
 // The partial histograms of every replica, added to the result: one block
-// per replica and 64 bins, 16 partial histograms at a time.
+// per replica and 64 bins, 16 partial histograms at a time.  The additions are
+// atomic: another context may be adding to the same result on its own stream.
 __global__ __launch_bounds__(1024) void k_rdf_reduce(Dev d, int nbins, uint64_t *hist, const double *scratch)
 {
     __shared__ uint64_t red[16][WAVE];
@@ -423,7 +424,7 @@ __global__ __launch_bounds__(1024) void k_rdf_reduce(Dev d, int nbins, uint64_t 
     __syncthreads();
     if (q == 0 && b < row) {
         for (int k = 1; k < 16; ++k) v += red[k][lane_id()];
-        hist[(size_t)rep * row + b] += v;
+        if (v) atomicAdd((unsigned long long *)&hist[(size_t)rep * row + b], (unsigned long long)v);
     }
 }
 

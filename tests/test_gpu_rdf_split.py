@@ -61,3 +61,26 @@ def test_uneven_batch():
     check(s, pos, reps, 3.1 / 200, 200)
     check(s, pos, reps, 3.05 / 3000, 3000)
     s.close()
+
+
+def test_two_contexts_add_to_one_histogram():
+    """Measurements of two contexts on their own streams accumulate into one
+    tensor at the same time: no count is lost, of partial histograms (20 bins)
+    or of blocks that add to the result themselves (600 bins of 200 particles)."""
+    print("case rdf two contexts", flush=True)
+    for n, nb in ((3000, 20), (200, 600)):
+        L = max(W.box_for(n, 1.2), 6.2)
+        reps = [(n, W.n_a_for(n), L, 1.0, 1)]
+        pos = [W.lattice_config(n, L, 7 + k, 0.2) for k in range(2)]
+        ss = [md.System(reps, precision="mixed", positions=p, velocities=W.gaussian_velocities(n, 1.0, 2)) for p in pos]
+        hist = ss[0]._zeros((1, 3, nb), ss[0].torch.int64)
+        ss[0].stream.synchronize()
+        for _ in range(200):
+            for s in ss:
+                s.rdf(3.0 / nb, nb, hist)
+        for s in ss:
+            s.stream.synchronize()
+        ref = sum(O.rdf_hist(*p, reps[0][1], L, 3.0 / nb, nb).astype(np.int64) for p in pos)
+        assert np.array_equal(ss[0]._host(hist)[0], 200 * ref)
+        for s in ss:
+            s.close()
