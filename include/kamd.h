@@ -377,8 +377,10 @@ int md_autotune(kamd_ctx *ctx, int32_t probe_steps, double *host_out);
  * thirds of the given one, where that gives its box more cells per edge and
  * (cell-volume ratio) x (smaller skin / skin) is 1.15 or more: small boxes,
  * whose cells are otherwise well over a list radius wide.  The largest such
- * skin is taken, and the replica's rebuild test uses it too.  md_stats
- * reports the smallest skin in use.  The forces do not depend on the skin. */
+ * skin is taken, and the replica's rebuild test uses it too.  A box too small
+ * for the given skin, one of edge L < (largest cutoff + skin) / 0.707, takes
+ * 0.707 L - largest cutoff.  md_stats reports the smallest skin in use.  The
+ * forces do not depend on the skin. */
 int md_set_list_params(kamd_ctx *ctx, double skin, int32_t cell_div);
 
 /* Step-kernel variant.  windows (mixed precisions): 1 gathers

@@ -209,6 +209,13 @@ static int cell_cap(int dim) { return dim == 2 ? 4096 : 256; }  // nc^(dim) <= M
 // cutoff, and so every force, does not depend on it.
 constexpr double SKIN_TRIM = 2.0 / 3.0;
 constexpr double CELL_GAIN = 1.15;
+// Largest list radius of a replica, in box edges.  The list builders compare
+// squared separations in units of 2^-16 edges with a signed 32-bit bound
+// (RepInfo::r2c), which holds radii of up to 0.7071 edges: with a longer one
+// they would leave out the pairs beyond that and still wait for moves of half
+// the longer skin.  A replica whose box is too small for the requested skin
+// takes the largest that fits (the cutoff alone is below half an edge).
+constexpr double LIST_REACH = 0.707;
 
 static double list_skin(const kamd_config *cfg) { return cfg->skin < 0.0 ? 0.3 : cfg->skin; }
 
@@ -234,14 +241,15 @@ static void make_plan(const kamd_config *cfg, const kamd_replica *reps, int n_re
         return (int)std::max(1.0, std::min(std::floor(box * reach / (rcmax + s)), (double)cell_cap(dim_of(cfg))));
     };
     auto rep_skin = [&](double box) {
-        if (reach != 1 || !(skin > 0.0)) return skin;
-        const double lo = SKIN_TRIM * skin;
-        const int n0 = cells_per_edge(box, skin), n1 = cells_per_edge(box, lo);
-        if (n1 < 3 || n1 <= n0) return skin;
-        double s = std::min(skin, box / n1 - rcmax);  // the largest skin with n1 cells, up to rounding
+        const double top = std::min(skin, LIST_REACH * box - rcmax);
+        if (reach != 1 || !(top > 0.0)) return top;
+        const double lo = SKIN_TRIM * top;
+        const int n0 = cells_per_edge(box, top), n1 = cells_per_edge(box, lo);
+        if (n1 < 3 || n1 <= n0) return top;
+        double s = std::min(top, box / n1 - rcmax);  // the largest skin with n1 cells, up to rounding
         while (s > lo && cells_per_edge(box, s) < n1) s = std::nextafter(s, 0.0);
         s = std::max(s, lo);
-        return std::pow((double)n1 / n0, planar ? 2 : 3) * (s / skin) >= CELL_GAIN ? s : skin;
+        return std::pow((double)n1 / n0, planar ? 2 : 3) * (s / top) >= CELL_GAIN ? s : top;
     };
     std::vector<double> rskin(n_rep);
     for (int r = 0; r < n_rep; ++r) {  // the grid size first (an oversize plan is refused)
@@ -279,10 +287,10 @@ static void make_plan(const kamd_config *cfg, const kamd_replica *reps, int n_re
             const double rl = rc + skin_r;
             R.rc2_fx[p] = (float)((rc / h) * (rc / h));
             R.rl2_fx[p] = (float)((rl / h) * (rl / h) * (1.0 + 4e-6));
-            // list radius in 2^16-step units + sqrt(3), squared (see k_rb_list); boxes
-            // too small for the unit to matter have radii far below 2^16 units
+            // list radius in 2^16-step units + sqrt(3), squared (see k_rb_list);
+            // below 2^31 for radii of up to LIST_REACH edges
             const double rc16 = std::sqrt((double)R.rl2_fx[p]) * (1.0 / 65536.0) + 1.7320508075688772;
-            R.r2c[p] = (int32_t)std::min(std::ceil(rc16 * rc16) + 1.0, 2147483647.0);
+            R.r2c[p] = (int32_t)(std::ceil(rc16 * rc16) + 1.0);
             R.sig2_fx[p] = (float)((cfg->model.sigma[p] / h) * (cfg->model.sigma[p] / h));
             R.c48_h[p] = 48.0 * cfg->model.eps[p] / h;
             R.fix_k[p] = R.c48_h[p] * FIX_SCALE;
