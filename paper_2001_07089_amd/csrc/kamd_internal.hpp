@@ -234,7 +234,8 @@ hipError_t launch_ke_partial(const Dev &d, hipStream_t s);
 hipError_t launch_import(const Dev &d, const double *const *arr, const int32_t *img, hipStream_t s);
 // Export and restore use the sort's scratch arrays (sx ..., simg).
 constexpr int EXPORT_RECORD_BYTES = 96;  // per particle
-hipError_t launch_export(const Dev &d, double *const *arr, int32_t *img, hipStream_t s);
+// An export does nothing while the device error word has a bit of `unless`.
+hipError_t launch_export(const Dev &d, double *const *arr, int32_t *img, uint32_t unless, hipStream_t s);
 // A state kept by slot, without the padding.
 struct Snapshot {
     double *state;         // [9][n_total]

@@ -302,8 +302,9 @@ struct Arr9w {
 
 // Blocks remapped: the particles of a replica are written from one XCD, whose L2
 // puts their scattered words together (64 replicas of 16,384: 138 -> 64 us).
-__global__ __launch_bounds__(BLOCK) void k_export(Dev d, Arr9w a, int32_t *img)
+__global__ __launch_bounds__(BLOCK) void k_export(Dev d, Arr9w a, int32_t *img, uint32_t unless)
 {
+    if (*d.err & unless) return;
     SlotCtx c;
     if (!slot_ctx(d, c, xcd_block(blockIdx.x, gridDim.x))) return;
     if (!c.real) return;
@@ -354,8 +355,9 @@ __global__ __launch_bounds__(BLOCK) void k_export_records(Dev d)
     reinterpret_cast<ExportRecord *>(d.sx)[g] = r;
 }
 
-__global__ __launch_bounds__(BLOCK) void k_export_arrays(Dev d, Arr9w a, int32_t *img)
+__global__ __launch_bounds__(BLOCK) void k_export_arrays(Dev d, Arr9w a, int32_t *img, uint32_t unless)
 {
+    if (*d.err & unless) return;
     const int g = blockIdx.x * BLOCK + threadIdx.x;
     if (g >= d.n_total) return;
     const ExportRecord r = reinterpret_cast<const ExportRecord *>(d.sx)[g];
@@ -535,15 +537,16 @@ hipError_t launch_import(const Dev &d, const double *const *arr, const int32_t *
 // particles 8.9 / 10.2, 100,000 14.2 / 13.2, 262,144 40 / 21, 2^20 155 / 69; 64
 // replicas of 16,384 64 / 68, eight of 131,072 136 / 67.
 constexpr int EXPORT_RECORD_WAVES = 1500;
-hipError_t launch_export(const Dev &d, double *const *arr, int32_t *img, hipStream_t s)
+hipError_t launch_export(const Dev &d, double *const *arr, int32_t *img, uint32_t unless, hipStream_t s)
 {
     Arr9w a;
     for (int k = 0; k < 9; ++k) a.p[k] = arr[k];
     if (d.rep_waves_max >= EXPORT_RECORD_WAVES) {
         hipLaunchKernelGGL(k_export_records, dim3(nblk(d)), dim3(BLOCK), 0, s, d);
-        hipLaunchKernelGGL(k_export_arrays, dim3((d.n_total + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, d, a, img);
+        hipLaunchKernelGGL(k_export_arrays, dim3((d.n_total + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, d, a, img,
+                           unless);
     } else {
-        hipLaunchKernelGGL(k_export, dim3(nblk(d)), dim3(BLOCK), 0, s, d, a, img);
+        hipLaunchKernelGGL(k_export, dim3(nblk(d)), dim3(BLOCK), 0, s, d, a, img, unless);
     }
     return hipGetLastError();
 }

@@ -794,14 +794,15 @@ static int mb_reassign(kamd_ctx *c, bool device_tag, uint32_t tag)
     return KAMD_OK;
 }
 
-static int do_export(kamd_ctx *c)
+// unless: error bits under which the device leaves the caller's arrays alone.
+static int do_export(kamd_ctx *c, uint32_t unless = 0)
 {
     double *a[9] = {c->st.x, c->st.y, c->st.z, c->st.vx, c->st.vy, c->st.vz, c->st.ax, c->st.ay, c->st.az};
-    HIPCHK(c, launch_export(c->d, a, c->st.img, c->stream));
+    HIPCHK(c, launch_export(c->d, a, c->st.img, unless, c->stream));
     return KAMD_OK;
 }
 
-static int maybe_export(kamd_ctx *c) { return c->cfg.auto_sync ? do_export(c) : KAMD_OK; }
+static int maybe_export(kamd_ctx *c, uint32_t unless = 0) { return c->cfg.auto_sync ? do_export(c, unless) : KAMD_OK; }
 
 // Whether the observables are sampled at the end of global step gstep.
 static bool sample_step(const kamd_ctx *c, int64_t gstep)
@@ -1014,25 +1015,26 @@ static int heal_build(kamd_ctx *c, bool force, bool energy)
 static int heal_forces(kamd_ctx *c, bool energy) { return heal_build(c, true, energy); }
 
 // Eager steps, redone from the call's starting state while a list overflows.
-// On failure (a caller-owned workspace too small for the grown list) the state
-// is that of the start of the call.  The export, where the caller wants one, is
-// launched before the wait rather than after it.
+// On failure (a caller-owned workspace too small for the grown list, or no
+// more attempts) the state is that of the start of the call, and the caller's
+// arrays are as they were.  The export, where the caller wants one, is
+// launched before the wait rather than after it: whether a list has overflowed
+// is known on the device.
 static int heal_steps(kamd_ctx *c, int nsteps, int ensemble, int mode, int nb)
 {
     TRY(snapshot_save(c));
     for (int attempt = 0;; ++attempt) {
         TRY(enqueue_steps(c, nsteps, ensemble, mode, nb, false));
-        TRY(maybe_export(c));
+        TRY(maybe_export(c, KAMD_DEV_LIST_OVERFLOW));
         bool redo = false;
-        const int rc = heal_list(c, redo);
+        int rc = heal_list(c, redo);
+        if (!rc && redo && attempt + 1 >= HEAL_ATTEMPTS)
+            rc = fail(c, KAMD_EDEVICE, "neighbour list still overflows after %d rebuilds", attempt + 1);
         if (rc) {
             (void)snapshot_restore(c);
-            (void)maybe_export(c);
             return rc;
         }
         if (!redo) return KAMD_OK;
-        if (attempt + 1 >= HEAL_ATTEMPTS)
-            return fail(c, KAMD_EDEVICE, "neighbour list still overflows after %d rebuilds", attempt + 1);
         TRY(snapshot_restore(c));
     }
 }
@@ -1605,7 +1607,7 @@ extern "C" int md_get_state(kamd_ctx *c, void *blob, size_t *bytes)
     const size_t nt = c->d.n_total;
     double *a[9];
     for (int k = 0; k < 9; ++k) a[k] = c->state_tmp + k * nt;
-    HIPCHK(c, launch_export(c->d, a, c->img_tmp, c->stream));
+    HIPCHK(c, launch_export(c->d, a, c->img_tmp, 0, c->stream));
     char *p = (char *)blob;
     BlobHeader h{BLOB_MAGIC, (int64_t)nt, (int64_t)c->reps.size(), c->step};
     std::memcpy(p, &h, sizeof h);
