@@ -1247,8 +1247,7 @@ __global__ __launch_bounds__(BLOCK, 5) void k_rb_list_masks(Dev d, int min_waves
         const int sub = half ? base : 0;   // entries are held as the list stores them
         const int padv = s - sub;          // padding: the own slot
         int cnt = 0;                       // entries accepted
-        int taken = 0;                     // of those, taken out of the queue
-        int emitted = 0;                   // entries of the list written (every lane's: a multiple of group)
+        int emitted = 0;                   // of those, written (a multiple of group)
         int qh = 0, qn = 0;                // queue: first entry, entries
         uint32_t ma = 0, mb = 0;           // the queue entry being taken apart
         int ent = 0;
@@ -1275,24 +1274,26 @@ __global__ __launch_bounds__(BLOCK, 5) void k_rb_list_masks(Dev d, int min_waves
             if (k < rows) *reinterpret_cast<int4 *>(col + (k >> 2) * 256) = v;
             emitted += group;
         };
-        auto emit = [&](int n) __attribute__((always_inline)) {  // n more entries of every lane's list
-#pragma unroll 1
-            for (int k = 0; k < n; k += group) {
-                int e[4];
+        auto emit = [&]() __attribute__((always_inline)) {  // the lane's next group of entries
+            int e[4];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    e[t] = take();
-                    if (half) e[t] |= take() << 16;
-                }
-                write(make_int4(e[0], e[1], e[2], e[3]));
+            for (int t = 0; t < 4; ++t) {
+                e[t] = take();
+                if (half) e[t] |= take() << 16;
             }
+            write(make_int4(e[0], e[1], e[2], e[3]));
         };
-        // The queue of some lane is full: as many entries as every lane has, or
-        // where one has none, all that there are (that lane's list is padded).
+        // The queue of some lane is full: as many groups as every lane has
+        // entries for or, where one has too few, one group of those that have
+        // (the full one among them: each entry of its queue holds a partner).
         auto make_room = [&]() __attribute__((always_inline)) {
-            const int have = -wave_max_all(real ? taken - cnt : -INT_MAX) & -group;
-            emit(have > 0 ? have : wave_max_all(cnt - taken));
-            taken = have > 0 ? taken + have : cnt;
+            const int have = -wave_max_all(real ? emitted - cnt : -INT_MAX);
+            if (have >= group) {
+#pragma unroll 1
+                for (int k = group; k <= have; k += group) emit();
+            } else if (cnt - emitted >= group) {
+                emit();
+            }
         };
         // slot ranges of one stencil row: main run and wrapped end cell
         auto bounds = [&](int oz, int oy) __attribute__((always_inline)) {
@@ -1364,13 +1365,14 @@ __global__ __launch_bounds__(BLOCK, 5) void k_rb_list_masks(Dev d, int min_waves
                 if (any_wrap) piece(cur.z, cur.w);
             }
         }
-        emit(wave_max_all(cnt - taken));
+        while (__any(emitted < cnt))
+            if (emitted < cnt) emit();
         total += cnt;
-        const int align = half ? 2 * LIST_ROW_ALIGN : LIST_ROW_ALIGN;  // whole 16-byte words
-        const int kmax = (emitted + align - 1) & -align;
+        const int kmax = (wave_max_all(cnt) + group - 1) & -group;  // whole 16-byte words
         const int words = half ? kmax / 2 : kmax;  // 32-bit words the part occupies
         const int pad = half ? padv | (padv << 16) : padv;
-        while (emitted < kmax) write(make_int4(pad, pad, pad, pad));
+        while (__any(emitted < kmax))
+            if (emitted < kmax) write(make_int4(pad, pad, pad, pad));
         if (row + words > rows && lane == 0) set_err(d.err, KAMD_DEV_LIST_OVERFLOW);
         kpart.x = tj == 0 ? kmax : kpart.x;
         kpart.y = tj == 1 ? kmax : kpart.y;
