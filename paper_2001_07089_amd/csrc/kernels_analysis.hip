@@ -280,11 +280,12 @@ __global__ __launch_bounds__(RDF_THREADS) void k_rdf_hist(Dev d, double dr, int 
     const double rp = rmax * (1.0 + 1e-9) + 1e-12 * L;
     const double rp2 = rp * rp;
     const double h = R.fx_to_len;
-    const float scale = (float)(h / dr);
-    // a replica with a position that is not finite: every pair by the definition
-    const bool odd = (g.w & RDF_NONFINITE) != 0;
-    const float eps = (float)fmin(0.5, 6e-7 * nbins + 2.5 * h / dr + 1e-6);
-    const float sure = odd || eps >= 0.5f ? -1.0f : 0.5f - eps;  // |fraction - 1/2| up to which the bin is certain
+    // every pair by the definition: a replica with a position that is not
+    // finite, and bins about as narrow as the fixed-point step
+    const double eps_d = 6e-7 * nbins + 2.5 * h / dr + 1e-6;
+    const bool odd = (g.w & RDF_NONFINITE) != 0 || !(eps_d < 0.5);
+    const float eps = (float)eps_d, scale = odd ? 0.0f : (float)(h / dr);
+    const float sure = odd ? -1.0f : 0.5f - eps;  // |fraction - 1/2| up to which the bin is certain
     const float lim = odd ? INFINITY : (float)nbins + eps;
     uint64_t *part = reinterpret_cast<uint64_t *>(scratch) + 9 * (int64_t)R.caller_off +
                      (int64_t)((int)blockIdx.x - plan.x) * row;
