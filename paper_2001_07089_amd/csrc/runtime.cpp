@@ -440,7 +440,8 @@ static void carve_fixed(Dev &d, CtxBufs &b, const Shape &z, Carve &k)
     d.obs = k.take<double>(8 * z.nrep);
     d.dyn = k.take<RepDyn>(z.nrep);
     d.err = k.take<uint32_t>(4);
-    d.counters = k.take<int32_t>(8);
+    d.counters = k.take<int32_t>(16);
+    b.cnt_snap = k.base ? d.counters + 8 : nullptr;
     b.Q_dev = k.take<double>(z.nrep);
     b.rep_arg = k.take<double>(z.nrep);
     b.obs_stage = k.take<double>(4 * z.nrep);
@@ -458,7 +459,6 @@ static void carve_fixed(Dev &d, CtxBufs &b, const Shape &z, Carve &k)
     b.img_tmp = k.take<int32_t>(3 * nt);
     b.id_snap = k.take<int32_t>(nt);
     b.dyn_snap = k.take<RepDyn>(z.nrep);
-    b.cnt_snap = k.take<int32_t>(8);
 }
 
 // The part that depends on the list parameters: per sub-cell counters, chains
