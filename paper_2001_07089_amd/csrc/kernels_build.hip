@@ -691,11 +691,10 @@ __device__ inline void copy_back(const Dev &d, int s, bool real, const uint4 &mi
 // parts whose windows fit are written in the window format; without it the
 // window code is compiled out.
 template <bool STAGE>
-__global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach, int min_waves)
+__global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach)
 {
     __shared__ int32_t stage[WAVES_PER_BLOCK][LIST_STAGE][WAVE];
     __shared__ __attribute__((aligned(16))) uint32_t win_s[WAVES_PER_BLOCK][3][LIST_WIN + LIST_UNROLL];
-    if (d.rb_any[0] < min_waves) return;  // nothing to do, or k_rb_list_wide's
     const int w = rb_work_wave(d);  // each XCD walks a contiguous part of the worklist
     if (w < 0) return;
     const SegInfo &S = d.seg[d.wave_seg[w]];
@@ -704,7 +703,6 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach, int min_wav
     const int lane = lane_id();
     const int s = w * WAVE + lane;
     const bool real = (s - S.slot0) < S.n;
-    const int np = d.npad_total;
     uint4 mi = make_uint4(0, 0, 0, 0);
     if (real) mi = d.smirror[s];
     copy_back(d, s, real, mi);
@@ -1788,39 +1786,42 @@ hipError_t launch_rb_sortgather(const Dev &d, hipStream_t s)
     hipLaunchKernelGGL(k_rb_sortgather, dim3(nblk_capped(d.nwaves)), dim3(BLOCK), 0, s, d);
     return hipGetLastError();
 }
-// Which list builder: the wide one for worklists of up to WIDE_WAVES waves
-// where it can build them (one cell per list radius, boxes of the coarse test,
-// replicas of up to 2^16 slots, no windows).  A single system rebuilds all its
-// waves or none, so only one of the two is launched; a batch launches both and
-// the worklist decides, except where its worklists are hardly ever that short
-// (the extra launch would cost the 256-replica batch 0.5%).
-// Measured (us per MIXED NVE step, k_rb_list, then wide): N = 1000 35.1, 23.7;
-// 32,000 (501 waves) 39.4, 30.9; 50,000 (782) 42.4, 39.0; 62,000 (970) 45.4,
-// 42.4; 64 replicas of 1000 under the bath (worklists of up to 1088) 101, 68.
-// Larger worklists keep one wavefront per list (the 256-replica batch, whose
-// worklists reach 4500 waves, 416 with either limit up to 1600, 496 with the wide
-// kernel alone), where it can be k_rb_list_masks.  With that one the line lies
-// lower for a single system, but hardly matters there (us per step, masks, then
-// wide: 40,000 32.7, 31.2; 50,000 34.7, 34.8; 62,000 35.7, 36.5; the bath 61.0,
-// 59.2).
-constexpr int WIDE_WAVES = 1100, WIDE_BATCH_WAVES = 8192;
+// Which list builder: the wide one for short worklists where it can build them
+// (one cell per list radius, boxes of the coarse test, replicas of up to 2^16
+// slots, no windows), k_rb_list_masks otherwise, k_rb_list for finer cells,
+// windows and larger boxes.
+//
+// A single system rebuilds all its waves or none, so only one of the two is
+// launched.  Measured (us per NVE step, masks / wide, MIXED and MIXED_FIXED):
+// 32,000 particles (501 waves) 28.6 / 25.1 and 27.0 / 23.5; 40,000 (626) 30.2 /
+// 29.0 and 30.0 / 28.7; 45,000 (704) 30.6 / 29.7 and 30.1 / 29.1; 50,000 (782)
+// 33.0 / 33.1 and 33.6 / 33.5; 55,000 (860) 33.1 / 33.6 and 33.2 / 33.7; 62,000
+// (970) 33.2 / 33.8 and 33.0 / 33.6.
+//
+// A batch launches both and the worklist decides, except where its worklists are
+// hardly ever that short (the extra launch would cost 256 replicas of 250 to 8000
+// particles 0.5%).  Limits of 800 / 1100 / 1280 / 1600: baths of 64 replicas of 1000
+// (worklists of up to 1088) 40.5 / 39.2 / 39.2 / 39.2, 75 (1275) 43.7 / 43.7 / 42.5 /
+// 42.5, 96 (1632) 53.4 / 53.9 / 54.0 / 54.2, 128 62.9 / 63.0 / 63.4 / 64.0; NVE of 10 x
+// 8000 (1260) 51.0 / 50.9 / 49.6 / 49.6, 16 x 8000 63.1 / 62.9 / 63.5 / 64.3, 256 x
+// 1000 104.0 / 104.8 / 107.3 / 110.4, 64 of 250 to 8000 114.0 / 114.3 / 115.0 / 119.6.
+constexpr int WIDE_WAVES = 768, WIDE_BATCH_LIST = 1280, WIDE_BATCH_WAVES = 8192;
 hipError_t launch_rb_list(const Dev &d, int cell_div, hipStream_t s)
 {
     const bool can = cell_div == 1 && !d.stage_ok && d.box_max <= COARSE_MAX_BOX && d.rep_waves_max <= 65536 / WAVE;
-    const bool wide = can && d.nwaves <= (d.nrep > 1 ? WIDE_BATCH_WAVES : WIDE_WAVES);
-    const bool rest = !wide || d.nwaves > WIDE_WAVES;
+    const int limit = d.nrep > 1 ? WIDE_BATCH_LIST : WIDE_WAVES;  // of a worklist
+    const bool wide = can && d.nwaves <= (d.nrep > 1 ? WIDE_BATCH_WAVES : limit);
     const int rows = d.dim == 2 ? 3 : LIST_ROWS;
     if (wide)
         hipLaunchKernelGGL(k_rb_list_wide, dim3(std::min(d.nwaves, WIDE_BLOCKS * (LIST_ROWS / rows))), dim3(WAVE * rows),
-                           0, s, d, WIDE_WAVES);
-    if (rest) {
-        const int least = wide ? WIDE_WAVES + 1 : 1;
+                           0, s, d, limit);
+    if (!wide || d.nwaves > limit) {
         if (cell_div == 1 && !d.stage_ok && d.box_max <= COARSE_MAX_BOX)
-            hipLaunchKernelGGL(k_rb_list_masks, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, least);
+            hipLaunchKernelGGL(k_rb_list_masks, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, wide ? limit + 1 : 1);
         else if (d.stage_ok)
-            hipLaunchKernelGGL(k_rb_list<true>, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, cell_div, least);
+            hipLaunchKernelGGL(k_rb_list<true>, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, cell_div);
         else
-            hipLaunchKernelGGL(k_rb_list<false>, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, cell_div, least);
+            hipLaunchKernelGGL(k_rb_list<false>, dim3(nblk_slots(d)), dim3(BLOCK), 0, s, d, cell_div);
     }
     return hipGetLastError();
 }
