@@ -178,11 +178,18 @@ def kernel_name(precision, windows=0, wg=256):  # at the headline's size
     then STAGE and waves per block for the unsplit mixed kernel, waves per list
     for the others."""
     if precision == "fp64":
-        return f"k_force_fp64<false,true,{wg // 64}>"
+        return "k_force_fp64<false,true,4>"  # four wavefronts share a list
     if precision == "mixed_fixed" and not windows:
         return "k_force_split<true,false,true,2>"  # two wavefronts share a list
     fixed = "true" if precision == "mixed_fixed" else "false"
     return f"k_force_mixed<{fixed},false,true,{'true' if windows else 'false'},{wg // 64}>"
+
+
+def kernel_threads(precision, windows=0, wg=256):
+    """Threads per block of that kernel: the setting, except where wavefronts share a list."""
+    if precision == "fp64" or (precision == "mixed_fixed" and not windows):
+        return 64 * int(kernel_name(precision, windows, wg)[:-1].rsplit(",", 1)[1])
+    return wg
 
 
 def source_digest():
@@ -756,7 +763,8 @@ def main():
         "data": "synthetic",
         "config": {"workload": wl.name, "n_atoms": n, "precision": a.precision, "dt": wl.dt,
                    "skin": st["skin"], "cell_div": int(st["cell_div"]), "step_kernel_windows": int(st["windows"]),
-                   "step_kernel_threads_per_block": int(st["wg_size"]), "init": init, "equil_steps": a.equil,
+                   "step_kernel_threads_per_block": kernel_threads(a.precision, int(st["windows"]), int(st["wg_size"])),
+                   "init": init, "equil_steps": a.equil,
                    "hip_graph": True, "parallelism": "single-gpu"},
         "drift": dict(drift, nve_steps=a.drift_steps, atom_steps_per_s=n * a.drift_steps / el_d),
         "rebuilds_per_step": prof["rebuilds"] / prof["steps"],

@@ -399,7 +399,7 @@ int md_set_force_kernel(kamd_ctx *ctx, int32_t windows, int32_t wg_size);
 /* Statistics: host_out (host, FP64 [14]) = {steps, rebuilds, n_total,
  * list_rows, mean_list_len, max_list_len, skin, cell_div, mean_list_bytes,
  * windows (the force-kernel variant), fraction of list parts gathered from a
- * window, step-kernel threads per block, mean_walked, skin_min (the smallest
+ * window, the block-size setting (md_set_force_kernel), mean_walked, skin_min (the smallest
  * skin a replica uses; see md_set_list_params)}.  List lengths count
  * partners at the last build (without wavefront padding); mean_list_bytes is
  * their stored size per particle (4 bytes per 32-bit entry, 2 per 16-bit

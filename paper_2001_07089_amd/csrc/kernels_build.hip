@@ -568,32 +568,6 @@ __global__ __launch_bounds__(BLOCK) void k_rb_gather(Dev d)
     }
 }
 
-// Neighbour lists.  One thread per particle.  Entries [0, kA) of a list hold
-// the particle's A partners, entries [kA, kA + kB) its B partners, where kA,
-// kB are the wavefront maxima rounded up to LIST_ROW_ALIGN.  The part of the
-// particle's own type also holds its own slot once (it passes the distance
-// test), and unused entries hold it too; the force kernels skip it (zero
-// separation).  Storage follows list_index: a particle appends 16 contiguous
-// bytes at a time, so cache lines fill completely before they leave the L2.
-//
-// The stencil is walked row by row: the cells of one stencil row differ only
-// in x and are consecutive in the cell-sorted slot order, so a row is one
-// contiguous slot range (two when it wraps around the box), scanned eight
-// candidates at a time.  With cells as wide as the list radius (reach 1) all
-// particles of a cell walk the same 27 cells in the same order, so the lanes
-// of a wavefront that share a cell load the same addresses and one cache-line
-// access serves all of them; no per-particle pruning is done there, since it
-// would break that sharing for little gain.  With finer cells (reach 2) rows,
-// and the end cells of a row, that lie farther than the list radius from the
-// particle are skipped (in FP64, with a margin), which removes most of the
-// 125-cell stencil.  Grids with fewer than 2*reach+1 cells per edge scan
-// whole rows.
-//
-// Candidate test in u32 fixed-point units: the integer difference of two
-// coordinates is the minimum-image separation (the box maps onto the full
-// 2^32 range), converted to float; rl2_fx is enlarged by a few parts in 10^6
-// so that the list is a superset of the exact one.  The sorted mirror has
-// LIST_UNROLL spare entries past its end, so the unrolled loads need no clamp.
 // Maximum of v over the 64 lanes of a wavefront whose lanes are all active:
 // a running maximum along each row of 16 lanes by DPP row shifts (a lane
 // with no source lane in its row keeps the identity), then the last lane of
@@ -632,6 +606,33 @@ __device__ inline double gap(int o, int c, double cw, double u)
     return o > 0 ? (c + o) * cw - u : (o < 0 ? u - (c + o + 1) * cw : 0.0);
 }
 
+// Neighbour lists.  One thread per particle.  Entries [0, kA) of a list hold
+// the particle's A partners, entries [kA, kA + kB) its B partners, where kA,
+// kB are the wavefront maxima rounded up to LIST_ROW_ALIGN.  The part of the
+// particle's own type also holds its own slot once (it passes the distance
+// test), and unused entries hold it too; the force kernels skip it (zero
+// separation).  Storage follows list_index: a particle appends 16 contiguous
+// bytes at a time, so cache lines fill completely before they leave the L2.
+//
+// The stencil is walked row by row: the cells of one stencil row differ only
+// in x and are consecutive in the cell-sorted slot order, so a row is one
+// contiguous slot range (two when it wraps around the box), scanned eight
+// candidates at a time.  With cells as wide as the list radius (reach 1) all
+// particles of a cell walk the same 27 cells in the same order, so the lanes
+// of a wavefront that share a cell load the same addresses and one cache-line
+// access serves all of them; no per-particle pruning is done there, since it
+// would break that sharing for little gain.  With finer cells (reach 2) rows,
+// and the end cells of a row, that lie farther than the list radius from the
+// particle are skipped (in FP64, with a margin), which removes most of the
+// 125-cell stencil.  Grids with fewer than 2*reach+1 cells per edge scan
+// whole rows.
+//
+// Candidate test in u32 fixed-point units: the integer difference of two
+// coordinates is the minimum-image separation (the box maps onto the full
+// 2^32 range), converted to float; rl2_fx is enlarged by a few parts in 10^6
+// so that the list is a superset of the exact one.  The sorted mirror has
+// LIST_UNROLL spare entries past its end, so the unrolled loads need no clamp.
+//
 // Accepted entries are staged in LDS, LIST_STAGE per lane, and written out
 // four at a time (one 16-byte store per lane) when some lane's stage fills.
 // Staging keeps stores out of the scan loop: on this architecture a wait for

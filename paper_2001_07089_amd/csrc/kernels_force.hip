@@ -699,6 +699,9 @@ __global__ __launch_bounds__(WAVE * P) void k_force_split(Dev d, Model m, int fl
 //                100,000      67.6, 58.9,    -, 61.0
 //                400,000       152,  145,    -,  148
 //                2^20          314,  319,    -,  357
+// Either side of 512 wavefronts, with the other kernels as they are now (P = 4,
+// 8): FP64 32,000 particles (501) 26.8, 26.6, 36,000 (563) 32.6, 34.2;
+// MIXED_FIXED 28,000 22.7, 22.3, 32,000 24.2, 23.6, 36,000 27.5, 31.8.
 // A whole md_forces call with energies, 100,000 / 200,000 particles: MIXED 115
 // -> 104 / 155 -> 154 us, MIXED_FIXED 114 -> 108 / 144 -> 139 us (2^20: slower).
 // Two wavefronts that share the lists of two (each closing one) measured 306
