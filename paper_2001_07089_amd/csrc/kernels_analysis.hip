@@ -473,12 +473,28 @@ __global__ __launch_bounds__(BLOCK) void k_msd_measure(Dev d, int slot)
 }
 
 // Self part of the van Hove function: per replica and species, the histogram
-// of |r_u - r_u(origin)| over particles, bin = int(r / dr) kept when
-// < n_bins.  A block takes a run of consecutive waves (a wave holds one replica
-// and one type) and counts into one u32 histogram in LDS, which it adds to the
-// uint64 result [n_rep][2][n_bins] whenever the replica or type changes and at
-// the end.  Bound by those 64-bit atomics, which all go to the same few lines:
-// one flush per 16 or more waves instead of one per wave took 262,147 particles
+// of |r_u - r_u(origin)| over particles, bin = int(r / dr) kept when < n_bins.
+// Particle of slot s (replica and type of S) into the histogram h.
+__device__ inline void vh_count(const Dev &d, const SegInfo &S, int s, int slot, double dr, int nbins, uint32_t *h)
+{
+    if (s - S.slot0 >= S.n) return;
+    const double L = d.rep[S.rep].L;
+    const int np = d.npad_total;
+    const int g = d.id[s];
+    const double *o = d.origin + (size_t)slot * 3 * d.n_total;
+    const double dx = d.x[s] + (double)d.img[s] * L - o[g];
+    const double dy = d.y[s] + (double)d.img[np + s] * L - o[d.n_total + g];
+    const double dz = d.z[s] + (double)d.img[2 * np + s] * L - o[2 * d.n_total + g];
+    const double r = sqrt(dx * dx + dy * dy + dz * dz);
+    const int bin = (int)(r / dr);
+    if (bin < nbins) atomicAdd(&h[bin], 1u);
+}
+
+// A block takes a run of consecutive waves (a wave holds one replica and one
+// type) and counts into one u32 histogram in LDS, which it adds to the uint64
+// result [n_rep][2][n_bins] whenever the replica or type changes and at the
+// end.  Bound by those 64-bit atomics, which all go to the same few lines: one
+// flush per 16 or more waves instead of one per wave took 262,147 particles
 // with 200 bins from 76 to 13.5 us.
 constexpr int VH_THREADS = 1024;
 constexpr int VH_BLOCKS = 256;
@@ -491,24 +507,9 @@ __global__ __launch_bounds__(VH_THREADS) void k_van_hove(Dev d, int slot, double
     for (int b = threadIdx.x; b < nbins; b += VH_THREADS) h[b] = 0u;
     __syncthreads();
     for (int w = w0; w < w1;) {  // block-uniform
-        const int sg = d.wave_seg[w];
-        const SegInfo &S = d.seg[sg];
+        const SegInfo &S = d.seg[d.wave_seg[w]];
         const int e = min(w1, (S.slot0 + S.npad) / WAVE);  // this segment's waves of the block
-        for (int q = w + wv; q < e; q += NW) {
-            const int s = q * WAVE + lane;
-            if (s - S.slot0 < S.n) {
-                const double L = d.rep[S.rep].L;
-                const int np = d.npad_total;
-                const int g = d.id[s];
-                const double *o = d.origin + (size_t)slot * 3 * d.n_total;
-                const double dx = d.x[s] + (double)d.img[s] * L - o[g];
-                const double dy = d.y[s] + (double)d.img[np + s] * L - o[d.n_total + g];
-                const double dz = d.z[s] + (double)d.img[2 * np + s] * L - o[2 * d.n_total + g];
-                const double r = sqrt(dx * dx + dy * dy + dz * dz);
-                const int bin = (int)(r / dr);
-                if (bin < nbins) atomicAdd(&h[bin], 1u);
-            }
-        }
+        for (int q = w + wv; q < e; q += NW) vh_count(d, S, q * WAVE + lane, slot, dr, nbins, h);
         __syncthreads();
         uint64_t *out = hist + ((size_t)S.rep * 2 + S.type) * nbins;
         for (int b = threadIdx.x; b < nbins; b += VH_THREADS)
@@ -518,6 +519,31 @@ __global__ __launch_bounds__(VH_THREADS) void k_van_hove(Dev d, int slot, double
             }
         __syncthreads();
         w = e;
+    }
+}
+
+// The same for small replicas, whose segments of a wave or a few the kernel
+// above would take one after the other: all waves of a block at once, with a
+// histogram in LDS for each segment that the block has waves of, at the place of
+// its first one.
+constexpr int VH_SMALL_WAVES = 8;
+__global__ __launch_bounds__(VH_SMALL_WAVES * WAVE) void k_van_hove_small(Dev d, int slot, double dr, int nbins,
+                                                                          uint64_t *hist)
+{
+    extern __shared__ uint32_t lh[];  // [VH_SMALL_WAVES][nbins]
+    const int wv = threadIdx.x / WAVE, lane = lane_id();
+    const int w0 = blockIdx.x * VH_SMALL_WAVES, w = w0 + wv;
+    for (int b = lane; b < nbins; b += WAVE) lh[wv * nbins + b] = 0u;
+    __syncthreads();
+    const SegInfo &S = d.seg[d.wave_seg[min(w, d.nwaves - 1)]];
+    const int first = max(S.slot0 / WAVE - w0, 0);  // of the segment's waves, in the block
+    if (w < d.nwaves) vh_count(d, S, w * WAVE + lane, slot, dr, nbins, lh + first * nbins);
+    __syncthreads();
+    if (w >= d.nwaves || first != wv) return;
+    uint64_t *out = hist + ((size_t)S.rep * 2 + S.type) * nbins;
+    for (int b = lane; b < nbins; b += WAVE) {
+        const uint32_t n = lh[wv * nbins + b];
+        if (n) atomicAdd((unsigned long long *)&out[b], (unsigned long long)n);
     }
 }
 
@@ -565,11 +591,23 @@ hipError_t launch_msd_measure(const Dev &d, int slot, hipStream_t s)
     return hipGetLastError();
 }
 
+// By the mean number of waves per segment.  Measured (us per call, calls in a row,
+// 200 bins, k_van_hove / small): 4096 replicas of 70 (1 wave) 36 / 7, 126 of 75 18 /
+// 5, 64 of 1000 (8.5) 6 / 5, 512 of 1000 10 / 11, 2000 of 1000 35 / 30, 64 of 2000 (16)
+// 5 / 5, 256 of 2000 9 / 12, 64 of 4000 (31) 8 / 9; one of 64,000 6 / 6.
+constexpr int VH_SMALL_SEG = 12;
 hipError_t launch_van_hove(const Dev &d, int slot, double dr, int nbins, uint64_t *hist, hipStream_t s)
 {
-    constexpr int nw = VH_THREADS / WAVE;  // at least one pass of the block's wavefronts per block
-    const int per = std::max(nw, (d.nwaves + VH_BLOCKS - 1) / VH_BLOCKS);
-    hipLaunchKernelGGL(k_van_hove, dim3((d.nwaves + per - 1) / per), dim3(VH_THREADS), 0, s, d, slot, dr, nbins, per, hist);
+    if (d.nwaves <= 2 * VH_SMALL_SEG * (int64_t)d.nrep) {
+        hipLaunchKernelGGL(k_van_hove_small, dim3((d.nwaves + VH_SMALL_WAVES - 1) / VH_SMALL_WAVES),
+                           dim3(VH_SMALL_WAVES * WAVE), sizeof(uint32_t) * VH_SMALL_WAVES * nbins, s, d, slot, dr, nbins,
+                           hist);
+    } else {
+        constexpr int nw = VH_THREADS / WAVE;  // at least one pass of the block's wavefronts per block
+        const int per = std::max(nw, (d.nwaves + VH_BLOCKS - 1) / VH_BLOCKS);
+        hipLaunchKernelGGL(k_van_hove, dim3((d.nwaves + per - 1) / per), dim3(VH_THREADS), 0, s, d, slot, dr, nbins, per,
+                           hist);
+    }
     return hipGetLastError();
 }
 
