@@ -169,6 +169,7 @@ struct Dev {
     int32_t dim;          // 3, or 2 for a planar system (z = vz = 0)
     int32_t ncells;
     int32_t rows;         // neighbour-list row capacity
+    int32_t list_len;     // expected entries of a particle's list (the densest replica's)
     double box_max;       // largest box edge
     int32_t rep_waves_max; // wavefronts of the largest replica
     int32_t sort_small;   // every replica within SORT_SLOTS and SORT_CELLS

@@ -29,6 +29,7 @@ struct Plan {
     std::vector<int32_t> wave_seg;
     int32_t npad = 0, nwaves = 0, ncells = 0, rows = 0, n_total = 0;
     int32_t scan_cps = 1;     // scan chunks of the largest segment
+    int32_t list_len = 0;     // expected entries of a particle's list (the densest replica's)
     int64_t ncells_wide = 0;  // the same count without 32-bit truncation
     bool fp64 = false;        // FP64 precision: two packed position buffers
 };
@@ -338,6 +339,7 @@ static void make_plan(const kamd_config *cfg, const kamd_replica *reps, int n_re
     P.npad = slot;
     P.nwaves = slot / WAVE;
     P.ncells = cell + (int32_t)P.segs.size();
+    P.list_len = (int32_t)std::min(std::ceil(rows_need), 1e9);
     int rows = std::max((int)std::ceil(cap * rows_need) + 32, rows_floor);
     rows = (rows + LIST_ROW_ALIGN - 1) / LIST_ROW_ALIGN * LIST_ROW_ALIGN;
     P.rows = rows;
@@ -582,6 +584,7 @@ static void bind_workspace(kamd_ctx *c, const Plan &P)
     for (const SegInfo &S : P.segs) d.sort_small = d.sort_small && (int64_t)CELL_SUBX * (2 * S.ncell + 1) <= SORT_CELLS;
     d.ncells = P.ncells;
     d.scan_cps = P.scan_cps;
+    d.list_len = P.list_len;
     d.rdf_cells_cap = (int64_t)c->shape.rdf_cells;
     d.stage_ok = c->cfg.precision != KAMD_PREC_FP64 && c->stage_windows;
     d.ring_cap = ring_rows(&c->cfg);
