@@ -703,16 +703,17 @@ __global__ __launch_bounds__(WAVE * P) void k_force_split(Dev d, Model m, int fl
 // 8): FP64 32,000 particles (501) 26.8, 26.6, 36,000 (563) 32.6, 34.2;
 // MIXED_FIXED 28,000 22.7, 22.3, 32,000 24.2, 23.6, 36,000 27.5, 31.8.
 // FP64 with short lists: four wavefronts find too few units.  300,000 particles
-// at densities 0.02, 0.1, 0.4, 0.6, 0.7 (2, 9, 34, 50, 59 entries expected), unsplit,
-// then P = 2, 4: 53.4, 50.5, 57.6; 57.4, 48.6, 56.7; 82.0, 64.0, 69.6; 95.9, 77.2, 79.1;
-// 104, 84.7, 83.6; 4096 x 70 (42 entries) 108.9, 94.6, 106.8; 60,000 at 0.3 and 0.6 32.5,
-// 24.4, 23.8 and 39.9, 27.2, 26.7.
+// at densities 0.02, 0.1, 0.2, 0.4, 0.6, 0.7 (2, 9, 17, 34, 50, 59 entries expected),
+// unsplit, then P = 1, 2, 4: 53.4, 45.9, 50.5, 57.6; 57.4, 46.5, 48.6, 56.7; 65.6, 56.5,
+// 53.5, 58.8; 82.0, 67.9, 64.0, 69.6; 95.9, -, 77.2, 79.1; 104, -, 84.7, 83.6; 4096 x 70 (42
+// entries) 108.9, 90.7, 94.6, 106.8; 60,000 at 0.02, 0.1, 0.6 25.3, 25.6, 27.1, 25.9;
+// 27.9, 24.6, 23.5, 24.2; 39.9, -, 27.2, 26.7.
 // A whole md_forces call with energies, 100,000 / 200,000 particles: MIXED 115
 // -> 104 / 155 -> 154 us, MIXED_FIXED 114 -> 108 / 144 -> 139 us (2^20: slower).
 // Two wavefronts that share the lists of two (each closing one) measured 306
 // (MIXED_FIXED) and 460 us (FP64) at 2^20; units of 4 entries 326 and 434.
 constexpr int SPLIT8_WAVES = 512, SPLIT4_WAVES = 1280, SPLIT_ORD_WAVES = 1024, SPLIT1_WAVES = 8192;
-constexpr int SPLIT_ORD_ENERGY_WAVES = 2048, SHORT_LIST = 54;
+constexpr int SPLIT_ORD_ENERGY_WAVES = 2048, SHORT_LIST = 54, TINY_LIST = 12;
 
 template <bool ENERGY, bool KD, int P>
 static void launch_fp64(const Dev &d, const Model &m, int flags, double dt, uint4 *mirror_out, uint32_t *md_out,
@@ -727,6 +728,8 @@ static void launch_fp64(const Dev &d, const Model &m, int flags, double dt, uint
                         double4 *pos4_out, hipStream_t s)
 {
     if (d.nwaves <= SPLIT8_WAVES) launch_fp64<ENERGY, KD, 8>(d, m, flags, dt, mirror_out, md_out, pos4_out, s);
+    else if (d.nwaves > SPLIT4_WAVES && d.list_len <= TINY_LIST)
+        launch_fp64<ENERGY, KD, 1>(d, m, flags, dt, mirror_out, md_out, pos4_out, s);
     else if (d.nwaves > SPLIT4_WAVES && d.list_len <= SHORT_LIST)
         launch_fp64<ENERGY, KD, 2>(d, m, flags, dt, mirror_out, md_out, pos4_out, s);
     else launch_fp64<ENERGY, KD, 4>(d, m, flags, dt, mirror_out, md_out, pos4_out, s);

@@ -1,5 +1,6 @@
 """FP64 forces of dilute systems: the number of wavefronts that share a list
-follows the expected length of the lists (54 entries) from 1280 wavefronts on.
+follows the expected length of the lists (12 and 54 entries) from 1280
+wavefronts on.
 Forces and energies against the oracle on either side, through a step and a
 rebuild, and one step of a call against the fused ones."""
 import numpy as np
@@ -12,8 +13,8 @@ from paper_2001_07089_amd import workload as W
 pytestmark = pytest.mark.gpu
 
 
-# 1250 wavefronts (four each, whatever the length), and 1594 with 2, 45 and 59 entries
-@pytest.mark.parametrize("n,rho", [(80000, 0.1), (102000, 0.02), (102000, 0.53), (102000, 0.7)])
+# 1250 wavefronts (four each, whatever the length), and 1594 with 2, 9, 17, 45 and 59 entries
+@pytest.mark.parametrize("n,rho", [(80000, 0.1), (102000, 0.02), (102000, 0.1), (102000, 0.2), (102000, 0.53), (102000, 0.7)])
 def test_fp64_forces_of_short_lists(n, rho):
     print(f"case short lists n={n} rho={rho}", flush=True)
     L = W.box_for(n, rho)
