@@ -606,6 +606,38 @@ __device__ inline double gap(int o, int c, double cw, double u)
     return o > 0 ? (c + o) * cw - u : (o < 0 ? u - (c + o + 1) * cw : 0.0);
 }
 
+// Base slot of a wavefront's 16-bit entries in the part of its own type (cells
+// from cell0 on): the lowest slot that its lanes' stencils and its own slots s
+// reach, if all of them lie within 2^16 of it; else -1.  All lanes take part.
+__device__ inline int own_base(const Dev &d, int cell0, int s, bool real, int cy, int cz, int reach, int noff, int oz0,
+                               int nz, int nc)
+{
+    int lo = s, hi = s + 1;
+    if (real) {
+        // lowest and highest stencil row (qz * nc + qy) in slot order; a range
+        // that wraps around the box covers both ends
+        int z0 = cz + oz0, z1 = cz + oz0 + nz - 1;
+        if (z0 < 0 || z1 >= nc) z0 = 0, z1 = nc - 1;
+        int y0 = cy - reach, y1 = cy - reach + noff - 1;
+        if (y0 < 0 || y1 >= nc) y0 = 0, y1 = nc - 1;
+        lo = min(lo, d.cell_start[CELL_SUBX * (cell0 + (z0 * nc + y0) * nc)]);
+        hi = max(hi, d.cell_start[CELL_SUBX * (cell0 + (z1 * nc + y1) * nc + nc)]);
+    }
+    lo = -wave_max_all(-lo);
+    hi = wave_max_all(hi);
+    return hi - lo <= 65536 ? lo : -1;
+}
+
+// Entries of the parts of a list (16-bit ones where `base` is not -1) cut to
+// the rows there are, so that the force kernels stay inside it.
+__device__ inline int2 cut_to_rows(int2 k, int2 base, int rows)
+{
+    const bool h0 = base.x != -1, h1 = base.y != -1;
+    const int w0 = min(h0 ? k.x / 2 : k.x, rows);
+    const int w1 = min(h1 ? k.y / 2 : k.y, rows - w0);
+    return make_int2(h0 ? 2 * w0 : w0, h1 ? 2 * w1 : w1);
+}
+
 // Neighbour lists.  One thread per particle.  Entries [0, kA) of a list hold
 // the particle's A partners, entries [kA, kA + kB) its B partners, where kA,
 // kB are the wavefront maxima rounded up to LIST_ROW_ALIGN.  The part of the
@@ -853,22 +885,7 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach)
         // the other part, as 32-bit slot indices.  base = -1 marks 32-bit
         // entries; staged windows use base 0.
         int base = staged ? 0 : -1;
-        if (!staged && tj == S.type && SJ.n > 0) {
-            int lo = s, hi = s + 1;
-            if (real) {
-                // lowest and highest stencil row (qz * nc + qy) in slot order;
-                // a range that wraps around the box covers both ends
-                int z0 = cz + oz0, z1 = cz + oz0 + nz - 1;
-                if (z0 < 0 || z1 >= nc) z0 = 0, z1 = nc - 1;
-                int y0 = cy - reach, y1 = cy - reach + noff - 1;
-                if (y0 < 0 || y1 >= nc) y0 = 0, y1 = nc - 1;
-                lo = min(lo, cs(SJ.cell0 + (z0 * nc + y0) * nc));
-                hi = max(hi, ce(SJ.cell0 + (z1 * nc + y1) * nc + nc - 1));
-            }
-            lo = -wave_max_all(-lo);
-            hi = wave_max_all(hi);
-            if (hi - lo <= 65536) base = lo;
-        }
+        if (!staged && tj == S.type && SJ.n > 0) base = own_base(d, SJ.cell0, s, real, cy, cz, reach, noff, oz0, nz, nc);
         const bool half = base >= 0;
         const int group = half ? 8 : 4;  // entries per 16-byte store
         auto pack = [&](int a, int b) __attribute__((always_inline)) { return (a - base) | ((b - base) << 16); };
@@ -1129,11 +1146,7 @@ __global__ __launch_bounds__(BLOCK) void k_rb_list(Dev d, int reach)
     }
     if (row > rows) {  // keep the force kernels inside the list
         if (lane == 0) atomicMax(&d.counters[3], row);  // the rows a healing rebuild must provide
-        const bool h0 = bpart.x >= 0 || bpart.x <= -2, h1 = bpart.y >= 0 || bpart.y <= -2;  // 16-bit parts
-        const int w0 = min(h0 ? kpart.x / 2 : kpart.x, rows);
-        const int w1 = min(h1 ? kpart.y / 2 : kpart.y, rows - w0);
-        kpart.x = h0 ? 2 * w0 : w0;
-        kpart.y = h1 ? 2 * w1 : w1;
+        kpart = cut_to_rows(kpart, bpart, rows);
     }
     if (lane == 0) {
         d.kmax[w] = kpart;
@@ -1227,20 +1240,7 @@ __global__ __launch_bounds__(BLOCK, 5) void k_rb_list_masks(Dev d, int min_waves
         const int cell0 = SJ.cell0;
         // base slot of 16-bit entries (the part of the own type), or -1
         int base = -1;
-        if (tj == S.type && SJ.n > 0) {
-            int lo = s, hi = s + 1;
-            if (real) {
-                int z0 = cz + oz0, z1 = cz + oz0 + nz - 1;
-                if (z0 < 0 || z1 >= nc) z0 = 0, z1 = nc - 1;
-                int y0 = cy - 1, y1 = cy - 1 + noff - 1;
-                if (y0 < 0 || y1 >= nc) y0 = 0, y1 = nc - 1;
-                lo = min(lo, cstart[CELL_SUBX * (cell0 + (z0 * nc + y0) * nc)]);
-                hi = max(hi, cend[CELL_SUBX * (cell0 + (z1 * nc + y1) * nc + nc) - 1]);
-            }
-            lo = -wave_max_all(-lo);
-            hi = wave_max_all(hi);
-            if (hi - lo <= 65536) base = lo;
-        }
+        if (tj == S.type && SJ.n > 0) base = own_base(d, cell0, s, real, cy, cz, 1, noff, oz0, nz, nc);
         const bool half = base >= 0;
         const int group = half ? 8 : 4;    // entries per 16-byte store
         const int sub = half ? base : 0;   // entries are held as the list stores them
@@ -1382,11 +1382,7 @@ __global__ __launch_bounds__(BLOCK, 5) void k_rb_list_masks(Dev d, int min_waves
     }
     if (row > rows) {  // keep the force kernels inside the list
         if (lane == 0) atomicMax(&d.counters[3], row);  // the rows a healing rebuild must provide
-        const bool h0 = bpart.x >= 0, h1 = bpart.y >= 0;  // 16-bit parts
-        const int w0 = min(h0 ? kpart.x / 2 : kpart.x, rows);
-        const int w1 = min(h1 ? kpart.y / 2 : kpart.y, rows - w0);
-        kpart.x = h0 ? 2 * w0 : w0;
-        kpart.y = h1 ? 2 * w1 : w1;
+        kpart = cut_to_rows(kpart, bpart, rows);
     }
     if (lane == 0) {
         d.kmax[w] = kpart;
@@ -1499,22 +1495,7 @@ __global__ __launch_bounds__(WAVE * LIST_ROWS) void k_rb_list_wide(Dev d, int ma
             }
         }
         // base slot of 16-bit entries (the part of the own type), or -1
-        int base = -1;
-        {
-            const SegInfo &SJ = d.seg[R.seg[S.type]];
-            int lo = s, hi = s + 1;
-            if (real) {
-                int z0 = cz + oz0, z1 = cz + oz0 + nz - 1;
-                if (z0 < 0 || z1 >= nc) z0 = 0, z1 = nc - 1;
-                int y0 = cy - 1, y1 = cy - 1 + noff - 1;
-                if (y0 < 0 || y1 >= nc) y0 = 0, y1 = nc - 1;
-                lo = min(lo, cstart[CELL_SUBX * (SJ.cell0 + (z0 * nc + y0) * nc)]);
-                hi = max(hi, cend[CELL_SUBX * (SJ.cell0 + (z1 * nc + y1) * nc + nc) - 1]);
-            }
-            lo = -wave_max_all(-lo);
-            hi = wave_max_all(hi);
-            if (hi - lo <= 65536) base = lo;
-        }
+        const int base = own_base(d, d.seg[R.seg[S.type]].cell0, s, real, cy, cz, 1, noff, oz0, nz, nc);
         // Unions over the lanes, staged one after the other while they fit;
         // longest range and chunks of each piece.  (The loops over the pieces
         // stay rolled: the kernel runs for some 20 us, and four copies of its
@@ -1718,10 +1699,7 @@ __global__ __launch_bounds__(WAVE * LIST_ROWS) void k_rb_list_wide(Dev d, int ma
                     set_err(d.err, KAMD_DEV_LIST_OVERFLOW);
                     atomicMax(&d.counters[3], used_rows);  // the rows a healing rebuild must provide
                 }
-                const int w0 = min(row1, rows);
-                const int w1 = min(h1 ? kpart.y / 2 : kpart.y, rows - w0);
-                kp.x = h0 ? 2 * w0 : w0;
-                kp.y = h1 ? 2 * w1 : w1;
+                kp = cut_to_rows(kpart, bpart, rows);
             }
             if (lane == 0) {
                 d.kmax[w] = kp;
