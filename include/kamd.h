@@ -354,9 +354,9 @@ int md_graph_capture(kamd_ctx *ctx, int32_t nsteps, int32_t ensemble, int32_t mo
 int md_graph_launch(kamd_ctx *ctx);
 
 /* Tuning of the list and of the step kernel, on a copy of the current state
- * that is restored afterwards.  A run of a candidate is probe_steps NVE steps,
- * or as many as take about 10 ms if that is more, replayed from a graph of up
- * to 100 steps after one warm-up replay.  Every candidate of a stage is run
+ * that is restored afterwards.  A run of a candidate is 3 probe_steps NVE
+ * steps, or as many as take about 30 ms if that is more, replayed from a graph
+ * of up to 100 steps after one warm-up replay.  Every candidate of a stage is run
  * once, those within 5% of the fastest then twice more in turn, and their
  * medians compared.  Stage 1 times each skin (0.2 .. min(0.5, L/2 - r_c,max))
  * with each cell division (1, 2) on the current step kernel; stage 2 times, at

@@ -1735,11 +1735,13 @@ extern "C" int md_autotune(kamd_ctx *c, int32_t probe_steps, double *host_out)
     // `chunk` steps: eager steps of a small system take about as long as the
     // host needs to launch them, and would time the host.  (A stream that
     // cannot be captured, the null stream, has its steps enqueued.)  The first
-    // chunk warms up and gives the rate; the timed ones make probe_steps
-    // steps, or as many as take about 10 ms if that is more (a run must see
-    // several list rebuilds, whose cost dominates the differences between
-    // candidates of a small system).  A candidate whose list overflows is
-    // skipped.
+    // chunk warms up and gives the rate; the timed ones make three times
+    // probe_steps steps, or as many as take about 30 ms if that is more.  Runs
+    // of a candidate repeat the same trajectory, so its rebuilds fall on the
+    // same steps each time: a run must see many of them for one more or less
+    // not to matter (2^20 particles: over 100 steps a skin of 0.25 came out 1%
+    // ahead of 0.3, over 1000 it is 2% behind).  A candidate whose list
+    // overflows is skipped.
     auto probe = [&](Cand &k) -> int {
         drop_graph(c);
         c->stage_windows = k.win;
@@ -1754,7 +1756,7 @@ extern "C" int md_autotune(kamd_ctx *c, int32_t probe_steps, double *host_out)
         double warm = 0.0, ms = 0.0;
         TRY(timed(1, warm));
         const double per = std::max(1e-4, warm / chunk);
-        const double steps = std::min(20000.0, std::max((double)probe_steps, std::ceil(10.0 / per)));
+        const double steps = std::min(60000.0, std::max(3.0 * probe_steps, std::ceil(30.0 / per)));
         const int n = (int)std::ceil(steps / chunk);
         TRY(timed(n, ms));
         uint32_t word = 0;
