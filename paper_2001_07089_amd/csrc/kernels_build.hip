@@ -31,7 +31,8 @@
 //                 position, write its neighbour list
 // Every kernel returns at once when the worklist is empty; the scan also
 // skips replicas whose flag is clear.  Plans of small replicas only run
-// everything before rb_list as one kernel (k_rb_sort_small).
+// everything before rb_list as one kernel (k_rb_sort_small; in batches of many
+// replicas after the gate).
 #include <climits>
 
 #include "common_dev.hpp"
