@@ -48,8 +48,9 @@ def _replay_ms(s):
 
 def test_pick_is_timed_on_the_device():
     """Four processes take turns of some milliseconds on one CPU: eager steps
-    would take about four times the launch time of one, 60 us or more; replays
-    21 us.  Half as much again is allowed for the clocks."""
+    take about four times their launch time, 34 us or more; a replay of 100 steps
+    takes the host 0.2 ms, four times that is well below the device's 2.1 ms.  A
+    quarter as much again is allowed for the clocks."""
     print("case autotune under host load", flush=True)
     s = _system(32000, "mixed_fixed")
     before = os.sched_getaffinity(0)
@@ -71,7 +72,7 @@ def test_pick_is_timed_on_the_device():
     ms = _replay_ms(s)
     print(f"  pick {pick}, replay {ms:.4f} ms", flush=True)
     sys.stdout.flush()
-    assert pick["ms_per_step"] <= 1.5 * ms
+    assert pick["ms_per_step"] <= 1.25 * ms
     s.close()
 
 
