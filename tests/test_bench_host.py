@@ -63,15 +63,3 @@ def test_traffic_records_parse_sections(tmp_path):
                  "### Record B\n- skin: 0.4\nprose\n- hbm_bytes_per_launch: 5\n")
     recs = bench.traffic_records(str(p))
     assert recs == [{"skin": "0.3", "kernel": "k<a>"}, {"skin": "0.4", "hbm_bytes_per_launch": "5"}]
-
-
-def test_step_kernel_and_its_block_whatever_the_block_size_setting():
-    """Kernels whose wavefronts share a list have blocks of their own; the
-    setting is that of the others."""
-    for wg in (64, 128, 256):
-        assert bench.kernel_name("fp64", 0, wg) == "k_force_fp64<false,true,4>"
-        assert bench.kernel_threads("fp64", 0, wg) == 256
-        assert bench.kernel_name("mixed_fixed", 0, wg) == "k_force_split<true,false,true,2>"
-        assert bench.kernel_threads("mixed_fixed", 0, wg) == 128
-        assert bench.kernel_threads("mixed_fixed", 1, wg) == wg
-        assert bench.kernel_threads("mixed", 0, wg) == wg

@@ -162,15 +162,3 @@ def test_log_schedule_matches_oracle_and_definition():
         md.md_log_schedule(0, 1.0, 60)
     with pytest.raises(md.KamdError):
         md.md_log_schedule(100, 0.2, 60)
-
-
-@pytest.mark.parametrize("prec,rep,kw,count,limit", [
-    ("mixed", (8, 6, 6.5, 1.0, 0), dict(cell_div=2), 1, 71424),
-    ("fp64", (2, 1, 5.01, 1.0, 0), {}, 1, 71424),
-    ("fp64", (1, 1, 9.0, 1.0, 0), dict(dim=2), 1, 41472),
-    ("mixed", (8, 6, 6.5, 1.0, 0), dict(cell_div=2), 300, 19367680),
-])
-def test_tiny_workspaces_fit_the_sizes_they_had(prec, rep, kw, count, limit):
-    """Callers may hold blocks of the sizes that md_workspace_size gave before
-    eager calls kept their starting state in slot order."""
-    assert md.md_workspace_size(md.make_config(prec, **kw), md.make_replicas([rep] * count)) <= limit
